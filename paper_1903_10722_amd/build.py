@@ -17,6 +17,7 @@ HIPCC_FLAGS = [
 ]
 
 
+PICK_PARTS = 6   # kernel families of csrc/ffs_pick.hip, one object each
 PROBE_LIB = os.path.join(BUILD, "liblds_probe.so")
 
 
@@ -25,19 +26,22 @@ def _run(cmd):
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compile csrc/ffs_api.hip and csrc/ffs_tt.hip (+ headers) into
-    _build/libffs.so, and csrc/lds_probe.hip (the benchmark's LDS bandwidth
-    probe) into _build/liblds_probe.so; always recompiles.  The sources are
-    compiled in parallel, then linked."""
+    """Compile csrc/ffs_api.hip, csrc/ffs_tt.hip and the kernel families of
+    csrc/ffs_pick.hip (+ headers) into _build/libffs.so, and
+    csrc/lds_probe.hip (the benchmark's LDS bandwidth probe) into
+    _build/liblds_probe.so; always recompiles.  The sources are compiled in
+    parallel, then linked."""
     os.makedirs(BUILD, exist_ok=True)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
     objs = []
     procs = []
-    for src in ("ffs_api.hip", "ffs_tt.hip"):
-        obj = os.path.join(BUILD, src.replace(".hip", ".o"))
+    parts = [("ffs_pick.hip", p) for p in range(PICK_PARTS)]
+    for src, part in [("ffs_api.hip", None), ("ffs_tt.hip", None), *parts]:
+        obj = os.path.join(BUILD, src.replace(".hip", ".o" if part is None else f"{part}.o"))
         objs.append(obj)
-        procs.append(_run([hipcc, *HIPCC_FLAGS, "-c", *inc, os.path.join(CSRC, src), "-o", obj]))
+        define = [] if part is None else [f"-DFFS_PART={part}"]
+        procs.append(_run([hipcc, *HIPCC_FLAGS, *define, "-c", *inc, os.path.join(CSRC, src), "-o", obj]))
     probe_tmp = PROBE_LIB + ".tmp"
     procs.append(_run([hipcc, *HIPCC_FLAGS, os.path.join(CSRC, "lds_probe.hip"), "-o", probe_tmp]))
     errs = []

@@ -20,6 +20,7 @@
 #include "ffs.h"
 #include "ffs_kernels.h"
 #include "ffs_lane.h"
+#include "ffs_pick.h"
 
 using namespace flowshop;
 
@@ -44,17 +45,46 @@ __global__ void __launch_bounds__(256) k_build_table(const int* __restrict__ p, 
     else reinterpret_cast<uint16_t*>(pT)[i] = (uint16_t)v;
 }
 
-// Completion shifts of the three-field decode key (completion, dispatch
-// index, job): the lane decode's where its completion field holds 1.5 times
-// the lower bound LB (makespans above it fall back to the two-field key),
-// the pipelined decode's where every completion (at most the sum E of all
-// processing times) fits, the key 0xFFFFFFFF staying padding; 0: not used.
-static void key_shifts(int jb, long long LB, long long E, int& fsh, int& psh)
+// Key formats of an instance's decodes.  No completion exceeds
+// UB = min(sum of all p, sum_k (floor(P_k / m_k) + pmax_k)): at a stage, a job
+// that waits finds every machine busy from its ready time with jobs dispatched
+// before it, so it starts at most floor(P_k / m_k) after it, and every ready
+// time is a completion of the stage before.  The pipelined decode's indexed
+// key holds UB below the padding's value (checked: 1.5 times the lower bound
+// LB; makespans above it fall back to the two-field key).  fsh: the lane
+// decode's completion shift of its three-field key, 0 if that is not used.
+struct DecodeKeys {
+    int fsh, pkey;
+};
+
+static DecodeKeys decode_keys(int n, int S, const int* m, const int* p, int jb, int mmax)
 {
-    const bool ok = 2 * jb <= 30;
-    const long long cap = ok ? (1ll << (32 - 2 * jb)) : 0;
-    fsh = (ok && 3 * LB < 2 * cap) ? 2 * jb : 0;
-    psh = (ok && E < cap - 1) ? 2 * jb : 0;
+    long long jobmax = 0, E = 0, LB = 0, UB = 0;
+    std::vector<long long> P(S, 0);
+    std::vector<int> pmax(S, 0);
+    for (int j = 0; j < n; ++j) {
+        long long sj = 0;
+        for (int k = 0; k < S; ++k) {
+            const int v = p[(size_t)j * S + k];
+            P[k] += v;
+            pmax[k] = std::max(pmax[k], v);
+            sj += v;
+        }
+        jobmax = std::max(jobmax, sj);
+        E += sj;
+    }
+    LB = jobmax;
+    for (int k = 0; k < S; ++k) {
+        LB = std::max(LB, (P[k] + m[k] - 1) / m[k]);
+        UB += P[k] / m[k] + pmax[k];
+    }
+    UB = std::min(UB, E);
+    DecodeKeys d;
+    const bool three = 2 * jb <= 30;
+    d.fsh = (three && 3 * LB < 2 * (1ll << (32 - 2 * jb))) ? 2 * jb : 0;
+    const long long cap = (1ll << (32 - jb - pipe_index_bits(mmax))) - 1;
+    d.pkey = UB < cap ? kKeyIdx : (3 * LB < 2 * cap ? kKeyIdxChecked : kKeyTwo);
+    return d;
 }
 
 namespace {
@@ -90,77 +120,7 @@ struct HostInstance {
     int lds_bucket = 0, cls = 0;  // its LDS class
 };
 
-using GenKernel = void (*)(const InstDesc*, const IslandDesc*, const WorkItem*, Control*, int, int, int, int);
-using EvalKernel = void (*)(const InstDesc*, const int*, int, int*, Control*);
-
-template <int M, typename PT>
-void* gen_ptr() { return reinterpret_cast<void*>(&k_generation<M, PT>); }
-template <int M, typename PT>
-void* eval_ptr() { return reinterpret_cast<void*>(&k_evaluate<M, PT>); }
-template <int M, typename PT>
-void* cand_ptr() { return reinterpret_cast<void*>(&k_candidates<M, PT>); }
-template <int M, typename PT>
-void* gen_lane_ptr() { return reinterpret_cast<void*>(&k_generation_lane<M, PT>); }
-template <int M, typename PT>
-void* eval_lane_ptr() { return reinterpret_cast<void*>(&k_evaluate_lane<M, PT>); }
-
 const int kMmaxList[] = {2, 3, 4, 5, 6, 8, 16};
-
-void* pick_gen(int mm, int ptb)
-{
-#define FFS_CASE(M)                                                          \
-    if (mm == M) return ptb == 1 ? gen_ptr<M, uint8_t>() : gen_ptr<M, uint16_t>();
-    FFS_CASE(2) FFS_CASE(3) FFS_CASE(4) FFS_CASE(5) FFS_CASE(6) FFS_CASE(8) FFS_CASE(16)
-#undef FFS_CASE
-    return nullptr;
-}
-
-void* pick_cand_features(int sm, int ptb)
-{
-#define FFS_CASE(SM)                                                                             \
-    if (sm == SM) return ptb == 1 ? reinterpret_cast<void*>(&k_cand_features<SM, uint8_t>)      \
-                                  : reinterpret_cast<void*>(&k_cand_features<SM, uint16_t>);
-    FFS_CASE(8) FFS_CASE(16) FFS_CASE(20) FFS_CASE(24) FFS_CASE(32)
-#undef FFS_CASE
-    return nullptr;
-}
-
-void* pick_cand(int mm, int ptb)
-{
-#define FFS_CASE(M)                                                          \
-    if (mm == M) return ptb == 1 ? cand_ptr<M, uint8_t>() : cand_ptr<M, uint16_t>();
-    FFS_CASE(2) FFS_CASE(3) FFS_CASE(4) FFS_CASE(5) FFS_CASE(6) FFS_CASE(8) FFS_CASE(16)
-#undef FFS_CASE
-    return nullptr;
-}
-
-void* pick_eval(int mm, int ptb)
-{
-#define FFS_CASE(M)                                                          \
-    if (mm == M) return ptb == 1 ? eval_ptr<M, uint8_t>() : eval_ptr<M, uint16_t>();
-    FFS_CASE(2) FFS_CASE(3) FFS_CASE(4) FFS_CASE(5) FFS_CASE(6) FFS_CASE(8) FFS_CASE(16)
-#undef FFS_CASE
-    return nullptr;
-}
-
-// Lane-mapping kernels exist for machine counts up to 8.
-void* pick_gen_lane(int mm, int ptb)
-{
-#define FFS_CASE(M)                                                          \
-    if (mm == M) return ptb == 1 ? gen_lane_ptr<M, uint8_t>() : gen_lane_ptr<M, uint16_t>();
-    FFS_CASE(2) FFS_CASE(3) FFS_CASE(4) FFS_CASE(5) FFS_CASE(6) FFS_CASE(8)
-#undef FFS_CASE
-    return nullptr;
-}
-
-void* pick_eval_lane(int mm, int ptb)
-{
-#define FFS_CASE(M)                                                          \
-    if (mm == M) return ptb == 1 ? eval_lane_ptr<M, uint8_t>() : eval_lane_ptr<M, uint16_t>();
-    FFS_CASE(2) FFS_CASE(3) FFS_CASE(4) FFS_CASE(5) FFS_CASE(6) FFS_CASE(8)
-#undef FFS_CASE
-    return nullptr;
-}
 
 // Below this many individuals in a context the lane mapping leaves most
 // SIMDs idle (one wave per 64 individuals), and the per-stage lane mapping
@@ -981,7 +941,7 @@ int launch_eval(ffs_ctx* c, int inst, const int32_t* perms, int count, int32_t* 
     const int per_block = c->wpb * (lane ? kWave : I.G);
     const int blocks = (count + per_block - 1) / per_block;
     const size_t lds = align16((size_t)I.S * ((size_t)I.n_pad * c->ptb + 4)) +
-                       (size_t)c->wpb * (lane ? I.lane_wlds_eval : wave_lds_bytes(I.G, I.n_pad));
+                       (size_t)c->wpb * (lane ? I.lane_wlds_eval : (size_t)I.G * eval_stride(I.n_pad) * 2);
     void* args[] = {(void*)&di, (void*)&perms, (void*)&count, (void*)&out, (void*)&ctl};
     HIP_TRY(c, hipLaunchKernel(lane ? kl : c->keval, dim3(blocks), dim3(64 * c->wpb), args, lds, c->stream));
     return FFS_OK;
@@ -1440,7 +1400,9 @@ int ffs_bind_workspace(ffs_ctx* c, void* dptr, size_t bytes)
         d.n_pad = I.n_pad;
         d.jb = I.jb;
         d.G = I.G;
-        key_shifts(I.jb, I.LB, I.E, d.fsh, d.psh);
+        const DecodeKeys dk = decode_keys(I.n, I.S, I.m.data(), I.p.data(), I.jb, c->mm);
+        d.fsh = dk.fsh;
+        d.pkey = dk.pkey;
         d.island0 = isl_base;
         d.n_islands = (int)I.isl.size();
         d.interval = (I.isl.size() >= 2) ? I.cfg.migration_interval : 0;
@@ -2114,21 +2076,9 @@ int ffs_evaluate_noalloc(void* hip_stream, int32_t n, int32_t S, const int32_t* 
     d.S = S;
     d.n_pad = n_pad;
     d.jb = jb;
-    {
-        // lower bound: the longest job, and every stage's work over its machines
-        long long LB = 0;
-        for (int j = 0; j < n; ++j) {
-            long long sj = 0;
-            for (int k = 0; k < S; ++k) sj += p[(size_t)j * S + k];
-            LB = std::max(LB, sj);
-        }
-        for (int k = 0; k < S; ++k) {
-            long long pk = 0;
-            for (int j = 0; j < n; ++j) pk += p[(size_t)j * S + k];
-            LB = std::max(LB, (pk + machines[k] - 1) / machines[k]);
-        }
-        key_shifts(jb, LB, E, d.fsh, d.psh);
-    }
+    const DecodeKeys dk = decode_keys(n, S, machines, p, jb, mm);
+    d.fsh = dk.fsh;
+    d.pkey = dk.pkey;
     d.G = std::min(kWave / S, std::max(1, 32768 / (2 * group_stride(n_pad))));
     d.msum = msum;
     for (int k = 0; k < S; ++k) d.mach[k] = machines[k];
@@ -2140,7 +2090,7 @@ int ffs_evaluate_noalloc(void* hip_stream, int32_t n, int32_t S, const int32_t* 
     void* kern = lane ? kl : pick_eval(mm, ptb);
     if (!kern) return FFS_EUNSUPPORTED;
     const size_t lds = align16((size_t)S * ((size_t)n_pad * ptb + 4)) +
-                       (size_t)wpb * (lane ? (size_t)d.lane_wlds_eval : wave_lds_bytes(d.G, n_pad));
+                       (size_t)wpb * (lane ? (size_t)d.lane_wlds_eval : (size_t)d.G * eval_stride(n_pad) * 2);
     int max_lds = 0;
     if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
         return FFS_EDEVICE;

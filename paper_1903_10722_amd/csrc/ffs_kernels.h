@@ -6,11 +6,8 @@
 //   * decode (paper Section 3 problem; list-scheduling rule documented in
 //     include/ffs.h) runs as a systolic pipeline along the group: the lane of
 //     stage k keeps the m_k machine-free times of its stage, sorted, in
-//     registers, dispatches one job per step and releases finished jobs, in
-//     (completion, dispatch order), through a small LDS ring to stage k+1.
-//     A job can be released once the stage has started a later job at or
-//     after its completion time: later starts never decrease and every
-//     processing time is >= 1, so no later completion can precede it.
+//     registers, dispatches one job per step and hands the job it takes off
+//     the list, in (completion, dispatch order), to the lane of stage k+1.
 //   * the genetic operators (Section 4.1-4.2: neighbourhood choice, order
 //     crossover, swap mutation, complementary pairs) run on the same group of
 //     lanes on chromosomes staged in LDS; the crossover's fill uses a wave
@@ -51,7 +48,7 @@ struct InstDesc {
     int inst_id;
     int n, S, n_pad, jb, G;
     int fsh;                     // lane decode: completion shift of the three-field key (2 jb), 0: not used
-    int psh;                     // pipelined decode: the same where every completion fits, 0: not used
+    int pkey;                    // pipelined decode: KeyFormat
     int island0, n_islands;
     int interval, topology;
     // learned pre-screen (surr_k > 1): candidate streams per cell, replay ring
@@ -260,16 +257,13 @@ __device__ __forceinline__ void row_l2g(uint16_t* dst, const uint16_t* src, int 
 }
 
 // ---- pipelined decode -----------------------------------------------------
-// Value of `x` held by lane - 1 (whole-wave shift right by one lane, DPP;
-// lane 0 reads 0).
+// Value of `x` held by lane - 1 (whole-wave rotation by one lane, DPP; lane 0
+// reads lane 63).
 __device__ __forceinline__ uint32_t from_prev_lane(uint32_t x)
 {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x138 /* wave_shr:1 */, 0xF, 0xF, true);
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x13C /* wave_ror:1 */, 0xF, 0xF, true);
 }
 
-// One step of stage k (see decode_pipelined).  With PRED the lane acts only
-// while rel < n_act and takes a job only while rel < n; without it the caller
-// guarantees both for every lane that matters.
 // Median of three unsigned words (one VALU operation).
 __device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c)
 {
@@ -278,75 +272,124 @@ __device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c)
     return r;
 }
 
-// Key formats: F = false, completion << jb | job, a new key entering after
-// the entries of equal completion by a threshold compare per entry; F =
-// true, completion << sh | dispatch index << jb | job (sh = 2 jb, the
-// dispatch index counting stage k's dispatches, dsh = that index << jb), whose
-// numeric order is (completion, dispatch order), so the new key enters by
-// one min, median or max per entry.
-template <int MMAX, bool PRED, bool F, typename PT>
-__device__ __forceinline__ void pipe_step(uint32_t (&key)[MMAX], uint32_t& o_key, uint32_t& o_p, uint32_t& pn_pre,
-                                          uint32_t ap, uint32_t rel, uint32_t n_act, uint32_t un, bool first,
-                                          uint32_t jb, uint32_t jmask, const PT* prow_next, uint32_t sh,
-                                          uint32_t dsh)
+// Key formats of the decodes (InstDesc::pkey, lkey), both with the completion
+// time in the high bits:
+//   kKeyTwo: completion << jb | job; a new key enters after the entries of
+//     equal completion by a threshold compare per entry (3 M operations for a
+//     list of M);
+//   kKeyIdx: completion << (jb + IB) | index << jb | job; the keys of one list
+//     are distinct and their numeric order is (completion, dispatch order), so
+//     a new key enters by one min, max or median per entry (M operations).
+//     The index only has to order the entries of one list, so it is local to a
+//     block of consecutive dispatches: at a block's start the list's entries
+//     are renumbered by their place (0, 1, ...), and the block's dispatches
+//     take the indices after them.  IB bits hold both, whatever the number of
+//     jobs (a dispatch index of the whole stage would take jb bits and leave
+//     12 for the completion at 1000 jobs; this leaves 18);
+//   kKeyIdxChecked: the same, and the largest completion is kept, since the
+//     instance's completions may outgrow the field: the wave then decodes
+//     again with kKeyTwo.
+enum KeyFormat { kKeyTwo = 0, kKeyIdx = 1, kKeyIdxChecked = 2 };
+
+// The pipelined decode's blocks are eight steps: the list takes the indices
+// below 8 (16 with up to 16 machines), the block's dispatches the next eight.
+constexpr int kPipeBlock = 8;
+constexpr int pipe_first(int mmax) { return mmax <= 8 ? 8 : 16; }
+constexpr int pipe_index_bits(int mmax) { return mmax <= 8 ? 4 : 5; }
+
+// LDS views of generic pointers, for code behind a call: accesses through
+// them compile to LDS (not flat) instructions.
+template <typename T>
+using lds_ptr = const __attribute__((address_space(3))) T*;
+template <typename T>
+__device__ __forceinline__ lds_ptr<T> as_lds(const T* p)
+{
+    return (lds_ptr<T>)p;
+}
+
+// What one lane of the pipelined decode is given.
+template <typename PT>
+struct PipeLane {
+    lds_ptr<uint16_t> feed_row;  // the permutation that this lane feeds (in bounds on every lane)
+    lds_ptr<PT> prow;            // processing times it looks up: the next stage's, the first stage's if it feeds
+    bool feed;                   // this lane feeds the next group
+    int k;                       // its stage
+};
+
+// One step of stage k (see decode_pipe).  With PRED the lane inserts
+// nothing while rel >= n_act (the key it removed goes back in: the list stays
+// as it is), padding while rel >= n, and a job below that; without PRED the
+// caller guarantees that every lane that matters takes a job.
+template <int MMAX, bool PRED, int KEY, typename PT>
+__device__ __forceinline__ void pipe_step(uint32_t (&key)[MMAX], uint32_t& o_key, uint32_t& o_p, uint32_t& nx_key,
+                                          uint32_t& pn, uint32_t feed_gene, uint32_t rel, uint32_t n_act,
+                                          uint32_t un, bool feed, uint32_t sh, uint32_t jmask, lds_ptr<PT> prow,
+                                          uint32_t idx, uint32_t& cmx)
 {
     constexpr uint32_t PAD = 0xFFFFFFFFu;
     const uint32_t in_key = from_prev_lane(o_key);
     const uint32_t in_p = from_prev_lane(o_p);
-    if (!PRED || rel < n_act) {
-        const bool have = !PRED || rel < un;
-        // stage 0 takes its job word (p << jb | job) from AP, the others the
-        // handed-on key and processing time
-        const uint32_t x = first ? ap : in_key;
-        const uint32_t j = x & jmask;
-        const uint32_t o = key[0];
+    const bool have = !PRED || rel < un;
+    const bool act = !PRED || rel < n_act;
+    const uint32_t o = key[0];
+    // start = max(machine free, job ready): the larger key has the larger (or
+    // equal) time in its high bits
+    const uint32_t mx = o > in_key ? o : in_key;
+    const uint32_t c = (mx >> sh) + in_p;
+    if (KEY == kKeyTwo) {
+        uint32_t nk = (c << sh) | (in_key & jmask), ithr = (c + 1u) << sh;
+        if (PRED) {
+            nk = have ? nk : PAD;
+            nk = act ? nk : o;
+            ithr = have ? ithr : PAD;
+            ithr = act ? ithr : 0u;
+        }
         uint32_t nkey[MMAX];
-        if (F) {
-            const uint32_t mx = first ? o : (o > in_key ? o : in_key);
-            const uint32_t pj = first ? (ap >> jb) : in_p;
-            const uint32_t c = (mx >> sh) + pj;
-            const uint32_t nk = have ? ((c << sh) | dsh | j) : PAD;
-            if (MMAX == 1) {
-                nkey[0] = nk;
-            } else {
-                nkey[0] = key[1 < MMAX ? 1 : 0] < nk ? key[1 < MMAX ? 1 : 0] : nk;
+        bool prev = true;
 #pragma unroll
-                for (int i = 1; i + 1 < MMAX; ++i) nkey[i] = umed3(key[i], nk, key[i + 1]);
-                nkey[MMAX - 1] = key[MMAX - 1] > nk ? key[MMAX - 1] : nk;
-            }
-        } else {
-            const uint32_t hi = x >> jb;
-            const uint32_t r = first ? 0u : hi;
-            const uint32_t pj = first ? hi : in_p;
-            const uint32_t f = o >> jb;
-            const uint32_t st = f > r ? f : r;
-            const uint32_t c = st + pj;
-            const uint32_t nk = have ? ((c << jb) | j) : PAD;
-            const uint32_t ithr = have ? ((c + 1u) << jb) : PAD;
-            bool prev = true;
-#pragma unroll
-            for (int i = 0; i < MMAX; ++i) {
-                const bool lt = (i + 1 < MMAX) ? (key[(i + 1 < MMAX) ? i + 1 : i] < ithr) : false;
-                nkey[i] = lt ? key[(i + 1 < MMAX) ? i + 1 : i] : (prev ? nk : key[i]);
-                prev = lt;
-            }
+        for (int i = 0; i < MMAX; ++i) {
+            const bool lt = (i + 1 < MMAX) ? (key[(i + 1 < MMAX) ? i + 1 : i] < ithr) : false;
+            nkey[i] = lt ? key[(i + 1 < MMAX) ? i + 1 : i] : (prev ? nk : key[i]);
+            prev = lt;
         }
 #pragma unroll
         for (int i = 0; i < MMAX; ++i) key[i] = nkey[i];
-        o_key = o;
-        o_p = pn_pre;
+    } else {
+        uint32_t nk = (c << sh) | ((in_key & jmask) | idx);
+        if (KEY == kKeyIdxChecked) {
+            const uint32_t cc = (PRED && !have) ? 0u : c;
+            cmx = cc > cmx ? cc : cmx;
+        }
+        if (PRED) {
+            nk = have ? nk : PAD;
+            nk = act ? nk : o;
+        }
+        if (MMAX == 1) {
+            key[0] = nk;
+        } else {
+            uint32_t nkey[MMAX];
+            nkey[0] = key[1 < MMAX ? 1 : 0] < nk ? key[1 < MMAX ? 1 : 0] : nk;
+#pragma unroll
+            for (int i = 1; i + 1 < MMAX; ++i) nkey[i] = umed3(key[i], nk, key[i + 1]);
+            nkey[MMAX - 1] = key[MMAX - 1] > nk ? key[MMAX - 1] : nk;
+#pragma unroll
+            for (int i = 0; i < MMAX; ++i) key[i] = nkey[i];
+        }
     }
-    // every lane holds real jobs while all stages dispatch, so only the
-    // predicated fill and drain steps clamp the index
-    const uint32_t q = key[0] & jmask;
-    pn_pre = (uint32_t)prow_next[PRED ? min(q, un - 1u) : q];
+    // handed on in the next step: the key removed next and its job's time at
+    // the next stage, whose read has a whole step to arrive; a feeding lane
+    // hands on the next gene but one and its time at the first stage
+    o_key = nx_key;
+    o_p = pn;
+    nx_key = feed ? feed_gene : key[0];
+    pn = (uint32_t)prow[nx_key & jmask];
 }
 
 // One group of S lanes decodes one permutation; lane k runs stage k.
 //
-// Stage k keeps its m_k machine-free times as a sorted list of keys (one of
-// pipe_step's two formats) in registers; a machine that has not run a job yet
-// holds key 0, a padding entry (fewer than MMAX machines) 0xFFFFFFFF.  Each
+// Stage k keeps its m_k machine-free times as a sorted list of keys (see
+// KeyFormat) in registers; a machine that has not run a job yet holds
+// completion 0, a padding entry (fewer than MMAX machines) all ones.  Each
 // step dispatches the next job: it takes the machine of entry 0 (free first;
 // ties on time only relabel machines), starts at max(free, ready) and inserts
 // its completion.  The removed entry 0 is handed to stage k+1: entries leave
@@ -362,17 +405,36 @@ __device__ __forceinline__ void pipe_step(uint32_t (&key)[MMAX], uint32_t& o_key
 // The decode therefore runs exactly n + sum_{k<S-1} (m_k + 1) steps, and a
 // job handed on in one step is taken by the next lane in the next step, so
 // one register pair per lane carries it: (key, processing time at k+1).
-// In steps [a_{S-1}, n) every stage is dispatching, so that stretch runs
-// without per-lane predication; lanes of unused groups then compute values
-// nobody reads (their loads stay in bounds).
 //
-// AP[t] = (p[job][0] << jb) | job for the permutation's t-th job.  Returns
-// the makespan on the lane of the last stage.
-template <int MMAX, bool F, typename PT>
-__device__ __forceinline__ uint32_t decode_pipelined_keys(const uint32_t* AP, const PT* prow_next, const int* mach,
-                                                          int k, int S, int n, int jb, bool active)
+// Stage 0 takes its jobs the same way: the lane before it, whose own stage is
+// the last one and hands nothing on (lane 63 for group 0), feeds it the
+// permutation's genes, each with completion 0 and its time at the first
+// stage.  So every lane runs the same instructions, without selects for the
+// first stage and without a table of (time, job) words built beforehand, and
+// the permutation's 16-bit row is all a group keeps in LDS: 14 + M / 8 VALU
+// operations a step for lists of M = 4, from about 31, and a third of the LDS.
+// What bounds it: the chain of a step, about 15 dependent VALU operations and
+// the table read that the next step waits for, when a SIMD holds one or two
+// waves; VALU issue beyond that.  ffs_evaluate, from the version with table
+// words and two-field keys: a million rows of 100 jobs and 5 stages 562 ->
+// 376 us, 4099 rows of 1000 jobs and 20 stages 275 -> 147 us (one round of
+// workgroups instead of two).
+//
+// Steps run in blocks of eight.  A block in which every stage dispatches in
+// every step runs without predication; lanes of unused groups then compute
+// values nobody reads (a job index never exceeds jmask, so their reads stay
+// inside the workgroup's LDS: prow reaches at most 2 n entries into a table
+// that the groups' rows follow).
+//
+// Returns the makespan on the lane of the last stage; cmx receives the
+// largest completion (kKeyIdxChecked).
+template <int MMAX, int KEY, typename PT>
+__device__ __forceinline__ uint32_t decode_pipe(const PipeLane<PT>& pl, const int* mach, int S, int n, int n_pad,
+                                                int jb, uint32_t& cmx)
 {
     constexpr uint32_t PAD = 0xFFFFFFFFu;
+    constexpr int IB = pipe_index_bits(MMAX), NB0 = pipe_first(MMAX);
+    const int k = pl.k;
     int a_k = 0, total = n;
     for (int i = 0; i + 1 < S; ++i) {
         const int step = mach[i] + 1;
@@ -381,96 +443,103 @@ __device__ __forceinline__ uint32_t decode_pipelined_keys(const uint32_t* AP, co
     }
     const int a_last = total - n;
     const int mstage = mach[k];
+    const bool feed = pl.feed;
+    const uint32_t jmask = (1u << jb) - 1u;
+    const uint32_t sh = (uint32_t)(KEY == kKeyTwo ? jb : jb + IB);
+    const uint32_t keep = ~(((1u << IB) - 1u) << jb);
+    const uint32_t un = (uint32_t)n;
+    const uint32_t n_act = (k == S - 1) ? un : un + (uint32_t)mstage;
     uint32_t key[MMAX];
 #pragma unroll
     for (int i = 0; i < MMAX; ++i) key[i] = (i < mstage) ? 0u : PAD;
-    uint32_t o_key = 0, o_p = 0;
-    const bool first = (k == 0), last = (k == S - 1);
-    const uint32_t jmask = (1u << jb) - 1u;
-    const uint32_t ujb = (uint32_t)jb;
-    const uint32_t un = (uint32_t)n;
-    const uint32_t n_act = active ? (last ? un : un + (uint32_t)mstage) : 0u;
-    uint32_t pn_pre = (uint32_t)prow_next[0];
-    // three-field keys: the dispatch index of step it is it - a_k
-    const uint32_t sh = 2u * ujb, dstep = 1u << ujb;
-    uint32_t dsh = F ? (uint32_t)(0 - a_k) << ujb : 0u;
-    // the steady stretch starts on a multiple of 4 so that its job words can
-    // be read four at a time (AP is 16-byte aligned)
-    const int steady0 = (a_last + 3) & ~3;
-    const int fill_end = steady0 < n ? steady0 : n;
-    int it = 0;
-    for (; it < fill_end; ++it) {
-        pipe_step<MMAX, true, F, PT>(key, o_key, o_p, pn_pre, AP[it], (uint32_t)(it - a_k), n_act, un, first, ujb,
-                                     jmask, prow_next, sh, dsh);
-        dsh += dstep;
-    }
-    if (it + 3 < n) {
-        uint4 cur = *reinterpret_cast<const uint4*>(AP + it);
-        for (; it + 3 < n; it += 4) {
-            const int nx = (it + 7 < n) ? it + 4 : it;
-            const uint4 nxt = *reinterpret_cast<const uint4*>(AP + nx);
-            asm volatile("" ::: "memory");   // keep the read ahead of the four steps
-            pipe_step<MMAX, false, F, PT>(key, o_key, o_p, pn_pre, cur.x, 0u, 0u, un, first, ujb, jmask, prow_next,
-                                          sh, dsh);
-            pipe_step<MMAX, false, F, PT>(key, o_key, o_p, pn_pre, cur.y, 0u, 0u, un, first, ujb, jmask, prow_next,
-                                          sh, dsh + dstep);
-            pipe_step<MMAX, false, F, PT>(key, o_key, o_p, pn_pre, cur.z, 0u, 0u, un, first, ujb, jmask, prow_next,
-                                          sh, dsh + 2u * dstep);
-            pipe_step<MMAX, false, F, PT>(key, o_key, o_p, pn_pre, cur.w, 0u, 0u, un, first, ujb, jmask, prow_next,
-                                          sh, dsh + 3u * dstep);
-            dsh += 4u * dstep;
-            cur = nxt;
+    // the genes, eight per 16-byte read (rows hold n_pad + 8 entries)
+    typedef const __attribute__((address_space(3))) u32x4* row_vec;
+    const row_vec row = (row_vec)pl.feed_row;
+    const int vmax = n_pad >> 3;
+    u32x4 cur = row[0], nxt = row[vmax < 1 ? vmax : 1];
+    auto gene = [&](const u32x4& v, int e) -> uint32_t {
+        return __builtin_amdgcn_ubfe(v[e >> 1], 16 * (e & 1), jb);
+    };
+    uint32_t o_key = gene(cur, 0), nx_key = gene(cur, 1);
+    uint32_t o_p = (uint32_t)pl.prow[o_key], pn = (uint32_t)pl.prow[nx_key];
+    for (int t = 0; t < total; t += kPipeBlock) {
+        const int vn = (t >> 3) + 2;
+        const u32x4 nn = row[vn < vmax ? vn : vmax];   // for the next block
+        if (KEY != kKeyTwo) {
+#pragma unroll
+            for (int i = 0; i < MMAX; ++i) key[i] = (key[i] & keep) | ((uint32_t)i << jb);
         }
-    }
-    for (; it < total; ++it) {
-        pipe_step<MMAX, true, F, PT>(key, o_key, o_p, pn_pre, AP[it < n ? it : n - 1], (uint32_t)(it - a_k), n_act,
-                                     un, first, ujb, jmask, prow_next, sh, dsh);
-        dsh += dstep;
+        if (t >= a_last && t + kPipeBlock <= n) {
+#pragma unroll
+            for (int i = 0; i < kPipeBlock; ++i) {
+                const uint32_t fg = i < 6 ? gene(cur, i + 2) : gene(nxt, i - 6);
+                pipe_step<MMAX, false, KEY, PT>(key, o_key, o_p, nx_key, pn, fg, 0u, 0u, un, feed, sh, jmask, pl.prow,
+                                                (uint32_t)(NB0 + i) << jb, cmx);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < kPipeBlock; ++i) {
+                const uint32_t fg = i < 6 ? gene(cur, i + 2) : gene(nxt, i - 6);
+                pipe_step<MMAX, true, KEY, PT>(key, o_key, o_p, nx_key, pn, fg, (uint32_t)(t + i - a_k), n_act, un,
+                                               feed, sh, jmask, pl.prow, (uint32_t)(NB0 + i) << jb, cmx);
+            }
+        }
+        cur = nxt;
+        nxt = nn;
     }
     // the last stage's list now holds every machine's final completion time
     uint32_t cmax = 0;
 #pragma unroll
     for (int i = 0; i < MMAX; ++i) {
-        const uint32_t c = (key[i] == PAD) ? 0u : (key[i] >> (F ? sh : ujb));
+        const uint32_t c = (key[i] >> sh) == (PAD >> sh) ? 0u : (key[i] >> sh);
         cmax = c > cmax ? c : cmax;
     }
     return cmax;
 }
 
-// The pipelined decode with the instance's key format: three-field keys
-// where every completion fits their completion field (psh = 2 jb, set when
-// the sum of all processing times does), else two-field keys.
+// The two-field decode as a function of its own: the fallback of the checked
+// one, and the decode of instances whose completions do not fit beside an
+// index.
 template <int MMAX, typename PT>
-__device__ __forceinline__ uint32_t decode_pipelined(const uint32_t* AP, const PT* prow_next, const int* mach,
-                                                     int k, int S, int n, int jb, int psh, bool active)
+__device__ __attribute__((noinline)) uint32_t decode_pipe_two(PipeLane<PT> pl, const int* mach, int S, int n,
+                                                              int n_pad, int jb)
 {
-    if (psh > 0) return decode_pipelined_keys<MMAX, true, PT>(AP, prow_next, mach, k, S, n, jb, active);
-    return decode_pipelined_keys<MMAX, false, PT>(AP, prow_next, mach, k, S, n, jb, active);
+    uint32_t cmx = 0u;
+    return decode_pipe<MMAX, kKeyTwo, PT>(pl, mach, S, n, n_pad, jb, cmx);
 }
 
-// AP[t] = (p[A[t]][0] << jb) | A[t], built by the group's lanes.
-template <typename PT>
-__device__ __forceinline__ void build_ap(uint32_t* AP, const uint16_t* A, const PT* prow0, int n, int jb, int k,
-                                         int S, bool active)
+// The pipelined decode with the instance's key format.
+template <int MMAX, typename PT>
+__device__ __forceinline__ uint32_t decode_pipelined(const PipeLane<PT>& pl, const InstDesc* I, bool active)
 {
-    constexpr int U = 4;
-    if (active)
-        for (int t0 = k; t0 < n; t0 += U * S) {
-            uint32_t j[U], pj[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = t0 + u * S;
-                j[u] = A[t < n ? t : 0];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) pj[u] = prow0[j[u]];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = t0 + u * S;
-                if (t < n) AP[t] = (pj[u] << jb) | j[u];
-            }
-        }
-    wave_sync();
+    const int *mach = I->mach, S = I->S, n = I->n, n_pad = I->n_pad, jb = I->jb, fmt = I->pkey;
+    uint32_t cmx = 0u;
+    if (fmt == kKeyIdx) return decode_pipe<MMAX, kKeyIdx, PT>(pl, mach, S, n, n_pad, jb, cmx);
+    if (fmt == kKeyTwo) return decode_pipe_two<MMAX, PT>(pl, mach, S, n, n_pad, jb);
+    const uint32_t cm = decode_pipe<MMAX, kKeyIdxChecked, PT>(pl, mach, S, n, n_pad, jb, cmx);
+    // a completion that reaches the field's largest value (padding's) or
+    // outgrows it, on any lane of any group: every group takes the two-field
+    // result, which is the same wherever both are right
+    const uint32_t cap = 0xFFFFFFFFu >> (jb + pipe_index_bits(MMAX));
+    if (__ballot(active && cmx >= cap) == 0ull) return cm;
+    return decode_pipe_two<MMAX, PT>(pl, mach, S, n, n_pad, jb);
+}
+
+// The lane's part in the pipeline: group g of a wave of G groups, stage k,
+// of which the first `groups` hold a chromosome (one at least); rows at
+// gbase, `stride` entries apart.
+template <typename PT>
+__device__ __forceinline__ PipeLane<PT> pipe_lane(const uint16_t* gbase, int stride, const PT* pT, int n_pad, int lane,
+                                                  int g, int k, int S, int G, int groups)
+{
+    PipeLane<PT> pl;
+    pl.k = k;
+    pl.feed = k == S - 1 || lane == kWave - 1;
+    int fg = lane == kWave - 1 ? 0 : g + 1;
+    fg = (fg < G && fg < groups) ? fg : 0;
+    pl.feed_row = as_lds(gbase + (size_t)fg * stride);
+    pl.prow = as_lds(pT + (size_t)(pl.feed ? 0 : k + 1) * pt_stride<PT>(n_pad));
+    return pl;
 }
 
 // ---- order crossover on a group -------------------------------------------
@@ -1055,7 +1124,7 @@ __device__ void fold_best(const InstDesc* __restrict__ insts, const IslandDesc* 
 
 // Folds the completed generation into the best-ever records of every fold
 // group that has not done so yet (one workgroup).
-__global__ void __launch_bounds__(256) k_best_flush(const InstDesc* __restrict__ insts,
+static __global__ void __launch_bounds__(256) k_best_flush(const InstDesc* __restrict__ insts,
                                                     const IslandDesc* __restrict__ isls, Control* ctl, int n_inst,
                                                     int groups)
 {
@@ -1110,7 +1179,7 @@ __global__ void __launch_bounds__(512) k_generation(const InstDesc* __restrict__
     const InstDesc* I = insts + wi.inst;
     const IslandDesc* L = isls + wi.island;
     if (mode == 0 && L->sweep) return;   // line-sweep islands have launches of their own
-    const int n = I->n, S = I->S, n_pad = I->n_pad, jb = I->jb, G = I->G;
+    const int S = I->S, n_pad = I->n_pad, G = I->G;
 
     PT* pT = reinterpret_cast<PT*>(ffs_smem);
     stage_pt<PT>(pT, I->pT, S, n_pad);
@@ -1128,15 +1197,17 @@ __global__ void __launch_bounds__(512) k_generation(const InstDesc* __restrict__
     uint16_t* B = A + n_pad;
     uint16_t* V = B + n_pad;
     const int slot = wi.slot0 + (active ? local : 0);
-    const PT* prow_next = pT + (size_t)(k + 1 < S ? k + 1 : S - 1) * pt_stride<PT>(n_pad);
 
     const bool screened = mode == 0 && L->kind == 0 && I->surr_k > 1 && gen > I->surr_warmup;
     const uint32_t sub = screened ? (uint32_t)I->surr_choice[L->cell_base + slot] : 0u;
     const CellMeta meta = make_child(I, L, slot, sub, gen, cur, mode, A, B, V, k, S, g, active);
 
-    uint32_t* AP = reinterpret_cast<uint32_t*>(B);   // B..V: n_pad words
-    build_ap<PT>(AP, A, pT, n, jb, k, S, active);
-    const uint32_t cm = decode_pipelined<MMAX, PT>(AP, prow_next, I->mach, k, S, n, jb, I->psh, active);
+    // waves past the work item's chromosomes have nothing to decode
+    const int groups = wi.count - wave * G;
+    uint32_t cm = 0u;
+    if (groups > 0)
+        cm = decode_pipelined<MMAX, PT>(
+            pipe_lane<PT>(gbase, group_stride(n_pad), pT, n_pad, lane, g, k, S, G, groups), I, active);
     const int src = active ? (g * S + S - 1) : lane;
     const int cmg = __shfl((int)cm, src, 64);
 
@@ -1196,45 +1267,67 @@ __global__ void __launch_bounds__(512) k_generation(const InstDesc* __restrict__
 }
 
 // ---- decode of caller-supplied permutations -------------------------------
+// A group of S lanes per row.  The row's genes go to LDS as 16-bit values and
+// set their bits in a bit set beside it; a row is a permutation if every
+// value is in range and all n bits are set.
+// LDS of one group: the row with 16 bytes of padding, then the bit set.
+__host__ __device__ inline int eval_stride(int n_pad) { return n_pad + 8 + ((2 * (n_pad / 32) + 7) & ~7); }
+
 template <int MMAX, typename PT>
 __global__ void __launch_bounds__(512) k_evaluate(const InstDesc* __restrict__ I, const int* __restrict__ perms,
                                                   int count, int* __restrict__ out, Control* ctl)
 {
-    const int n = I->n, S = I->S, n_pad = I->n_pad, jb = I->jb, G = I->G;
+    const int n = I->n, S = I->S, n_pad = I->n_pad, G = I->G;
     PT* pT = reinterpret_cast<PT*>(ffs_smem);
     stage_pt<PT>(pT, I->pT, S, n_pad);
     __syncthreads();
     const int wpb = blockDim.x >> 6;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint16_t* gbase = reinterpret_cast<uint16_t*>(ffs_smem + pt_lds_bytes<PT>(S, n_pad) +
-                                                  wave * wave_lds_bytes(G, n_pad));
+    const int stride = eval_stride(n_pad);
+    uint16_t* gbase = reinterpret_cast<uint16_t*>(ffs_smem + pt_lds_bytes<PT>(S, n_pad)) + (size_t)wave * G * stride;
     const int g = lane / S, k = lane - g * S;
-    const long long idx = ((long long)blockIdx.x * wpb + wave) * G + g;
+    const long long first = ((long long)blockIdx.x * wpb + wave) * G;
+    if (first >= count) return;
+    const long long idx = first + g;
     const bool active = (g < G) && (idx < count);
-    uint16_t* A = gbase + (size_t)(active ? g : 0) * group_stride(n_pad);
-    uint16_t* V = A + 2 * n_pad;
+    uint16_t* A = gbase + (size_t)(active ? g : 0) * stride;
+    uint32_t* W = reinterpret_cast<uint32_t*>(A + n_pad + 8);
+    const int nw = (n + 31) >> 5;
+    if (active)
+        for (int q = k; q < nw; q += S) W[q] = 0u;
+    wave_sync();
     bool bad = false;
     if (active) {
-        const int* row = perms + idx * (long long)n;
-        for (int t = k; t < n; t += S) {
-            const int x = row[t];
-            const bool ob = (unsigned)x >= (unsigned)n;
-            bad |= ob;
-            A[t] = ob ? (uint16_t)0 : (uint16_t)x;
-            if (!ob) V[x] = (uint16_t)t;
+        constexpr int U = 8;
+        const auto* row = as_global(perms + idx * (long long)n);
+        for (int t0 = k; t0 < n; t0 += U * S) {
+            int x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = row[t0 + u * S < n ? t0 + u * S : n - 1];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (t0 + u * S < n) {
+                    const bool ob = (unsigned)x[u] >= (unsigned)n;
+                    bad |= ob;
+                    A[t0 + u * S] = ob ? (uint16_t)0 : (uint16_t)x[u];
+                    if (!ob) atomicOr(&W[x[u] >> 5], 1u << (x[u] & 31));
+                }
+            }
         }
     }
     wave_sync();
     if (active)
-        for (int t = k; t < n; t += S) bad |= (V[A[t]] != (uint16_t)t);
+        for (int q = k; q < nw; q += S) {
+            const int left = n - 32 * q;
+            bad |= W[q] != (left >= 32 ? 0xFFFFFFFFu : (1u << left) - 1u);
+        }
     const uint64_t gmask = (S >= 64) ? ~0ull : ((1ull << S) - 1ull);
     const uint64_t bb = __ballot(bad && active);
     const int shift = g * S;
     const bool gbad = ((shift < 64 ? (bb >> shift) : 0ull) & gmask) != 0ull;
-    uint32_t* AP = reinterpret_cast<uint32_t*>(A + n_pad);   // B..V: n_pad words
-    build_ap<PT>(AP, A, pT, n, jb, k, S, active);
-    const uint32_t cm = decode_pipelined<MMAX, PT>(AP, pT + (size_t)(k + 1 < S ? k + 1 : S - 1) * pt_stride<PT>(n_pad), I->mach,
-                                                   k, S, n, jb, I->psh, active);
+    const int groups = count - first < G ? (int)(count - first) : G;
+    const uint32_t cm = decode_pipelined<MMAX, PT>(
+        pipe_lane<PT>(gbase, stride, pT, n_pad, lane, g, k, S, G, groups), I, active);
     if (active && k == S - 1) out[idx] = gbad ? -1 : (int)cm;
     if (active && k == 0 && gbad) atomicOr(&ctl->err, 1);
 }
@@ -1250,7 +1343,7 @@ __global__ void __launch_bounds__(512) k_candidates(const InstDesc* __restrict__
                                                     float* __restrict__ Tout)
 {
     const InstDesc* I = insts + inst;
-    const int n = I->n, S = I->S, n_pad = I->n_pad, jb = I->jb, G = I->G, K = I->surr_k;
+    const int S = I->S, n_pad = I->n_pad, G = I->G, K = I->surr_k;
     const int done = completed_gen(ctl);
     const int gen = done + 1, cur = done & 1;
     PT* pT = reinterpret_cast<PT*>(ffs_smem);
@@ -1280,10 +1373,11 @@ __global__ void __launch_bounds__(512) k_candidates(const InstDesc* __restrict__
     const CellMeta meta = cellular_offspring(I, L, slot, (uint32_t)c, gen, cur, A, B, V, k, S, g, active);
     features_group<PT>(A, pT, I, k, active, meta, Xout + (size_t)qq * kFeat);
     if (Tout) {
-        uint32_t* AP = reinterpret_cast<uint32_t*>(B);
-        build_ap<PT>(AP, A, pT, n, jb, k, S, active);
-        const uint32_t cm = decode_pipelined<MMAX, PT>(AP, pT + (size_t)(k + 1 < S ? k + 1 : S - 1) * pt_stride<PT>(n_pad),
-                                                       I->mach, k, S, n, jb, I->psh, active);
+        const int groups = Nc - (blockIdx.x * wpb + wave) * G;
+        uint32_t cm = 0u;
+        if (groups > 0)
+            cm = decode_pipelined<MMAX, PT>(
+                pipe_lane<PT>(gbase, group_stride(n_pad), pT, n_pad, lane, g, k, S, G, groups), I, active);
         const int cmg = __shfl((int)cm, active ? (g * S + S - 1) : lane, 64);
         if (active && k == 0) Tout[q] = __fdiv_rn((float)(cmg - I->LB), (float)I->LB);
     }
@@ -1296,7 +1390,7 @@ __global__ void __launch_bounds__(512) k_candidates(const InstDesc* __restrict__
 constexpr int kP_W1 = 0, kP_b1 = 131072, kP_W2 = 131584, kP_b2 = 393728, kP_w3 = 394240, kP_b3 = 394752;
 constexpr int kParams = 394753;
 
-__global__ void __launch_bounds__(256) k_mlp_init(uint64_t seed, uint64_t inst, float* __restrict__ w,
+static __global__ void __launch_bounds__(256) k_mlp_init(uint64_t seed, uint64_t inst, float* __restrict__ w,
                                                   uint16_t* __restrict__ wb, float* __restrict__ m,
                                                   float* __restrict__ v)
 {
@@ -1327,7 +1421,7 @@ __global__ void __launch_bounds__(256) k_mlp_init(uint64_t seed, uint64_t inst, 
 // g: uniform over the filled part of the replay ring (min(g * cells, ring)
 // rows), from the MLP_BATCH stream of step g (draw r -> row r).  The
 // generation comes from the control block, so a captured graph replays it.
-__global__ void __launch_bounds__(256) k_batch_idx(uint64_t seed, uint64_t inst, const Control* __restrict__ ctl,
+static __global__ void __launch_bounds__(256) k_batch_idx(uint64_t seed, uint64_t inst, const Control* __restrict__ ctl,
                                                    int cells, int ring, int rows, int* __restrict__ idx)
 {
     const int blk = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1343,7 +1437,7 @@ __global__ void __launch_bounds__(256) k_batch_idx(uint64_t seed, uint64_t inst,
     }
 }
 
-__global__ void __launch_bounds__(256) k_zero_u32(uint32_t* __restrict__ p, size_t count)
+static __global__ void __launch_bounds__(256) k_zero_u32(uint32_t* __restrict__ p, size_t count)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < count) p[i] = 0u;
@@ -1356,7 +1450,7 @@ __device__ __forceinline__ bool migrating_now(const InstDesc* I, int inst, int g
     return I->interval > 0 && gen > 0 && (gen % I->interval) == 0;
 }
 
-__global__ void __launch_bounds__(256) k_mig_minmax(const InstDesc* __restrict__ insts,
+static __global__ void __launch_bounds__(256) k_mig_minmax(const InstDesc* __restrict__ insts,
                                                     const IslandDesc* __restrict__ isls, const Control* ctl,
                                                     int force_inst)
 {
@@ -1389,7 +1483,7 @@ __global__ void __launch_bounds__(256) k_mig_minmax(const InstDesc* __restrict__
 }
 
 // ring c0, p0, c1, p1, ...: island x receives its predecessor's best into its worst slot
-__global__ void __launch_bounds__(256) k_mig_ring(const InstDesc* __restrict__ insts,
+static __global__ void __launch_bounds__(256) k_mig_ring(const InstDesc* __restrict__ insts,
                                                   const IslandDesc* __restrict__ isls, const Control* ctl,
                                                   int force_inst)
 {
@@ -1434,7 +1528,7 @@ __host__ __device__ inline size_t sort_lds_bytes(int R)
            (size_t)2 * kSortEnt * sizeof(uint32_t) + (size_t)2 * kSortWaves * sizeof(uint32_t);
 }
 
-__global__ void __launch_bounds__(kSortThreads) k_mig_sort(const InstDesc* __restrict__ insts,
+static __global__ void __launch_bounds__(kSortThreads) k_mig_sort(const InstDesc* __restrict__ insts,
                                                            const IslandDesc* __restrict__ isls,
                                                            const Control* ctl, int force_inst, int only_inst)
 {
@@ -1574,7 +1668,7 @@ __global__ void __launch_bounds__(kSortThreads) k_mig_sort(const InstDesc* __res
 // immigrant slot is replaced, the immigrant's best row itself is rewritten).
 constexpr int kMigRows = 32;
 
-__global__ void __launch_bounds__(256) k_mig_adapt(const InstDesc* __restrict__ insts,
+static __global__ void __launch_bounds__(256) k_mig_adapt(const InstDesc* __restrict__ insts,
                                                    const IslandDesc* __restrict__ isls,
                                                    const PairDesc* __restrict__ pairs, const Control* ctl,
                                                    int force_inst)

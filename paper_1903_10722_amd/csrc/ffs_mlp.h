@@ -222,7 +222,7 @@ __device__ __forceinline__ float sum_strided(const float* __restrict__ x, size_t
 }
 
 // out[i] = sum over splits s of part[s][i]  (fixed order: deterministic)
-__global__ void __launch_bounds__(256) k_sum_splits(const float* __restrict__ part, int splits, size_t count,
+static __global__ void __launch_bounds__(256) k_sum_splits(const float* __restrict__ part, int splits, size_t count,
                                                     float* __restrict__ out)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -234,7 +234,7 @@ __global__ void __launch_bounds__(256) k_sum_splits(const float* __restrict__ pa
 // y[i] = H2[i] . w3 + b3, one wave per row (64 lanes x 8 columns).  With
 // K > 0 (scoring) the wave then handles the K candidates of one cell and
 // writes the index of the smallest prediction (ties: lowest index).
-__global__ void __launch_bounds__(256) k_mlp_out(const uint16_t* __restrict__ H2, const uint16_t* __restrict__ w3,
+static __global__ void __launch_bounds__(256) k_mlp_out(const uint16_t* __restrict__ H2, const uint16_t* __restrict__ w3,
                                                  const float* __restrict__ b3, int rows, int K,
                                                  float* __restrict__ y, int* __restrict__ choice)
 {
@@ -268,7 +268,7 @@ __global__ void __launch_bounds__(256) k_mlp_out(const uint16_t* __restrict__ H2
 // Output layer and its gradient for training, one wave per row:
 // y[i] = H2[i] . w3 + b3 (as k_mlp_out), dy[i] = 2 (y[i] - t[i]) / rows and
 // dZ2[i][j] = bf16(dy[i] * w3[j]) where H2[i][j] > 0.
-__global__ void __launch_bounds__(256) k_mlp_out_dz2(const uint16_t* __restrict__ H2, const uint16_t* __restrict__ w3,
+static __global__ void __launch_bounds__(256) k_mlp_out_dz2(const uint16_t* __restrict__ H2, const uint16_t* __restrict__ w3,
                                                      const float* __restrict__ b3, const float* __restrict__ t,
                                                      int rows, float* __restrict__ y, float* __restrict__ dy,
                                                      uint16_t* __restrict__ dZ2)
@@ -308,7 +308,7 @@ struct Colsum3 {
     float* out[3];
 };
 
-__global__ void __launch_bounds__(256) k_colsum3(Colsum3 a, const float* __restrict__ dy, float* __restrict__ part,
+static __global__ void __launch_bounds__(256) k_colsum3(Colsum3 a, const float* __restrict__ dy, float* __restrict__ part,
                                                  float* __restrict__ dpart)
 {
     __shared__ float red[4][kHidden];
@@ -348,7 +348,7 @@ __global__ void __launch_bounds__(256) k_colsum3(Colsum3 a, const float* __restr
 // number) and writes step t + 1's bias corrections 1 - beta^(t+1) to bc,
 // from `table` (computed on the host in FP64 and rounded to FP32; entry t for
 // t < steps, both exactly 1 beyond).
-__global__ void __launch_bounds__(256) k_colsum3_sum(Colsum3 a, const float* __restrict__ part, int chunks,
+static __global__ void __launch_bounds__(256) k_colsum3_sum(Colsum3 a, const float* __restrict__ part, int chunks,
                                                      const float* __restrict__ dpart, float* __restrict__ dsum,
                                                      long long* step, const float2* __restrict__ table, int steps,
                                                      float* __restrict__ bc)
@@ -371,7 +371,7 @@ __global__ void __launch_bounds__(256) k_colsum3_sum(Colsum3 a, const float* __r
 // One Adam step on every parameter with the bias corrections bc[0] =
 // 1 - beta1^t, bc[1] = 1 - beta2^t of step t, which k_colsum3_sum looked up
 // when it advanced the step count kept in device memory.
-__global__ void __launch_bounds__(256) k_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
+static __global__ void __launch_bounds__(256) k_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
                                               const float* __restrict__ g, uint16_t* __restrict__ wb, int count,
                                               float lr, float beta1, float beta2, float eps,
                                               const float* __restrict__ bc)
@@ -389,7 +389,7 @@ __global__ void __launch_bounds__(256) k_adam(float* __restrict__ w, float* __re
     if (wb) wb[i] = f32_to_bf16(wi);
 }
 
-__global__ void __launch_bounds__(256) k_to_bf16(const float* __restrict__ x, uint16_t* __restrict__ y, int count)
+static __global__ void __launch_bounds__(256) k_to_bf16(const float* __restrict__ x, uint16_t* __restrict__ y, int count)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < count) y[i] = f32_to_bf16(x[i]);
@@ -397,7 +397,7 @@ __global__ void __launch_bounds__(256) k_to_bf16(const float* __restrict__ x, ui
 
 // Minibatch gather: rows idx_b (Philox stream of the training step) of the
 // replay ring into contiguous X / t.
-__global__ void __launch_bounds__(256) k_gather_batch(const uint16_t* __restrict__ ringX,
+static __global__ void __launch_bounds__(256) k_gather_batch(const uint16_t* __restrict__ ringX,
                                                       const float* __restrict__ ringT, const int* __restrict__ idx,
                                                       int rows, uint16_t* __restrict__ X, float* __restrict__ t)
 {
