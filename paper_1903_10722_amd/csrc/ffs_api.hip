@@ -287,7 +287,7 @@ void layout(ffs_ctx* c)
         I.wpb_eff = I.tile_wpb > 0 ? I.tile_wpb : c->wpb;
         for (;;) {
             I.lds = align16((size_t)I.S * ((size_t)I.n_pad * c->ptb + 4)) +
-                    (size_t)I.wpb_eff * (I.map_eff ? I.lane_wlds : wave_lds_bytes(I.G, I.n_pad));
+                    (size_t)I.wpb_eff * (I.map_eff ? I.lane_wlds : wave_lds_bytes(I.G, I.n, I.n_pad, I.S));
             if (I.lds <= (size_t)c->max_lds || I.wpb_eff == 1) break;
             I.wpb_eff >>= 1;
         }
@@ -1027,7 +1027,7 @@ size_t ckpt_bytes(const ffs_ctx* c)
 
 // The pieces of the image after the header, in order: device offset and
 // bytes, and for rows of permutations (u16, n_pad per row) the genes per row,
-// whose padding the image stores as zeros (kernels leave it undefined).
+// whose padding the image stores as zeros.
 struct CkptPiece {
     size_t off, bytes;
     int n = 0, n_pad = 0;
@@ -1147,9 +1147,9 @@ int ffs_create_instance(ffs_ctx* c, int32_t n, int32_t S, const int32_t* machine
         return fail(c, FFS_EUNSUPPORTED, "sum of processing times %lld too large for the packed key (limit %lld)",
                     I.E, (1ll << (32 - jb)) - 1);
     I.n_pad = (n + 31) & ~31;
-    // chromosomes per wave: one lane per stage, capped so that a wave's
-    // three LDS rows per chromosome stay within 32 KB
-    I.G = std::min(kWave / S, std::max(1, 32768 / (2 * group_stride(I.n_pad))));
+    // chromosomes per wave: one lane per stage, capped so that a wave's LDS
+    // rows stay within 32 KB
+    I.G = std::min(kWave / S, std::max(1, 32768 / (2 * group_stride(n, I.n_pad, S))));
     for (int x = 0; x < n_islands; ++x) {
         const ffs_island_spec& sp = islands[x];
         HostIsland L;
@@ -1487,10 +1487,13 @@ int ffs_bind_workspace(ffs_ctx* c, void* dptr, size_t bytes)
                 else reinterpret_cast<uint16_t*>(pt.data())[(size_t)k * I.n_pad + j] = (uint16_t)v;
             }
         HIP_TRY(c, hipMemcpy(c->ws + I.off_pT, pt.data(), pt.size(), hipMemcpyHostToDevice));
+        // best permutations (zero: a record that no chain uses stays as it is,
+        // and checkpoint images of equal states are equal), records, counters:
+        // adjacent pieces of the workspace
+        std::vector<uint8_t> br(I.off_counters - I.off_best_perm + 2 * sizeof(long long), 0);
         const int rec[4 * kChains] = {INT_MAX, -1, -1, -1, INT_MAX, -1, -1, -1};
-        HIP_TRY(c, hipMemcpy(c->ws + I.off_best_rec, rec, sizeof rec, hipMemcpyHostToDevice));
-        const long long cnt[2] = {0, 0};
-        HIP_TRY(c, hipMemcpy(c->ws + I.off_counters, cnt, sizeof cnt, hipMemcpyHostToDevice));
+        memcpy(br.data() + (I.off_best_rec - I.off_best_perm), rec, sizeof rec);
+        HIP_TRY(c, hipMemcpy(c->ws + I.off_best_perm, br.data(), br.size(), hipMemcpyHostToDevice));
         for (auto& L : I.isl) {
             const unsigned long long gk[2] = {~0ull, ~0ull};
             HIP_TRY(c, hipMemcpy(c->ws + L.off_genkey, gk, sizeof gk, hipMemcpyHostToDevice));
@@ -2079,7 +2082,7 @@ int ffs_evaluate_noalloc(void* hip_stream, int32_t n, int32_t S, const int32_t* 
     const DecodeKeys dk = decode_keys(n, S, machines, p, jb, mm);
     d.fsh = dk.fsh;
     d.pkey = dk.pkey;
-    d.G = std::min(kWave / S, std::max(1, 32768 / (2 * group_stride(n_pad))));
+    d.G = std::min(kWave / S, std::max(1, 32768 / (2 * group_stride(n, n_pad, S))));
     d.msum = msum;
     for (int k = 0; k < S; ++k) d.mach[k] = machines[k];
     d.lane_wlds_eval = (int)lane_eval_wave_lds(n, msum);

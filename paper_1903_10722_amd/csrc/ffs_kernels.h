@@ -133,15 +133,28 @@ __device__ __forceinline__ void wave_sync()
 
 __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
-// LDS of one group: three n_pad rows of uint16 and 16 bytes of padding, so
-// that the groups of a wave start 4 banks apart and same-offset accesses of
-// different groups do not collide.
-__host__ __device__ inline int group_stride(int n_pad) { return 3 * n_pad + 8; }
+// Vectors of eight genes that a lane owns when S lanes share a row, and the
+// most that the register path of the crossover holds.
+__host__ __device__ inline int ox_vectors(int n, int S) { return ((n + 7) / 8 + S - 1) / S; }
+constexpr int kOxVec = 13;
 
-__host__ __device__ inline size_t wave_lds_bytes(int G, int n_pad)
+// LDS of one group: the child's row of n_pad uint16 and 16 bytes of padding,
+// so that the groups of a wave start 4 banks apart and same-offset accesses of
+// different groups do not collide.  The crossover marks parent 1's positions
+// in the row itself before it writes the child there; rows of more than
+// kOxVec vectors per lane have the marks in a second row.
+__host__ __device__ inline int group_stride(int n, int n_pad, int S)
 {
-    return (size_t)G * group_stride(n_pad) * 2;
+    return ox_vectors(n, S) <= kOxVec ? n_pad + 8 : 2 * n_pad + 8;
 }
+
+__host__ __device__ inline size_t wave_lds_bytes(int G, int n, int n_pad, int S)
+{
+    return (size_t)G * group_stride(n, n_pad, S) * 2;
+}
+
+// LDS of one wave that works on whole rows (three n_pad rows of uint16).
+__host__ __device__ inline int wave_rows(int n_pad) { return 3 * n_pad + 8; }
 
 // The processing-time table is staged into LDS stage-major with each row
 // padded by 4 bytes, so that the S rows start on different LDS banks (the S
@@ -742,6 +755,236 @@ __device__ __forceinline__ void ox_group(uint16_t* A, const uint16_t* B, uint16_
     wave_sync();
 }
 
+// ---- order crossover on rows read as vectors --------------------------------
+// child[a..b] = P1[a..b]; P2 read cyclically from b+1 fills b+1, ..., n-1, 0,
+// ..., a-1 with the genes not in the segment (a = 0, b = n - 1: the child is
+// P1).  A parent may be given as its reversal (rev: position p of the parent
+// is entry n-1-p of the row), so a pseudo pair needs no reversed copy.
+//
+// Lane k of the S lanes that share a row owns 16-byte vectors [v0, v0 + vpl)
+// of both rows, in registers.  P1's genes mark the row, indexed by gene, with
+// their position - a (unsigned: the segment's are <= b - a); each P2 gene
+// reads its mark, and the genes to keep become one bit each; a scan over the
+// lanes gives every kept gene its place: with K kept genes before it in P2's
+// order, Ta kept genes after position b and T = n - 1 - (b - a) in all, its
+// rank from b+1 is (K + Ta) mod T, and the free positions in ascending order
+// start at rank T - a.  Then the child is written over the marks.  Three LDS
+// round trips and one scan; the rows themselves go from HBM to registers.
+// One LDS row per chromosome instead of three is what it gains where a
+// workgroup's LDS decides how many waves are resident: a generation of fifty
+// seeds of 300 jobs and 4 stages (400 workgroups of 124 KB, two rounds; now
+// 42 KB, one round) 92 -> 48 us, of 8192 chromosomes of 1000 jobs and 20
+// stages with the pre-screen 541 -> 463 us, of the medium size 20.7 -> 19.9 us.
+struct OxCut {
+    int n, a, len;       // segment [a, a + len]
+    bool rev1, rev2;     // parents 1 / 2 reversed
+};
+
+__device__ __forceinline__ uint32_t ox_gene(const u32x4& v, int e)
+{
+    return (e & 1) ? v[e >> 1] >> 16 : v[e >> 1] & 0xFFFFu;
+}
+
+// Vectors [v0, v0 + vpl) of a row of nv (past the row's end: its last one).
+template <int VC>
+__device__ __forceinline__ void ox_load(u32x4 (&x)[VC], const uint16_t* row, int v0, int vpl, int nv)
+{
+    const auto* r4 = as_global(reinterpret_cast<const u32x4*>(row));
+#pragma unroll
+    for (int v = 0; v < VC; ++v)
+        if (v < vpl) x[v] = r4[v0 + v < nv ? v0 + v : nv - 1];
+}
+
+// Marks of parent 1's genes; the lane holds `lim` genes from position 8 v0 on.
+template <int VC>
+__device__ __forceinline__ void ox_mark(uint16_t* M, const u32x4 (&x)[VC], const OxCut& o, int v0, int vpl, int lim)
+{
+    const int st = o.rev1 ? -1 : 1;
+    int t = (o.rev1 ? o.n - 1 - 8 * v0 : 8 * v0) - o.a;
+#pragma unroll
+    for (int v = 0; v < VC; ++v)
+        if (v < vpl) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (8 * v + e < lim) M[ox_gene(x[v], e)] = (uint16_t)t;
+                t += st;
+            }
+        }
+}
+
+// Bits of parent 2's genes to keep (gene e of a vector at bit 7 - e) and
+// their count, in the high half those after position b in P2's order.
+template <int VC>
+__device__ __forceinline__ int ox_keep(const uint16_t* M, const u32x4 (&x)[VC], uint32_t (&keep)[VC], const OxCut& o,
+                                       int v0, int vpl, int lim)
+{
+    const int b = o.a + o.len;
+    const int split = (o.rev2 ? o.n - 1 - b : b + 1) - 8 * v0;   // genes below it: after b if reversed, else up to b
+    const uint32_t flip = o.rev2 ? 0u : 0xFFu;
+    int cnt = 0;
+#pragma unroll
+    for (int v = 0; v < VC; ++v)
+        if (v < vpl) {
+            uint32_t m[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) m[e] = M[ox_gene(x[v], e)];
+            uint32_t kb = 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)   // outside the segment: len - mark < 0
+                kb = __builtin_amdgcn_alignbit(kb, (uint32_t)o.len - m[e], 31);
+            const int nval = lim - 8 * v, ns = split - 8 * v;
+            kb &= 0xFF00u >> (nval < 0 ? 0 : (nval > 8 ? 8 : nval));
+            const uint32_t below_split = (0xFF00u >> (ns < 0 ? 0 : (ns > 8 ? 8 : ns))) & 0xFFu;
+            keep[v] = kb & 0xFFu;
+            cnt += __popc(keep[v]) + (__popc(keep[v] & (below_split ^ flip)) << 16);
+        }
+    return cnt;
+}
+
+template <int VC>
+__device__ __forceinline__ void ox_place1(uint16_t* A, const u32x4 (&x)[VC], const OxCut& o, int v0, int vpl, int lim)
+{
+    const int st = o.rev1 ? -1 : 1;
+    int p = o.rev1 ? o.n - 1 - 8 * v0 : 8 * v0;
+#pragma unroll
+    for (int v = 0; v < VC; ++v)
+        if (v < vpl) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (8 * v + e < lim && (uint32_t)(p - o.a) <= (uint32_t)o.len) A[p] = (uint16_t)ox_gene(x[v], e);
+                p += st;
+            }
+        }
+}
+
+// Writes the kept genes from the place `idx` of the first one on (places are
+// the free positions in ascending order); returns the next place.
+template <int VC>
+__device__ __forceinline__ int ox_place2(uint16_t* A, const u32x4 (&x)[VC], const uint32_t (&keep)[VC], const OxCut& o,
+                                         int vpl, int idx)
+{
+    const int T = o.n - 1 - o.len, len1 = o.len + 1;
+    const int st = o.rev2 ? -1 : 1, wrap = o.rev2 ? -1 : T, to = o.rev2 ? T - 1 : 0;
+#pragma unroll
+    for (int v = 0; v < VC; ++v)
+        if (v < vpl) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (keep[v] & (0x80u >> e)) {
+                    A[idx + (idx >= o.a ? len1 : 0)] = (uint16_t)ox_gene(x[v], e);
+                    idx += st;
+                    idx = idx == wrap ? to : idx;
+                }
+        }
+    return idx;
+}
+
+// Inclusive sum over the wave's lanes (DPP: 1, 2, 4, 8 inside 16-lane rows,
+// then the rows' last lanes).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int scan_step(int x)
+{
+    return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false);
+}
+
+__device__ __forceinline__ int wave_scan(int x)
+{
+    x = scan_step<0x111, 0xF>(x);
+    x = scan_step<0x112, 0xF>(x);
+    x = scan_step<0x114, 0xF>(x);
+    x = scan_step<0x118, 0xF>(x);
+    x = scan_step<0x142, 0xA>(x);
+    x = scan_step<0x143, 0xC>(x);
+    return x;
+}
+
+// Place of the first kept gene of this lane from the scanned counts: `excl`
+// kept genes on the lanes before it, `after` kept genes after b in all.
+__device__ __forceinline__ int ox_first(const OxCut& o, int excl, int after)
+{
+    const int T = o.n - 1 - o.len;
+    if (T <= 0) return 0;
+    int z = after + o.a;                    // <= 2 T
+    z -= z >= 2 * T ? 2 * T : (z >= T ? T : 0);
+    int idx = (o.rev2 ? T - 1 - excl : excl) + z;   // excl <= T
+    idx = idx < 0 ? idx + T : idx;
+    return idx >= T ? (idx >= 2 * T ? idx - 2 * T : idx - T) : idx;
+}
+
+// Counts of the lanes below in this group and after-b total of the group.
+__device__ __forceinline__ int ox_group_first(const OxCut& o, int cnt, int g, int S)
+{
+    const int incl = wave_scan(cnt);
+    const int lo = __shfl(incl - cnt, g * S, 64), hi = __shfl(incl, g * S + S - 1, 64);
+    return ox_first(o, (incl - cnt - lo) & 0xFFFF, (hi >> 16) - (lo >> 16));
+}
+
+// The group's crossover with every vector in registers: row A (marks, then
+// the child) is in LDS, the parents' rows in HBM.
+template <int VC>
+__device__ __forceinline__ void ox_group_regs(uint16_t* A, const uint16_t* P1, const uint16_t* P2, const OxCut& o,
+                                              int vpl, int g, int k, int S, bool active)
+{
+    const int nv = (o.n + 7) >> 3, v0 = k * vpl;
+    const int lim = active ? o.n - 8 * v0 : 0;   // genes past vector vpl - 1 are not looked at
+    u32x4 x1[VC], x2[VC];
+    uint32_t keep[VC];
+    ox_load<VC>(x1, P1, v0, vpl, nv);
+    ox_load<VC>(x2, P2, v0, vpl, nv);
+    ox_mark<VC>(A, x1, o, v0, vpl, lim);
+    wave_sync();
+    const int cnt = ox_keep<VC>(A, x2, keep, o, v0, vpl, lim);
+    const int idx = ox_group_first(o, cnt, g, S);
+    wave_sync();
+    ox_place1<VC>(A, x1, o, v0, vpl, lim);
+    ox_place2<VC>(A, x2, keep, o, vpl, idx);
+    wave_sync();
+}
+
+// Longer rows: the same passes over chunks of four vectors, read from HBM
+// (L2) once per pass, with the marks in a row of their own.
+__device__ __forceinline__ void ox_group_long(uint16_t* A, uint16_t* M, const uint16_t* P1, const uint16_t* P2,
+                                              const OxCut& o, int vpl, int g, int k, int S, bool active)
+{
+    constexpr int VC = 4;
+    const int nv = (o.n + 7) >> 3, v0 = k * vpl, v1 = v0 + vpl;
+    u32x4 x[VC];
+    uint32_t keep[VC];
+    auto lim = [&](int v) { return active ? o.n - 8 * v : 0; };
+    for (int v = v0; v < v1; v += VC) {
+        const int c = v1 - v < VC ? v1 - v : VC;
+        ox_load<VC>(x, P1, v, c, nv);
+        ox_mark<VC>(M, x, o, v, c, lim(v));
+    }
+    wave_sync();
+    int cnt = 0;
+    for (int v = v0; v < v1; v += VC) {
+        const int c = v1 - v < VC ? v1 - v : VC;
+        ox_load<VC>(x, P2, v, c, nv);
+        cnt += ox_keep<VC>(M, x, keep, o, v, c, lim(v));
+    }
+    int idx = ox_group_first(o, cnt, g, S);
+    for (int v = v0; v < v1; v += VC) {
+        const int c = v1 - v < VC ? v1 - v : VC;
+        ox_load<VC>(x, P1, v, c, nv);
+        ox_place1<VC>(A, x, o, v, c, lim(v));
+        ox_load<VC>(x, P2, v, c, nv);
+        ox_keep<VC>(M, x, keep, o, v, c, lim(v));
+        idx = ox_place2<VC>(A, x, keep, o, c, idx);
+    }
+    wave_sync();
+}
+
+__device__ __forceinline__ void ox_group_rows(uint16_t* A, int n_pad, const uint16_t* P1, const uint16_t* P2,
+                                              const OxCut& o, int g, int k, int S, bool active)
+{
+    const int vpl = ox_vectors(o.n, S);
+    if (vpl <= 3) ox_group_regs<3>(A, P1, P2, o, vpl, g, k, S, active);
+    else if (vpl <= 7) ox_group_regs<7>(A, P1, P2, o, vpl, g, k, S, active);
+    else if (vpl <= kOxVec) ox_group_regs<kOxVec>(A, P1, P2, o, vpl, g, k, S, active);
+    else ox_group_long(A, A + n_pad, P1, P2, o, vpl, g, k, S, active);
+}
+
 __device__ __forceinline__ void swap_genes(uint16_t* A, bool doit, int i, int j)
 {
     if (doit) {
@@ -867,19 +1110,29 @@ __device__ __forceinline__ CellPlan cell_plan(const InstDesc* I, const IslandDes
     return pl;
 }
 
-// The child of cell `slot` (cell_plan) built on the group's LDS rows: order
-// crossover of P1 and P2, then the swap mutation.  A receives the child.
-template <bool LEAN = false>
+// The segment of a crossover with cuts a <= b; without one the child is
+// parent 1: the whole row.
+__device__ __forceinline__ OxCut ox_cut(int n, bool cx, int a, int b, bool rev1, bool rev2)
+{
+    OxCut o;
+    o.n = n;
+    o.a = cx ? a : 0;
+    o.len = cx ? b - a : n - 1;
+    o.rev1 = rev1;
+    o.rev2 = rev2;
+    return o;
+}
+
+// The child of cell `slot` (cell_plan) built in the group's LDS row A: order
+// crossover of P1 and P2, then the swap mutation.
 __device__ __forceinline__ CellMeta cellular_offspring(const InstDesc* I, const IslandDesc* L, int slot, uint32_t sub,
-                                                   int gen, int cur, uint16_t* A, uint16_t* B, uint16_t* V, int k,
-                                                   int S, int g, bool active)
+                                                   int gen, int cur, uint16_t* A, int g, int k, int S, bool active)
 {
     const int n = I->n, n_pad = I->n_pad;
     const CellPlan pl = cell_plan(I, L, slot, sub, gen, cur);
     const uint16_t* gp = L->genes[cur];
-    if (active) rows_g2l(A, gp + (size_t)pl.p1 * n_pad, B, gp + (size_t)pl.p2 * n_pad, n_pad, k, S);
-    wave_sync();
-    ox_group<!LEAN, !LEAN>(A, B, V, n, pl.meta.a, pl.meta.b, pl.meta.cx && active, k, S, g);
+    ox_group_rows(A, n_pad, gp + (size_t)pl.p1 * n_pad, gp + (size_t)pl.p2 * n_pad,
+                  ox_cut(n, pl.meta.cx, pl.meta.a, pl.meta.b, false, false), g, k, S, active);
     swap_genes(A, pl.meta.mx && active && k == 0, pl.meta.mi, pl.meta.mj);
     return pl.meta;
 }
@@ -994,67 +1247,104 @@ __device__ __forceinline__ void features_group(const uint16_t* A, const PT* pT, 
     }
 }
 
-// The chromosome of `slot` at generation `gen`, built in row A of a group of
-// S lanes (lane k) with B and V as scratch: generation 0 (mode 1) draws it;
-// a cellular cell gets the child of its neighbourhood's two best from
-// candidate stream `sub`; a pseudo slot gets its pair's complementary child.
-template <bool LEAN = false>
-__device__ __forceinline__ CellMeta make_child(const InstDesc* I, const IslandDesc* L, int slot, uint32_t sub,
-                                               int gen, int cur, int mode, uint16_t* A, uint16_t* B, uint16_t* V,
-                                               int k, int S, int g, bool active)
+// Generation 0's chromosome of `slot` in row A of a group of S lanes (lane
+// k): Fisher-Yates from the INIT stream; a pseudo pair is a permutation (even
+// slot) and its reversal (odd slot).  The swap partners pass through
+// `scratch`, a row of n_pad entries in HBM (the slot's row of the other
+// generation parity).
+__device__ __forceinline__ void initial_row(const InstDesc* I, const IslandDesc* L, int slot, uint16_t* A,
+                                            uint16_t* scratch, int k, int S, bool active)
 {
-    const int n = I->n, n_pad = I->n_pad;
-    const uint64_t seed = I->seed, iid = (uint64_t)I->inst_id;
-    const uint32_t isl_local = (uint32_t)L->local;
-    CellMeta meta{};
-    if (mode == 1) {
-        // generation 0: Fisher-Yates from the INIT stream; a pseudo pair is a
-        // permutation (even slot) and its reversal (odd slot).
-        const int fy_slot = (L->kind == 0) ? slot : (slot >> 1);
-        const bool rev = (L->kind == 1) && (slot & 1);
-        uint32_t* D = reinterpret_cast<uint32_t*>(B);   // B..V: n_pad words >= n - 1
-        const int nblk = (n - 1 + 7) / 8;
-        if (active) {
-            for (int blk = k; blk < nblk; blk += S) {
-                const Block4 bb = stream_block(seed, iid, isl_local, (uint32_t)fy_slot, 0, 0, kInit, (uint32_t)blk);
+    const int n = I->n;
+    const int fy_slot = (L->kind == 0) ? slot : (slot >> 1);
+    const bool rev = (L->kind == 1) && (slot & 1);
+    const int nblk = (n - 1 + 7) / 8;
+    u32x4* s4 = reinterpret_cast<u32x4*>(scratch);
+    if (active) {
+        for (int blk = k; blk < nblk; blk += S) {
+            const Block4 bb = stream_block(I->seed, (uint64_t)I->inst_id, (uint32_t)L->local, (uint32_t)fy_slot, 0, 0,
+                                           kInit, (uint32_t)blk);
+            uint32_t j[8];
 #pragma unroll
-                for (int d = 0; d < 8; ++d) {
-                    const int idx = blk * 8 + d;
-                    if (idx < n - 1) D[idx] = draw32(bb, d);
+            for (int d = 0; d < 8; ++d) {
+                const int idx = blk * 8 + d;
+                j[d] = idx < n - 1 ? below(draw32(bb, d), (uint32_t)(n - idx)) : 0u;
+            }
+            as_global(s4)[blk] = u32x4{j[0] | (j[1] << 16), j[2] | (j[3] << 16), j[4] | (j[5] << 16), j[6] | (j[7] << 16)};
+        }
+        for (int t = k; t < n; t += S) A[t] = (uint16_t)t;
+    }
+    // the partners are read back by another lane of this wave
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    if (active && k == 0 && nblk > 0) {
+        u32x4 nx = as_global((const u32x4*)s4)[0];
+        for (int blk = 0; blk < nblk; ++blk) {
+            const u32x4 w = nx;
+            if (blk + 1 < nblk) nx = as_global((const u32x4*)s4)[blk + 1];
+#pragma unroll
+            for (int d = 0; d < 8; ++d) {
+                const int i = n - 1 - (blk * 8 + d);
+                if (i >= 1) {
+                    const uint32_t j = ox_gene(w, d);
+                    const uint16_t x = A[i], y = A[j];
+                    A[i] = y;
+                    A[j] = x;
                 }
             }
-            for (int t = k; t < n; t += S) A[t] = (uint16_t)t;
         }
-        wave_sync();
-        if (active && k == 0) {
-            for (int i = n - 1; i >= 1; --i) {
-                const int j = (int)below(D[n - 1 - i], (uint32_t)(i + 1));
-                const uint16_t x = A[i], y = A[j];
-                A[i] = y;
-                A[j] = x;
-            }
+    }
+    wave_sync();
+    if (active && rev) {
+        for (int t = k; t < n / 2; t += S) {
+            const uint16_t x = A[t], y = A[n - 1 - t];
+            A[t] = y;
+            A[n - 1 - t] = x;
         }
-        wave_sync();
-        if (active && rev) {
-            for (int t = k; t < n / 2; t += S) {
-                const uint16_t x = A[t], y = A[n - 1 - t];
-                A[t] = y;
-                A[n - 1 - t] = x;
-            }
-        }
-        wave_sync();
-    } else if (L->kind == 0) {
-        meta = cellular_offspring<LEAN>(I, L, slot, sub, gen, cur, A, B, V, k, S, g, active);
+    }
+    wave_sync();
+}
+
+// The chromosome of `slot` at generation `gen`, built in row A of a group of
+// S lanes (lane k): generation 0 (mode 1) draws it; a cellular cell gets the
+// child of its neighbourhood's two best from candidate stream `sub`; a pseudo
+// slot gets its pair's complementary child.
+__device__ __forceinline__ CellMeta make_child(const InstDesc* I, const IslandDesc* L, int slot, uint32_t sub,
+                                               int gen, int cur, int mode, uint16_t* A, int g, int k, int S,
+                                               bool active)
+{
+    const int n = I->n, n_pad = I->n_pad;
+    CellMeta meta{};
+    if (mode == 1) {
+        initial_row(I, L, slot, A, L->genes[cur] + (size_t)slot * n_pad, k, S, active);
+        return meta;
+    }
+    int p1, p2, mi, mj;
+    bool mx;
+    OxCut o;
+    if (L->kind == 0) {
+        const CellPlan pl = cell_plan(I, L, slot, sub, gen, cur);
+        meta = pl.meta;
+        p1 = pl.p1;
+        p2 = pl.p2;
+        o = ox_cut(n, meta.cx, meta.a, meta.b, false, false);
+        mx = meta.mx;
+        mi = meta.mi;
+        mj = meta.mj;
     } else {
         // pseudo: X = better of the pair, Y = reverse(X); even slot gets
         // OX(X, Y), odd slot OX(Y, X), with shared cut points.
         const PairPlan pl = pair_plan(I, L, slot, gen, cur);
-        if (active) row_g2l(V, L->genes[cur] + (size_t)pl.xs * n_pad, n_pad, k, S);
-        wave_sync();
-        pair_parents(A, B, V, n, pl.odd, k, S, active);
-        ox_group<!LEAN, !LEAN>(A, B, V, n, pl.a, pl.b, pl.cx && active, k, S, g);
-        swap_genes(A, pl.mx && active && k == 0, pl.mi, pl.mj);
+        p1 = p2 = pl.xs;
+        o = ox_cut(n, pl.cx, pl.a, pl.b, pl.odd, !pl.odd);
+        mx = pl.mx;
+        mi = pl.mi;
+        mj = pl.mj;
     }
+    const uint16_t* gp = L->genes[cur];
+    ox_group_rows(A, n_pad, gp + (size_t)p1 * n_pad, gp + (size_t)p2 * n_pad, o, g, k, S, active);
+    swap_genes(A, mx && active && k == 0, mi, mj);
     return meta;
 }
 
@@ -1188,26 +1478,27 @@ __global__ void __launch_bounds__(512) k_generation(const InstDesc* __restrict__
     const int cur = (gen + 1) & 1, nxt = gen & 1;
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint16_t* gbase = reinterpret_cast<uint16_t*>(ffs_smem + pt_lds_bytes<PT>(S, n_pad) +
-                                                  wave * wave_lds_bytes(G, n_pad));
+    const int stride = group_stride(I->n, n_pad, S);
+    uint16_t* gbase = reinterpret_cast<uint16_t*>(ffs_smem + pt_lds_bytes<PT>(S, n_pad)) + (size_t)wave * G * stride;
     const int g = lane / S, k = lane - g * S;
     const int local = wave * G + g;
     const bool active = (g < G) && (local < wi.count);
-    uint16_t* A = gbase + (size_t)(active ? g : 0) * group_stride(n_pad);
-    uint16_t* B = A + n_pad;
-    uint16_t* V = B + n_pad;
+    uint16_t* A = gbase + (size_t)(active ? g : 0) * stride;
+    // the row's padding is zero (readers of a row look up its genes unmasked)
+    if (active)
+        for (int t = I->n + k; t < n_pad; t += S) A[t] = 0;
     const int slot = wi.slot0 + (active ? local : 0);
 
     const bool screened = mode == 0 && L->kind == 0 && I->surr_k > 1 && gen > I->surr_warmup;
     const uint32_t sub = screened ? (uint32_t)I->surr_choice[L->cell_base + slot] : 0u;
-    const CellMeta meta = make_child(I, L, slot, sub, gen, cur, mode, A, B, V, k, S, g, active);
+    const CellMeta meta = make_child(I, L, slot, sub, gen, cur, mode, A, g, k, S, active);
 
     // waves past the work item's chromosomes have nothing to decode
     const int groups = wi.count - wave * G;
     uint32_t cm = 0u;
     if (groups > 0)
         cm = decode_pipelined<MMAX, PT>(
-            pipe_lane<PT>(gbase, group_stride(n_pad), pT, n_pad, lane, g, k, S, G, groups), I, active);
+            pipe_lane<PT>(gbase, stride, pT, n_pad, lane, g, k, S, G, groups), I, active);
     const int src = active ? (g * S + S - 1) : lane;
     const int cmg = __shfl((int)cm, src, 64);
 
@@ -1351,8 +1642,8 @@ __global__ void __launch_bounds__(512) k_candidates(const InstDesc* __restrict__
     __syncthreads();
     const int wpb = blockDim.x >> 6;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint16_t* gbase = reinterpret_cast<uint16_t*>(ffs_smem + pt_lds_bytes<PT>(S, n_pad) +
-                                                  wave * wave_lds_bytes(G, n_pad));
+    const int stride = group_stride(I->n, n_pad, S);
+    uint16_t* gbase = reinterpret_cast<uint16_t*>(ffs_smem + pt_lds_bytes<PT>(S, n_pad)) + (size_t)wave * G * stride;
     const int g = lane / S, k = lane - g * S;
     const int q = (blockIdx.x * wpb + wave) * G + g;
     const bool active = (g < G) && (q < Nc);
@@ -1367,17 +1658,15 @@ __global__ void __launch_bounds__(512) k_candidates(const InstDesc* __restrict__
             slot = cell - X->cell_base;
         }
     }
-    uint16_t* A = gbase + (size_t)(active ? g : 0) * group_stride(n_pad);
-    uint16_t* B = A + n_pad;
-    uint16_t* V = B + n_pad;
-    const CellMeta meta = cellular_offspring(I, L, slot, (uint32_t)c, gen, cur, A, B, V, k, S, g, active);
+    uint16_t* A = gbase + (size_t)(active ? g : 0) * stride;
+    const CellMeta meta = cellular_offspring(I, L, slot, (uint32_t)c, gen, cur, A, g, k, S, active);
     features_group<PT>(A, pT, I, k, active, meta, Xout + (size_t)qq * kFeat);
     if (Tout) {
         const int groups = Nc - (blockIdx.x * wpb + wave) * G;
         uint32_t cm = 0u;
         if (groups > 0)
             cm = decode_pipelined<MMAX, PT>(
-                pipe_lane<PT>(gbase, group_stride(n_pad), pT, n_pad, lane, g, k, S, G, groups), I, active);
+                pipe_lane<PT>(gbase, stride, pT, n_pad, lane, g, k, S, G, groups), I, active);
         const int cmg = __shfl((int)cm, active ? (g * S + S - 1) : lane, 64);
         if (active && k == 0) Tout[q] = __fdiv_rn((float)(cmg - I->LB), (float)I->LB);
     }

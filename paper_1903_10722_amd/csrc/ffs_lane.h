@@ -43,7 +43,7 @@ constexpr int kLaneMaxMsum = 160;    // machine entries per lane (sum over stage
 // later reused for the decode state (64 lanes x msum keys).
 __host__ __device__ inline size_t lane_gen_wave_lds(int n_pad, int msum)
 {
-    const size_t ops = (size_t)group_stride(n_pad) * 2;
+    const size_t ops = (size_t)wave_rows(n_pad) * 2;
     const size_t st = (size_t)64 * msum * 4;
     return align16(ops > st ? ops : st);
 }
@@ -371,10 +371,13 @@ __global__ void __launch_bounds__(512) k_generation_lane(const InstDesc* __restr
         uint16_t* A = reinterpret_cast<uint16_t*>(wbase);
         uint16_t* B = A + n_pad;
         uint16_t* V = B + n_pad;
+        // the rows' padding is zero (readers of a row look up its genes unmasked)
+        for (int t = n + lane; t < n_pad; t += kWave) A[t] = 0;
         if (mode == 1) {
             for (int c = 0; c < wcount; ++c) {
-                make_child<true>(I, L, slot_of(sbase + c), 0u, gen, cur, 1, A, B, V, lane, kWave, 0, true);
-                row_l2g(L->genes[nxt] + (size_t)slot_of(sbase + c) * n_pad, A, n_pad, lane, kWave);
+                const int slot = slot_of(sbase + c);
+                initial_row(I, L, slot, A, L->genes[cur] + (size_t)slot * n_pad, lane, kWave, true);
+                row_l2g(L->genes[nxt] + (size_t)slot * n_pad, A, n_pad, lane, kWave);
                 wave_sync();
             }
         } else if (wcount > 0) {
@@ -735,10 +738,10 @@ __global__ void __launch_bounds__(1024) k_cand_features(const InstDesc* __restri
     const int cell = blockIdx.x * (blockDim.x >> 6) + wave;
     if (cell >= cells) return;
     uint16_t* A = reinterpret_cast<uint16_t*>(pJ + align16((size_t)n * rsb) +
-                                              (size_t)wave * (group_stride(n_pad) * 2 + 240 * 4));
+                                              (size_t)wave * (wave_rows(n_pad) * 2 + 240 * 4));
     uint16_t* B = A + n_pad;
     uint16_t* V = B + n_pad;
-    uint32_t* acc = reinterpret_cast<uint32_t*>(A + group_stride(n_pad));
+    uint32_t* acc = reinterpret_cast<uint32_t*>(A + wave_rows(n_pad));
     // the cellular island holding this cell
     const IslandDesc* L = isls + I->island0;
     int slot = 0;
@@ -814,7 +817,7 @@ __global__ void __launch_bounds__(1024) k_cand_features(const InstDesc* __restri
 // LDS bytes of a k_cand_features workgroup of `waves` waves.
 __host__ __device__ inline size_t cand_lds_bytes(int n, int n_pad, int rsb, int waves)
 {
-    return align16((size_t)n * rsb) + (size_t)waves * ((size_t)group_stride(n_pad) * 2 + 240 * 4);
+    return align16((size_t)n * rsb) + (size_t)waves * ((size_t)wave_rows(n_pad) * 2 + 240 * 4);
 }
 
 }  // namespace flowshop
