@@ -10,8 +10,7 @@
 //     the list, in (completion, dispatch order), to the lane of stage k+1.
 //   * the genetic operators (Section 4.1-4.2: neighbourhood choice, order
 //     crossover, swap mutation, complementary pairs) run on the same group of
-//     lanes on chromosomes staged in LDS; the crossover's fill uses a wave
-//     ballot and a per-group prefix count.
+//     lanes, the parents in registers and the child in LDS.
 //   * populations live in HBM as rows of n_pad uint16 genes (slot-major,
 //     64-byte aligned rows), double buffered by generation parity.
 #pragma once
@@ -153,8 +152,9 @@ __host__ __device__ inline size_t wave_lds_bytes(int G, int n, int n_pad, int S)
     return (size_t)G * group_stride(n, n_pad, S) * 2;
 }
 
-// LDS of one wave that works on whole rows (three n_pad rows of uint16).
-__host__ __device__ inline int wave_rows(int n_pad) { return 3 * n_pad + 8; }
+// LDS entries of a wave that builds whole rows, one at a time.
+// Above 1024 jobs the crossover's marks have a row of their own.
+__host__ __device__ inline int wave_row(int n_pad) { return n_pad <= 1024 ? n_pad + 8 : 2 * n_pad + 8; }
 
 // The processing-time table is staged into LDS stage-major with each row
 // padded by 4 bytes, so that the S rows start on different LDS banks (the S
@@ -194,56 +194,7 @@ __device__ __forceinline__ void stage_pt(PT* dst, const void* src, int S, int n_
 }
 
 // ---- row copies by the S lanes of a group (16-byte vectors) ---------------
-// The global reads of a row are all issued before the LDS writes.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ void rows_g2l(uint16_t* dA, const uint16_t* sA, uint16_t* dB, const uint16_t* sB,
-                                         int n_pad, int k, int S)
-{
-    constexpr int U = 4;
-    const auto* a4 = as_global(reinterpret_cast<const u32x4*>(sA));
-    const auto* b4 = as_global(reinterpret_cast<const u32x4*>(sB));
-    u32x4* da = reinterpret_cast<u32x4*>(dA);
-    u32x4* db = reinterpret_cast<u32x4*>(dB);
-    const int nv = n_pad >> 3;
-    for (int v0 = k; v0 < nv; v0 += U * S) {
-        u32x4 xa[U], xb[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int v = v0 + u * S < nv ? v0 + u * S : nv - 1;
-            xa[u] = a4[v];
-            xb[u] = b4[v];
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            // past the end: the last vector again, with the same value
-            const int v = v0 + u * S < nv ? v0 + u * S : nv - 1;
-            da[v] = xa[u];
-            db[v] = xb[u];
-        }
-    }
-}
-
-__device__ __forceinline__ void row_g2l(uint16_t* dst, const uint16_t* src, int n_pad, int k, int S)
-{
-    constexpr int U = 4;
-    const auto* s4 = as_global(reinterpret_cast<const u32x4*>(src));
-    u32x4* d4 = reinterpret_cast<u32x4*>(dst);
-    const int nv = n_pad >> 3;
-    for (int v0 = k; v0 < nv; v0 += U * S) {
-        u32x4 x[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int v = v0 + u * S < nv ? v0 + u * S : nv - 1;
-            x[u] = s4[v];
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int v = v0 + u * S < nv ? v0 + u * S : nv - 1;
-            d4[v] = x[u];
-        }
-    }
-}
 
 __device__ __forceinline__ void row_g2g(uint16_t* dst, const uint16_t* src, int n_pad, int k, int S)
 {
@@ -555,206 +506,6 @@ __device__ __forceinline__ PipeLane<PT> pipe_lane(const uint16_t* gbase, int str
     return pl;
 }
 
-// ---- order crossover on a group -------------------------------------------
-// A = parent 1 (becomes the child), B = parent 2, V = scratch for the inverse
-// of parent 1.  child[a..b] = P1[a..b]; P2 read cyclically from b+1 fills
-// b+1, ..., n-1, 0, ..., a-1 with the genes not in the segment.  Lane k of
-// the group owns the cyclic offsets [kC, kC + C) of P2 (C = ceil(n / S)):
-// it counts the genes it keeps, an exclusive scan over the group's lanes
-// gives its first destination, and a second pass writes them.  REG and MID
-// select which register-holding paths are compiled (REG up to RMAX genes
-// per lane); without both only the two-pass path remains (fewest registers).
-__device__ __forceinline__ uint32_t wrap_sub(uint32_t x, uint32_t n)
-{
-    const uint32_t y = x - n;   // x < 2n: x mod n
-    return y < x ? y : x;
-}
-
-// Register path for C <= kOxReg: each lane reads its parent-1 and parent-2
-// genes once, so the whole crossover costs three LDS round trips plus the
-// group scan.
-constexpr int kOxReg = 24;
-constexpr int kOxMid = 64;   // rows with up to this many positions per lane keep P2 in registers
-
-__device__ __forceinline__ int group_exclusive_scan(int v, int k, int S)
-{
-    int incl = v;
-    for (int d = 1; d < S; d <<= 1) {
-        const int up = __shfl_up(incl, d, 64);
-        if (k >= d) incl += up;
-    }
-    return incl - v;
-}
-
-// Register path: lane k holds positions [o0, o1) of parent 1 and cyclic
-// offsets [o0, o1) of parent 2 (o1 - o0 <= CM), so the crossover costs three
-// LDS round trips plus the group scan.
-template <int CM>
-__device__ __forceinline__ void ox_reg(uint16_t* A, const uint16_t* B, uint16_t* V, uint32_t un, uint32_t ua,
-                                       uint32_t ub, bool doit, int k, int S, int o0, int o1)
-{
-    // lane k: positions [o0, o1) of parent 1 and cyclic offsets [o0, o1) of parent 2
-    uint32_t x1[CM], x2[CM];
-#pragma unroll
-    for (int u = 0; u < CM; ++u) {
-        const bool ok = o0 + u < o1;
-        x1[u] = A[ok ? o0 + u : 0];
-        x2[u] = B[ok ? wrap_sub(ub + 1u + (uint32_t)(o0 + u), un) : 0u];
-    }
-    if (doit) {
-#pragma unroll
-        for (int u = 0; u < CM; ++u)
-            if (o0 + u < o1) V[x1[u]] = (uint16_t)(o0 + u);
-    }
-    wave_sync();
-    uint32_t keep = 0;
-    int cnt = 0;
-#pragma unroll
-    for (int u = 0; u < CM; ++u) {
-        const uint32_t iv = V[x2[u]];
-        const bool kp = (o0 + u < o1) && (iv < ua || iv > ub);
-        keep |= kp ? (1u << u) : 0u;
-        cnt += kp ? 1 : 0;
-    }
-    const int pre = group_exclusive_scan(cnt, k, S);
-    if (doit) {
-        uint32_t dst = wrap_sub(ub + 1u + (uint32_t)pre, un);
-#pragma unroll
-        for (int u = 0; u < CM; ++u)
-            if (keep & (1u << u)) {
-                A[dst] = (uint16_t)x2[u];
-                dst = wrap_sub(dst + 1u, un);
-            }
-    }
-    wave_sync();
-}
-
-// Middle path: P2's genes held in registers between the count and the write.
-template <int CM>
-__device__ __forceinline__ void ox_mid(uint16_t* A, const uint16_t* B, uint16_t* V, uint32_t un, uint32_t ua,
-                                       uint32_t ub, bool doit, int k, int S, int o0, int o1)
-{
-    constexpr int U = 8;
-    if (doit) {
-        for (int t0 = o0; t0 < o1; t0 += U) {
-            uint32_t x[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = A[t0 + u < o1 ? t0 + u : 0];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (t0 + u < o1) V[x[u]] = (uint16_t)(t0 + u);
-        }
-    }
-    wave_sync();
-    uint32_t x2[CM];
-    unsigned long long keep = 0ull;
-    int cnt = 0;
-    if (doit) {
-#pragma unroll
-        for (int u = 0; u < CM; ++u) {
-            const uint32_t p = wrap_sub(ub + 1u + (uint32_t)(o0 + u), un);
-            x2[u] = B[(o0 + u < o1) ? p : 0u];
-        }
-#pragma unroll
-        for (int u = 0; u < CM; ++u) {
-            const uint32_t iv = V[x2[u]];
-            const bool kp = (o0 + u < o1) && (iv < ua || iv > ub);
-            keep |= kp ? (1ull << u) : 0ull;
-            cnt += kp ? 1 : 0;
-        }
-    }
-    const int pre = group_exclusive_scan(cnt, k, S);
-    if (doit) {
-        uint32_t dst = wrap_sub(ub + 1u + (uint32_t)pre, un);
-#pragma unroll
-        for (int u = 0; u < CM; ++u)
-            if (keep & (1ull << u)) {
-                A[dst] = (uint16_t)x2[u];
-                dst = wrap_sub(dst + 1u, un);
-            }
-    }
-    wave_sync();
-}
-
-template <bool REG = true, bool MID = true, int RMAX = kOxReg>
-__device__ __forceinline__ void ox_group(uint16_t* A, const uint16_t* B, uint16_t* V, int n, int a, int b,
-                                         bool doit, int k, int S, int g)
-{
-    const uint32_t un = (uint32_t)n, ua = (uint32_t)a, ub = (uint32_t)b;
-    const int C = (n + S - 1) / S;
-    const int o0 = k * C, o1 = (o0 + C < n) ? o0 + C : n;
-    if (REG && C <= 8) {
-        ox_reg<8>(A, B, V, un, ua, ub, doit, k, S, o0, o1);
-        return;
-    }
-    if (REG && RMAX >= 16 && C <= 16) {
-        ox_reg<16>(A, B, V, un, ua, ub, doit, k, S, o0, o1);
-        return;
-    }
-    if (REG && RMAX >= kOxReg && C <= kOxReg) {
-        ox_reg<kOxReg>(A, B, V, un, ua, ub, doit, k, S, o0, o1);
-        return;
-    }
-    if (MID && C <= 32) {
-        ox_mid<32>(A, B, V, un, ua, ub, doit, k, S, o0, o1);
-        return;
-    }
-    if (MID && C <= kOxMid) {
-        ox_mid<kOxMid>(A, B, V, un, ua, ub, doit, k, S, o0, o1);
-        return;
-    }
-    // long rows: two passes over P2 in chunks of U
-    constexpr int U = 8;
-    if (doit) {
-        for (int t0 = o0; t0 < o1; t0 += U) {
-            uint32_t x[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = A[t0 + u < o1 ? t0 + u : 0];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (t0 + u < o1) V[x[u]] = (uint16_t)(t0 + u);
-        }
-    }
-    wave_sync();
-    int cnt = 0;
-    if (doit) {
-        for (int ob = o0; ob < o1; ob += U) {
-            uint32_t x[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t p = wrap_sub(ub + 1u + (uint32_t)(ob + u), un);
-                x[u] = B[(ob + u < o1) ? p : 0u];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t iv = V[x[u]];
-                cnt += (ob + u < o1 && (iv < ua || iv > ub)) ? 1 : 0;
-            }
-        }
-    }
-    const int pre = group_exclusive_scan(cnt, k, S);
-    if (doit) {
-        uint32_t dst = wrap_sub(ub + 1u + (uint32_t)pre, un);
-        for (int ob = o0; ob < o1; ob += U) {
-            uint32_t x[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t p = wrap_sub(ub + 1u + (uint32_t)(ob + u), un);
-                x[u] = B[(ob + u < o1) ? p : 0u];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t iv = V[x[u]];
-                if (ob + u < o1 && (iv < ua || iv > ub)) {
-                    A[dst] = (uint16_t)x[u];
-                    dst = wrap_sub(dst + 1u, un);
-                }
-            }
-        }
-    }
-    wave_sync();
-}
-
 // ---- order crossover on rows read as vectors --------------------------------
 // child[a..b] = P1[a..b]; P2 read cyclically from b+1 fills b+1, ..., n-1, 0,
 // ..., a-1 with the genes not in the segment (a = 0, b = n - 1: the child is
@@ -841,42 +592,71 @@ __device__ __forceinline__ int ox_keep(const uint16_t* M, const u32x4 (&x)[VC], 
     return cnt;
 }
 
+// Parent 1's genes at their positions in the child.  Those outside the
+// segment are overwritten by the kept genes, so a parent that is not reversed
+// goes in as whole vectors.
 template <int VC>
 __device__ __forceinline__ void ox_place1(uint16_t* A, const u32x4 (&x)[VC], const OxCut& o, int v0, int vpl, int lim)
 {
-    const int st = o.rev1 ? -1 : 1;
-    int p = o.rev1 ? o.n - 1 - 8 * v0 : 8 * v0;
+    if (!o.rev1) {
+        u32x4* a4 = reinterpret_cast<u32x4*>(A) + v0;
 #pragma unroll
-    for (int v = 0; v < VC; ++v)
-        if (v < vpl) {
+        for (int v = 0; v < VC; ++v)
+            if (v < vpl && 8 * v < lim) a4[v] = x[v];
+    } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                if (8 * v + e < lim && (uint32_t)(p - o.a) <= (uint32_t)o.len) A[p] = (uint16_t)ox_gene(x[v], e);
-                p += st;
+        for (int v = 0; v < VC; ++v)
+            if (v < vpl) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (8 * v + e < lim) A[o.n - 1 - 8 * (v0 + v) - e] = (uint16_t)ox_gene(x[v], e);
             }
-        }
+    }
 }
 
-// Writes the kept genes from the place `idx` of the first one on (places are
-// the free positions in ascending order); returns the next place.
+// The free positions in P2's order: from one, the next is beside it, with the
+// segment and the row's end skipped.
+struct OxStep {
+    int st, seg, seg_to, end, end_to;
+};
+
+__device__ __forceinline__ OxStep ox_step(const OxCut& o)
+{
+    const int b1 = o.a + o.len + 1;
+    OxStep s;
+    s.st = o.rev2 ? -1 : 1;
+    s.seg = o.rev2 ? b1 - 1 : o.a;
+    s.seg_to = o.rev2 ? o.a - 1 : b1;
+    s.end = o.rev2 ? -1 : o.n;
+    s.end_to = o.rev2 ? (b1 == o.n ? o.a - 1 : o.n - 1) : (o.a == 0 ? b1 : 0);
+    return s;
+}
+
+__device__ __forceinline__ int ox_next(const OxStep& s, int pos)
+{
+    pos += s.st;
+    pos = pos == s.seg ? s.seg_to : pos;
+    return pos == s.end ? s.end_to : pos;
+}
+
+// Writes the kept genes from position `pos` of the first one on; returns the
+// next position.
 template <int VC>
 __device__ __forceinline__ int ox_place2(uint16_t* A, const u32x4 (&x)[VC], const uint32_t (&keep)[VC], const OxCut& o,
-                                         int vpl, int idx)
+                                         int vpl, int pos)
 {
-    const int T = o.n - 1 - o.len, len1 = o.len + 1;
-    const int st = o.rev2 ? -1 : 1, wrap = o.rev2 ? -1 : T, to = o.rev2 ? T - 1 : 0;
+    const OxStep s = ox_step(o);
 #pragma unroll
     for (int v = 0; v < VC; ++v)
         if (v < vpl) {
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 if (keep[v] & (0x80u >> e)) {
-                    A[idx + (idx >= o.a ? len1 : 0)] = (uint16_t)ox_gene(x[v], e);
-                    idx += st;
-                    idx = idx == wrap ? to : idx;
+                    A[pos] = (uint16_t)ox_gene(x[v], e);
+                    pos = ox_next(s, pos);
                 }
         }
-    return idx;
+    return pos;
 }
 
 // Inclusive sum over the wave's lanes (DPP: 1, 2, 4, 8 inside 16-lane rows,
@@ -898,8 +678,8 @@ __device__ __forceinline__ int wave_scan(int x)
     return x;
 }
 
-// Place of the first kept gene of this lane from the scanned counts: `excl`
-// kept genes on the lanes before it, `after` kept genes after b in all.
+// Position of the first kept gene of this lane from the scanned counts:
+// `excl` kept genes on the lanes before it, `after` kept genes after b in all.
 __device__ __forceinline__ int ox_first(const OxCut& o, int excl, int after)
 {
     const int T = o.n - 1 - o.len;
@@ -908,7 +688,8 @@ __device__ __forceinline__ int ox_first(const OxCut& o, int excl, int after)
     z -= z >= 2 * T ? 2 * T : (z >= T ? T : 0);
     int idx = (o.rev2 ? T - 1 - excl : excl) + z;   // excl <= T
     idx = idx < 0 ? idx + T : idx;
-    return idx >= T ? (idx >= 2 * T ? idx - 2 * T : idx - T) : idx;
+    idx = idx >= T ? (idx >= 2 * T ? idx - 2 * T : idx - T) : idx;
+    return idx + (idx >= o.a ? o.len + 1 : 0);
 }
 
 // Counts of the lanes below in this group and after-b total of the group.
@@ -934,19 +715,67 @@ __device__ __forceinline__ void ox_group_regs(uint16_t* A, const uint16_t* P1, c
     ox_mark<VC>(A, x1, o, v0, vpl, lim);
     wave_sync();
     const int cnt = ox_keep<VC>(A, x2, keep, o, v0, vpl, lim);
-    const int idx = ox_group_first(o, cnt, g, S);
+    const int pos = ox_group_first(o, cnt, g, S);
     wave_sync();
     ox_place1<VC>(A, x1, o, v0, vpl, lim);
-    ox_place2<VC>(A, x2, keep, o, vpl, idx);
+    wave_sync();
+    ox_place2<VC>(A, x2, keep, o, vpl, pos);
     wave_sync();
 }
 
-// Longer rows: the same passes over chunks of four vectors, read from HBM
+// The crossover of a whole wave on one row of up to 512 VC genes: lane l
+// holds vectors [VC l, VC l + VC) of both parents, already in registers.  The
+// kept genes of each vector entry are one wave mask, so the counts below a
+// lane come from mask bit counts instead of a scan over the lanes.  About 170
+// VALU and 26 to 33 LDS instructions a child at 500 jobs (from 240 and 50 to
+// 80, with a reversed copy for pseudo pairs): a large generation 724 -> 690 us,
+// the pre-screen's candidates of 1000 jobs 145 -> 125 us.
+template <int VC>
+__device__ __forceinline__ void ox_wave(uint16_t* A, const u32x4 (&x1)[VC], const u32x4 (&x2)[VC], const OxCut& o,
+                                        int lane)
+{
+    constexpr int C = 8 * VC;
+    const int lim = o.n - C * lane;
+    ox_mark<VC>(A, x1, o, VC * lane, VC, lim);
+    wave_sync();
+    uint32_t m[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) m[i] = A[ox_gene(x2[i >> 3], i & 7)];
+    // entries of lane l lie after position b in P2's order from lane
+    // (q - i + C) / C on (below it if reversed)
+    const int b = o.a + o.len, q = o.rev2 ? o.n - 2 - b : b;
+    bool kp[C];
+    uint32_t excl = 0;
+    int after = 0;
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        kp[i] = i < lim && m[i] > (uint32_t)o.len;
+        const uint64_t bal = __ballot(kp[i]);
+        excl = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, excl));
+        const int s = (q - i + C) / C;   // q - i + C >= 0
+        const uint64_t up = s < 64 ? ~0ull << s : 0ull;
+        after += __popcll(bal & (o.rev2 ? ~up : up));
+    }
+    wave_sync();
+    ox_place1<VC>(A, x1, o, VC * lane, VC, lim);
+    wave_sync();
+    int pos = ox_first(o, (int)excl, after);
+    const OxStep st = ox_step(o);
+#pragma unroll
+    for (int i = 0; i < C; ++i)
+        if (kp[i]) {
+            A[pos] = (uint16_t)ox_gene(x2[i >> 3], i & 7);
+            pos = ox_next(st, pos);
+        }
+    wave_sync();
+}
+
+// Longer rows: the same passes over chunks of VC vectors, read from HBM
 // (L2) once per pass, with the marks in a row of their own.
+template <int VC>
 __device__ __forceinline__ void ox_group_long(uint16_t* A, uint16_t* M, const uint16_t* P1, const uint16_t* P2,
                                               const OxCut& o, int vpl, int g, int k, int S, bool active)
 {
-    constexpr int VC = 4;
     const int nv = (o.n + 7) >> 3, v0 = k * vpl, v1 = v0 + vpl;
     u32x4 x[VC];
     uint32_t keep[VC];
@@ -963,16 +792,28 @@ __device__ __forceinline__ void ox_group_long(uint16_t* A, uint16_t* M, const ui
         ox_load<VC>(x, P2, v, c, nv);
         cnt += ox_keep<VC>(M, x, keep, o, v, c, lim(v));
     }
-    int idx = ox_group_first(o, cnt, g, S);
+    int pos = ox_group_first(o, cnt, g, S);
     for (int v = v0; v < v1; v += VC) {
         const int c = v1 - v < VC ? v1 - v : VC;
         ox_load<VC>(x, P1, v, c, nv);
         ox_place1<VC>(A, x, o, v, c, lim(v));
-        ox_load<VC>(x, P2, v, c, nv);
-        ox_keep<VC>(M, x, keep, o, v, c, lim(v));
-        idx = ox_place2<VC>(A, x, keep, o, c, idx);
     }
     wave_sync();
+    for (int v = v0; v < v1; v += VC) {
+        const int c = v1 - v < VC ? v1 - v : VC;
+        ox_load<VC>(x, P2, v, c, nv);
+        ox_keep<VC>(M, x, keep, o, v, c, lim(v));
+        pos = ox_place2<VC>(A, x, keep, o, c, pos);
+    }
+    wave_sync();
+}
+
+// The whole wave on a row of more than 1024 genes, as a function of its own
+// (its registers and code stay out of the callers' main path).
+__device__ __attribute__((noinline)) void ox_wave_long(uint16_t* A, uint16_t* M, const uint16_t* P1,
+                                                       const uint16_t* P2, OxCut o, int lane)
+{
+    ox_group_long<2>(A, M, P1, P2, o, ox_vectors(o.n, kWave), 0, lane, kWave, true);
 }
 
 __device__ __forceinline__ void ox_group_rows(uint16_t* A, int n_pad, const uint16_t* P1, const uint16_t* P2,
@@ -982,7 +823,7 @@ __device__ __forceinline__ void ox_group_rows(uint16_t* A, int n_pad, const uint
     if (vpl <= 3) ox_group_regs<3>(A, P1, P2, o, vpl, g, k, S, active);
     else if (vpl <= 7) ox_group_regs<7>(A, P1, P2, o, vpl, g, k, S, active);
     else if (vpl <= kOxVec) ox_group_regs<kOxVec>(A, P1, P2, o, vpl, g, k, S, active);
-    else ox_group_long(A, A + n_pad, P1, P2, o, vpl, g, k, S, active);
+    else ox_group_long<4>(A, A + n_pad, P1, P2, o, vpl, g, k, S, active);
 }
 
 __device__ __forceinline__ void swap_genes(uint16_t* A, bool doit, int i, int j)
@@ -1173,31 +1014,6 @@ __device__ __forceinline__ PairPlan pair_plan(const InstDesc* I, const IslandDes
     if (mj >= n) mj -= n;
     pl.mj = mj;
     return pl;
-}
-
-// A = X (even slot) or reverse(X) (odd slot) and B the other, from X in V.
-__device__ __forceinline__ void pair_parents(uint16_t* A, uint16_t* B, const uint16_t* V, int n, bool odd, int k,
-                                             int S, bool active)
-{
-    if (active) {
-        constexpr int U = 4;
-        for (int t0 = k; t0 < n; t0 += U * S) {
-            uint16_t x[U], xr[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = t0 + u * S < n ? t0 + u * S : n - 1;
-                x[u] = V[t];
-                xr[u] = V[n - 1 - t];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = t0 + u * S < n ? t0 + u * S : n - 1;
-                A[t] = odd ? xr[u] : x[u];
-                B[t] = odd ? x[u] : xr[u];
-            }
-        }
-    }
-    wave_sync();
 }
 
 // Pre-screen input of the chromosome in A (the group's S lanes): lane k sums

@@ -32,6 +32,8 @@
 // there, then writes back the parent's row of every cellular cell whose
 // child is not strictly better.
 #pragma once
+#include <type_traits>
+
 #include "ffs_kernels.h"
 
 namespace flowshop {
@@ -39,11 +41,10 @@ namespace flowshop {
 constexpr int kLaneD = 16;           // slots per window
 constexpr int kLaneMaxMsum = 160;    // machine entries per lane (sum over stages) kept in LDS
 
-// LDS of one wave of the lane generation kernel: the operators' three rows,
-// later reused for the decode state (64 lanes x msum keys).
+// LDS of one wave of the lane generation kernel: the operators' row, later reused for the decode state (64 lanes x msum keys).
 __host__ __device__ inline size_t lane_gen_wave_lds(int n_pad, int msum)
 {
-    const size_t ops = (size_t)wave_rows(n_pad) * 2;
+    const size_t ops = (size_t)wave_row(n_pad) * 2;
     const size_t st = (size_t)64 * msum * 4;
     return align16(ops > st ? ops : st);
 }
@@ -369,9 +370,7 @@ __global__ void __launch_bounds__(512) k_generation_lane(const InstDesc* __restr
     // rows of the next one are already on their way into registers.
     {
         uint16_t* A = reinterpret_cast<uint16_t*>(wbase);
-        uint16_t* B = A + n_pad;
-        uint16_t* V = B + n_pad;
-        // the rows' padding is zero (readers of a row look up its genes unmasked)
+        // the row's padding is zero (readers of a row look up its genes unmasked)
         for (int t = n + lane; t < n_pad; t += kWave) A[t] = 0;
         if (mode == 1) {
             for (int c = 0; c < wcount; ++c) {
@@ -392,64 +391,67 @@ __global__ void __launch_bounds__(512) k_generation_lane(const InstDesc* __restr
                         (pl.meta.mx ? 1u << 25 : 0u);
                 w_mut = (uint32_t)pl.meta.mi | ((uint32_t)pl.meta.mj << 12);
             } else {
+                // both parents are X's row; bit 15: the odd slot of the pair
                 const PairPlan pl = pair_plan(I, L, pslot, gen, cur);
-                w_src = (uint32_t)pl.xs | (pl.odd ? 1u << 31 : 0u);
+                w_src = (uint32_t)pl.xs | ((uint32_t)pl.xs << 16) | (pl.odd ? 1u << 15 : 0u);
                 w_cut = (uint32_t)pl.a | ((uint32_t)pl.b << 12) | (pl.cx ? 1u << 24 : 0u) | (pl.mx ? 1u << 25 : 0u);
                 w_mut = (uint32_t)pl.mi | ((uint32_t)pl.mj << 12);
             }
-            const int nv = n_pad >> 3;                   // 16-byte vectors per row
-            constexpr int PV = 2;                         // vectors per lane per row held in registers
-            const bool pre = nv <= PV * kWave;            // rows of up to 1024 genes
-            const auto* g4 = as_global(reinterpret_cast<const u32x4*>(L->genes[cur]));
-            const auto* g4n = as_global(reinterpret_cast<const u32x4*>(L->genes[nxt]));
-            u32x4 ra[PV], rb[PV];
-            auto fetch = [&](int c) {
-                const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)w_src, c);
-                const size_t r1 = (size_t)(cell ? (src & 0x7FFFu) : (src & 0x7FFFFFFFu)) * nv;
-                const size_t r2 = (size_t)((src >> 16) & 0x7FFFu) * nv;
-                const auto* s1 = (cell && (src & 0x8000u)) ? g4n : g4;
-                const auto* s2 = (cell && (src >> 31)) ? g4n : g4;
-#pragma unroll
-                for (int v = 0; v < PV; ++v) {
-                    const int x = lane + v * kWave;
-                    if (x < nv) {
-                        ra[v] = s1[r1 + x];
-                        if (cell) rb[v] = s2[r2 + x];
-                    }
-                }
+            auto parent1 = [&](uint32_t src) {
+                return L->genes[cell && (src & 0x8000u) ? nxt : cur] + (size_t)(src & 0x7FFFu) * n_pad;
             };
-            if (pre) fetch(0);
-            for (int c = 0; c < wcount; ++c) {
-                const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)w_src, c);
+            auto parent2 = [&](uint32_t src) {
+                return L->genes[cell && (src >> 31) ? nxt : cur] + (size_t)((src >> 16) & 0x7FFFu) * n_pad;
+            };
+            auto cut_of = [&](uint32_t src, uint32_t cut) {
+                const bool odd = !cell && (src & 0x8000u);
+                return ox_cut(n, ((cut >> 24) & 1u) != 0u, (int)(cut & 0xFFFu), (int)((cut >> 12) & 0xFFFu), odd,
+                              !cell && !odd);
+            };
+            auto finish = [&](int c) {
                 const uint32_t cut = (uint32_t)__builtin_amdgcn_readlane((int)w_cut, c);
                 const uint32_t mut = (uint32_t)__builtin_amdgcn_readlane((int)w_mut, c);
-                const int slot = slot_of(sbase + c);
-                if (pre) {
-                    u32x4* da = reinterpret_cast<u32x4*>(cell ? A : V);
-                    u32x4* db = reinterpret_cast<u32x4*>(B);
-#pragma unroll
-                    for (int v = 0; v < PV; ++v) {
-                        const int x = lane + v * kWave;
-                        if (x < nv) {
-                            da[x] = ra[v];
-                            if (cell) db[x] = rb[v];
-                        }
-                    }
-                } else if (cell) {
-                    rows_g2l(A, L->genes[(src & 0x8000u) ? nxt : cur] + (size_t)(src & 0x7FFFu) * n_pad, B,
-                             L->genes[(src >> 31) ? nxt : cur] + (size_t)((src >> 16) & 0x7FFFu) * n_pad, n_pad,
-                             lane, kWave);
-                } else {
-                    row_g2l(V, L->genes[cur] + (size_t)(src & 0x7FFFFFFFu) * n_pad, n_pad, lane, kWave);
-                }
-                wave_sync();
-                if (pre && c + 1 < wcount) fetch(c + 1);
-                if (!cell) pair_parents(A, B, V, n, (src >> 31) != 0u, lane, kWave, true);
-                ox_group<true, false>(A, B, V, n, (int)(cut & 0xFFFu), (int)((cut >> 12) & 0xFFFu),
-                                      ((cut >> 24) & 1u) != 0u, lane, kWave, 0);
                 swap_genes(A, ((cut >> 25) & 1u) != 0u && lane == 0, (int)(mut & 0xFFFu), (int)(mut >> 12));
-                row_l2g(L->genes[nxt] + (size_t)slot * n_pad, A, n_pad, lane, kWave);
+                row_l2g(L->genes[nxt] + (size_t)slot_of(sbase + c) * n_pad, A, n_pad, lane, kWave);
                 wave_sync();
+            };
+            auto build = [&](auto vc) {
+                constexpr int VC = decltype(vc)::value;
+                u32x4 ra[VC], rb[VC];
+                const int nv = (n + 7) >> 3;
+                auto fetch = [&](int c) {
+                    const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)w_src, c);
+                    ox_load<VC>(ra, parent1(src), VC * lane, VC, nv);
+                    if (cell) ox_load<VC>(rb, parent2(src), VC * lane, VC, nv);
+                };
+                fetch(0);
+                for (int c = 0; c < wcount; ++c) {
+                    const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)w_src, c);
+                    const uint32_t cut = (uint32_t)__builtin_amdgcn_readlane((int)w_cut, c);
+                    u32x4 x1[VC], x2[VC];
+#pragma unroll
+                    for (int v = 0; v < VC; ++v) {
+                        x1[v] = ra[v];
+                        x2[v] = cell ? rb[v] : ra[v];
+                    }
+                    if (c + 1 < wcount) fetch(c + 1);
+                    ox_wave<VC>(A, x1, x2, cut_of(src, cut), lane);
+                    finish(c);
+                }
+            };
+            // up to 512 and 1024 jobs the next child's parents are read while
+            // this one is built; longer rows are read when they are needed
+            if (n <= 512) {
+                build(std::integral_constant<int, 1>{});
+            } else if (n <= 1024) {
+                build(std::integral_constant<int, 2>{});
+            } else {
+                for (int c = 0; c < wcount; ++c) {
+                    const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)w_src, c);
+                    const uint32_t cut = (uint32_t)__builtin_amdgcn_readlane((int)w_cut, c);
+                    ox_wave_long(A, A + n_pad, parent1(src), parent2(src), cut_of(src, cut), lane);
+                    finish(c);
+                }
             }
         }
     }
@@ -738,10 +740,8 @@ __global__ void __launch_bounds__(1024) k_cand_features(const InstDesc* __restri
     const int cell = blockIdx.x * (blockDim.x >> 6) + wave;
     if (cell >= cells) return;
     uint16_t* A = reinterpret_cast<uint16_t*>(pJ + align16((size_t)n * rsb) +
-                                              (size_t)wave * (wave_rows(n_pad) * 2 + 240 * 4));
-    uint16_t* B = A + n_pad;
-    uint16_t* V = B + n_pad;
-    uint32_t* acc = reinterpret_cast<uint32_t*>(A + wave_rows(n_pad));
+                                              (size_t)wave * (wave_row(n_pad) * 2 + 240 * 4));
+    uint32_t* acc = reinterpret_cast<uint32_t*>(A + wave_row(n_pad));
     // the cellular island holding this cell
     const IslandDesc* L = isls + I->island0;
     int slot = 0;
@@ -758,27 +758,13 @@ __global__ void __launch_bounds__(1024) k_cand_features(const InstDesc* __restri
                            (pl.meta.mx ? 1u << 25 : 0u);
     const uint32_t w_mut = (uint32_t)pl.meta.mi | ((uint32_t)pl.meta.mj << 12);
     const uint16_t* gp = L->genes[cur];
-    // the parents' rows of the next candidate are read into registers while
-    // the current one is built (rows of up to 1024 genes)
-    const int nv = n_pad >> 3;
-    constexpr int PV2 = 2;
-    const bool pre = nv <= PV2 * kWave;
-    const auto* g4 = as_global(reinterpret_cast<const u32x4*>(gp));
-    u32x4 ra[PV2], rb[PV2];
-    auto fetch = [&](int c) {
+    for (int t = n + lane; t < n_pad; t += kWave) A[t] = 0;   // the row's padding
+    auto parents = [&](int c, const uint16_t*& p1, const uint16_t*& p2) {
         const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)w_src, c);
-#pragma unroll
-        for (int v = 0; v < PV2; ++v) {
-            const int x = lane + v * kWave;
-            if (x < nv) {
-                ra[v] = g4[(size_t)(src & 0xFFFFu) * nv + x];
-                rb[v] = g4[(size_t)(src >> 16) * nv + x];
-            }
-        }
+        p1 = gp + (size_t)(src & 0xFFFFu) * n_pad;
+        p2 = gp + (size_t)(src >> 16) * n_pad;
     };
-    if (pre) fetch(0);
-    for (int c = 0; c < K; ++c) {
-        const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)w_src, c);
+    auto meta = [&](int c) {
         const uint32_t cut = (uint32_t)__builtin_amdgcn_readlane((int)w_cut, c);
         const uint32_t mut = (uint32_t)__builtin_amdgcn_readlane((int)w_mut, c);
         CellMeta cm;
@@ -790,34 +776,58 @@ __global__ void __launch_bounds__(1024) k_cand_features(const InstDesc* __restri
         cm.mx = ((cut >> 25) & 1u) != 0u;
         cm.mi = (int)(mut & 0xFFFu);
         cm.mj = (int)(mut >> 12);
-        if (pre) {
-            u32x4* da = reinterpret_cast<u32x4*>(A);
-            u32x4* db = reinterpret_cast<u32x4*>(B);
-#pragma unroll
-            for (int v = 0; v < PV2; ++v) {
-                const int x = lane + v * kWave;
-                if (x < nv) {
-                    da[x] = ra[v];
-                    db[x] = rb[v];
-                }
-            }
-        } else {
-            rows_g2l(A, gp + (size_t)(src & 0xFFFFu) * n_pad, B, gp + (size_t)(src >> 16) * n_pad, n_pad, lane,
-                     kWave);
-        }
-        wave_sync();
-        if (pre && c + 1 < K) fetch(c + 1);
-        ox_group<true, false, 16>(A, B, V, n, cm.a, cm.b, cm.cx, lane, kWave, 0);
+        return cm;
+    };
+    auto finish = [&](int c, const CellMeta& cm) {
         swap_genes(A, cm.mx && lane == 0, cm.mi, cm.mj);
         cand_features<SM, PT>(A, pJ, rsb, I, cm, acc, lane, Xout + ((size_t)cell * K + c) * kFeat);
         wave_sync();
+    };
+    auto build = [&](auto vc) {
+        constexpr int VC = decltype(vc)::value;
+        u32x4 ra[VC], rb[VC];
+        const int nv = (n + 7) >> 3;
+        auto fetch = [&](int c) {
+            const uint16_t *p1, *p2;
+            parents(c, p1, p2);
+            ox_load<VC>(ra, p1, VC * lane, VC, nv);
+            ox_load<VC>(rb, p2, VC * lane, VC, nv);
+        };
+        fetch(0);
+        for (int c = 0; c < K; ++c) {
+            const CellMeta cm = meta(c);
+            u32x4 x1[VC], x2[VC];
+#pragma unroll
+            for (int v = 0; v < VC; ++v) {
+                x1[v] = ra[v];
+                x2[v] = rb[v];
+            }
+            if (c + 1 < K) fetch(c + 1);
+            ox_wave<VC>(A, x1, x2, ox_cut(n, cm.cx, cm.a, cm.b, false, false), lane);
+            finish(c, cm);
+        }
+    };
+    // up to 512 and 1024 jobs the next candidate's parents are read while this
+    // one is built; longer rows are read when they are needed
+    if (n <= 512) {
+        build(std::integral_constant<int, 1>{});
+    } else if (n <= 1024) {
+        build(std::integral_constant<int, 2>{});
+    } else {
+        for (int c = 0; c < K; ++c) {
+            const CellMeta cm = meta(c);
+            const uint16_t *p1, *p2;
+            parents(c, p1, p2);
+            ox_wave_long(A, A + n_pad, p1, p2, ox_cut(n, cm.cx, cm.a, cm.b, false, false), lane);
+            finish(c, cm);
+        }
     }
 }
 
 // LDS bytes of a k_cand_features workgroup of `waves` waves.
 __host__ __device__ inline size_t cand_lds_bytes(int n, int n_pad, int rsb, int waves)
 {
-    return align16((size_t)n * rsb) + (size_t)waves * ((size_t)wave_rows(n_pad) * 2 + 240 * 4);
+    return align16((size_t)n * rsb) + (size_t)waves * ((size_t)wave_row(n_pad) * 2 + 240 * 4);
 }
 
 }  // namespace flowshop
