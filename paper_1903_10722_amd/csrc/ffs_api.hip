@@ -49,12 +49,13 @@ __global__ void __launch_bounds__(256) k_build_table(const int* __restrict__ p, 
 // UB = min(sum of all p, sum_k (floor(P_k / m_k) + pmax_k)): at a stage, a job
 // that waits finds every machine busy from its ready time with jobs dispatched
 // before it, so it starts at most floor(P_k / m_k) after it, and every ready
-// time is a completion of the stage before.  The pipelined decode's indexed
-// key holds UB below the padding's value (checked: 1.5 times the lower bound
-// LB; makespans above it fall back to the two-field key).  fsh: the lane
-// decode's completion shift of its three-field key, 0 if that is not used.
+// time is a completion of the stage before.  The indexed key holds every
+// completion up to UB (the pipelined decode's below its padding's value), or,
+// checked, up to 1.5 times the lower bound LB, which random and evolved
+// permutations stay below (they take 1.02 to 1.2 times LB on the workloads);
+// a wave that meets a longer schedule decodes again with the two-field key.
 struct DecodeKeys {
-    int fsh, pkey;
+    int lkey, pkey;
 };
 
 static DecodeKeys decode_keys(int n, int S, const int* m, const int* p, int jb, int mmax)
@@ -79,11 +80,12 @@ static DecodeKeys decode_keys(int n, int S, const int* m, const int* p, int jb, 
         UB += P[k] / m[k] + pmax[k];
     }
     UB = std::min(UB, E);
+    auto format = [&](long long cap) {   // completions below cap fit
+        return UB < cap ? kKeyIdx : (3 * LB < 2 * cap ? kKeyIdxChecked : kKeyTwo);
+    };
     DecodeKeys d;
-    const bool three = 2 * jb <= 30;
-    d.fsh = (three && 3 * LB < 2 * (1ll << (32 - 2 * jb))) ? 2 * jb : 0;
-    const long long cap = (1ll << (32 - jb - pipe_index_bits(mmax))) - 1;
-    d.pkey = UB < cap ? kKeyIdx : (3 * LB < 2 * cap ? kKeyIdxChecked : kKeyTwo);
+    d.lkey = format(1ll << (32 - jb - kLaneIndexBits));
+    d.pkey = format((1ll << (32 - jb - pipe_index_bits(mmax))) - 1);
     return d;
 }
 
@@ -1401,7 +1403,7 @@ int ffs_bind_workspace(ffs_ctx* c, void* dptr, size_t bytes)
         d.jb = I.jb;
         d.G = I.G;
         const DecodeKeys dk = decode_keys(I.n, I.S, I.m.data(), I.p.data(), I.jb, c->mm);
-        d.fsh = dk.fsh;
+        d.lkey = dk.lkey;
         d.pkey = dk.pkey;
         d.island0 = isl_base;
         d.n_islands = (int)I.isl.size();
@@ -2080,7 +2082,7 @@ int ffs_evaluate_noalloc(void* hip_stream, int32_t n, int32_t S, const int32_t* 
     d.n_pad = n_pad;
     d.jb = jb;
     const DecodeKeys dk = decode_keys(n, S, machines, p, jb, mm);
-    d.fsh = dk.fsh;
+    d.lkey = dk.lkey;
     d.pkey = dk.pkey;
     d.G = std::min(kWave / S, std::max(1, 32768 / (2 * group_stride(n, n_pad, S))));
     d.msum = msum;

@@ -58,60 +58,96 @@ __host__ __device__ inline size_t lane_eval_wave_lds(int n, int msum)
     return align16(st > seen ? st : seen);
 }
 
-// One stage over one window.  r[i] holds slot lo + i: a key from the
-// previous stage, or a gene at stage 0 (completion 0).  Key formats:
-//   F = false: completion << jb | job.  A new key goes after every entry
-//     with the same completion (those were dispatched earlier), by a
-//     threshold compare per entry.
-//   F = true:  completion << sh | dispatch index << jb | job (sh = 2 jb),
-//     the dispatch index counting this stage's dispatches.  Keys of one
-//     list are then distinct and their numeric order is (completion,
-//     dispatch order), so the new key goes in by one min, max or median
-//     per entry.  The completions must stay below 2^(32 - sh): cor
-//     collects the bits of every completion for the caller's check.
+// Index field of the lane decode's keys (see KeyFormat): a stage's list takes
+// the indices below kLaneFirst at the start of a window, the window's slot i
+// the index kLaneFirst + i.
+constexpr int kLaneFirst = 8;       // >= machines per stage
+constexpr int kLaneIndexBits = 5;   // kLaneFirst + kLaneD <= 32
+
+// (x & m) | o and (m & x) | (~m & y), one VALU operation each.
+__device__ __forceinline__ uint32_t and_or(uint32_t x, uint32_t m, uint32_t o)
+{
+    uint32_t r;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(m), "s"(o));
+    return r;
+}
+
+__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t x, uint32_t y)
+{
+    uint32_t r;
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(m), "v"(x), "v"(y));
+    return r;
+}
+
+// sorted list key[0 .. M-1] without key[0] and with nk
+template <int M>
+__device__ __forceinline__ void lane_insert(uint32_t (&key)[M], uint32_t nk)
+{
+    if (M == 1) {
+        key[0] = nk;
+        return;
+    }
+    uint32_t nkey[M];
+    nkey[0] = key[1 < M ? 1 : 0] < nk ? key[1 < M ? 1 : 0] : nk;
+#pragma unroll
+    for (int q = 1; q + 1 < M; ++q) nkey[q] = umed3(key[q], nk, key[q + 1]);
+    nkey[M - 1] = key[M - 1] > nk ? key[M - 1] : nk;
+#pragma unroll
+    for (int q = 0; q < M; ++q) key[q] = nkey[q];
+}
+
+// One stage over one window.  r[i] holds slot lo + i: a key from the previous
+// stage, or a gene at stage 0 (completion 0).  Key formats: see KeyFormat;
+// kKeyTwo places a new key after every entry with the same completion by a
+// threshold compare per entry.
 // With GUARD, slot i dispatches only if bit i of `act` is set, and if bit i
 // of `fl` is set it receives the list's first entry, which leaves the list
 // (the flush after the last dispatch); job indices are clamped to n - 1 for
 // the table read.
-template <int M, bool GUARD, bool F, typename PT>
-__device__ __forceinline__ void lane_stage(uint32_t (&r)[kLaneD], uint32_t (&key)[M], const PT* prow,
-                                           uint32_t jb, uint32_t jmask, uint32_t act, uint32_t fl, uint32_t nmax,
-                                           uint32_t sh, int dbase, uint32_t& cor)
+//
+// The indexed unguarded step is M + 5 VALU operations: the slot's job with
+// its index (which also addresses the table: the row's address less that
+// index), start = max(machine free, job ready) -- the larger key has the
+// larger (or equal) time in its high bits --, the new key from the start's
+// time and that word, plus the shifted processing time, and M for the list.
+// `over` collects the carries out of the completion field (kKeyIdxChecked).
+template <int M, bool GUARD, int KEY, typename PT>
+__device__ __forceinline__ void lane_stage(uint32_t (&r)[kLaneD], uint32_t (&key)[M], lds_ptr<PT> prow, uint32_t jb,
+                                           uint32_t jmask, uint32_t act, uint32_t fl, uint32_t nmax, bool& over)
 {
-    uint32_t jj[kLaneD], pj[kLaneD];
+    const uint32_t sh = KEY == kKeyTwo ? jb : jb + kLaneIndexBits;
+    const uint32_t himask = ~((1u << sh) - 1u);
+    uint32_t low[kLaneD], pj[kLaneD];
+    if (GUARD || KEY == kKeyTwo) {
 #pragma unroll
-    for (int i = 0; i < kLaneD; ++i) {
-        const uint32_t j = r[i] & jmask;
-        jj[i] = GUARD ? (j < nmax ? j : nmax) : j;
+        for (int i = 0; i < kLaneD; ++i) {
+            const uint32_t j = r[i] & jmask;
+            low[i] = GUARD ? (j < nmax ? j : nmax) : j;
+        }
+#pragma unroll
+        for (int i = 0; i < kLaneD; ++i) pj[i] = (uint32_t)prow[low[i]];
+    } else {
+#pragma unroll
+        for (int i = 0; i < kLaneD; ++i) low[i] = and_or(r[i], jmask, (uint32_t)(kLaneFirst + i) << jb);
+#pragma unroll
+        for (int i = 0; i < kLaneD; ++i) {
+            const lds_ptr<PT> at = prow - ((uint32_t)(kLaneFirst + i) << jb);   // uniform
+            pj[i] = (uint32_t)at[low[i]];
+        }
     }
-#pragma unroll
-    for (int i = 0; i < kLaneD; ++i) pj[i] = (uint32_t)prow[jj[i]];
 #pragma unroll
     for (int i = 0; i < kLaneD; ++i) {
         if (!GUARD || ((act >> i) & 1u)) {
-            // start = max(machine free, job ready): the larger key has the
-            // larger (or equal) time in its high bits
             const uint32_t o = key[0];
             const uint32_t mx = o > r[i] ? o : r[i];
-            if (F) {
-                const uint32_t c = (mx >> sh) + pj[i];
-                cor |= c;
-                if (M == 1) {
-                    key[0] = (c << sh) | jj[i];
-                } else {
-                    const uint32_t nk = (c << sh) | ((uint32_t)(dbase + i) << jb) | jj[i];
-                    // sorted list key[1 .. M-1] with nk added
-                    uint32_t nkey[M];
-                    nkey[0] = key[1] < nk ? key[1] : nk;
-#pragma unroll
-                    for (int q = 1; q + 1 < M; ++q) nkey[q] = umed3(key[q], nk, key[q + 1]);
-                    nkey[M - 1] = key[M - 1] > nk ? key[M - 1] : nk;
-#pragma unroll
-                    for (int q = 0; q < M; ++q) key[q] = nkey[q];
-                }
+            if (KEY != kKeyTwo) {
+                const uint32_t y = bit_select(himask, mx, GUARD ? low[i] | ((uint32_t)(kLaneFirst + i) << jb) : low[i]);
+                const uint32_t nk = (pj[i] << sh) + y;
+                if (KEY == kKeyIdxChecked) over |= nk < y;
+                lane_insert<M>(key, nk);
             } else {
                 const uint32_t c = (mx >> jb) + pj[i];
-                const uint32_t nk = (c << jb) | jj[i];
+                const uint32_t nk = (c << jb) | low[i];
                 if (M == 1) {
                     key[0] = nk;
                 } else {
@@ -139,15 +175,19 @@ __device__ __forceinline__ void lane_stage(uint32_t (&r)[kLaneD], uint32_t (&key
     }
 }
 
+// Per-lane decode state in LDS.
+typedef __attribute__((address_space(3))) uint32_t* lane_state;
+
 // Stage k (m_k = M) over window [lo, lo + kLaneD): its dispatch slots are
 // [d0, d0 + n), its flush slots [d0 + n, d0 + n + M) unless it is the last
 // stage.  Keys live at st[q * 64] (q < M) between windows (during a flush
-// that spans two windows, the entries not yet written, first at q = 0).  Returns the
-// makespan on the last window of the last stage, else 0.
-template <int M, bool F, typename PT>
-__device__ __forceinline__ uint32_t lane_stage_window(uint32_t (&r)[kLaneD], uint32_t* st, const PT* prow, int lo,
+// that spans two windows, the entries not yet written, first at q = 0), and
+// take their places' indices when a window begins.  Returns the makespan on
+// the last window of the last stage, else 0.
+template <int M, int KEY, typename PT>
+__device__ __forceinline__ uint32_t lane_stage_window(uint32_t (&r)[kLaneD], lane_state st, lds_ptr<PT> prow, int lo,
                                                       int d0, int n, bool last, uint32_t jb, uint32_t jmask,
-                                                      uint32_t sh, uint32_t& cor)
+                                                      bool& over)
 {
     const int d1 = d0 + n, end = last ? d1 : d1 + M;
     uint32_t key[M];
@@ -155,11 +195,15 @@ __device__ __forceinline__ uint32_t lane_stage_window(uint32_t (&r)[kLaneD], uin
 #pragma unroll
         for (int q = 0; q < M; ++q) key[q] = 0u;
     } else {
+        const uint32_t field = ((1u << kLaneIndexBits) - 1u) << jb;
 #pragma unroll
-        for (int q = 0; q < M; ++q) key[q] = st[q * 64];
+        for (int q = 0; q < M; ++q) {
+            key[q] = st[q * 64];
+            if (KEY != kKeyTwo && M > 1) key[q] = (key[q] & ~field) | ((uint32_t)q << jb);
+        }
     }
     if (d0 <= lo && lo + kLaneD <= d1) {
-        lane_stage<M, false, F, PT>(r, key, prow, jb, jmask, 0u, 0u, 0u, sh, lo - d0, cor);
+        lane_stage<M, false, KEY, PT>(r, key, prow, jb, jmask, 0u, 0u, 0u, over);
     } else {
         const int a0 = d0 > lo ? d0 - lo : 0, a1 = (d1 < lo + kLaneD ? d1 : lo + kLaneD) - lo;
         const uint32_t act = (a1 > a0) ? ((0xFFFFFFFFu >> (32 - (a1 - a0))) << a0) : 0u;
@@ -168,9 +212,9 @@ __device__ __forceinline__ uint32_t lane_stage_window(uint32_t (&r)[kLaneD], uin
             const int f0 = (d1 > lo ? d1 : lo) - lo, f1 = (end < lo + kLaneD ? end : lo + kLaneD) - lo;
             fl = (f1 > f0) ? ((0xFFFFFFFFu >> (32 - (f1 - f0))) << f0) : 0u;
         }
-        lane_stage<M, true, F, PT>(r, key, prow, jb, jmask, act, fl, (uint32_t)(n - 1), sh, lo - d0, cor);
+        lane_stage<M, true, KEY, PT>(r, key, prow, jb, jmask, act, fl, (uint32_t)(n - 1), over);
     }
-    if (end <= lo + kLaneD) return last ? (key[M - 1] >> (F ? sh : jb)) : 0u;
+    if (end <= lo + kLaneD) return last ? (key[M - 1] >> (KEY == kKeyTwo ? jb : jb + kLaneIndexBits)) : 0u;
 #pragma unroll
     for (int q = 0; q < M; ++q) st[q * 64] = key[q];
     return 0u;
@@ -210,12 +254,12 @@ struct GenesI32 {
     }
 };
 
-// Makespan of one chromosome per lane with the key format F (see
-// lane_stage).  pT is the LDS table (row stride pts), mach the stage machine
-// counts, st this wave's LDS state (msum keys per lane, lane-interleaved).
-template <int MMAX, bool F, typename PT, typename Src>
-__device__ __forceinline__ uint32_t lane_decode_keys(const Src& src, const PT* pT, int pts, const int* mach, int S, int n, int jb,
-                                     uint32_t sh, uint32_t* st, int lane, uint32_t& cor)
+// Makespan of one chromosome per lane with one key format.  pT is the LDS
+// table (row stride pts), mach the stage machine counts, st this lane's LDS
+// state (msum keys per lane, lane-interleaved).
+template <int MMAX, int KEY, typename PT, typename Src>
+__device__ __forceinline__ uint32_t lane_decode_keys(const Src& src, lds_ptr<PT> pT, int pts, const int* mach, int S,
+                                                     int n, int jb, lane_state st, bool& over)
 {
     const uint32_t ujb = (uint32_t)jb, jmask = (1u << jb) - 1u;
     int off_last = 0;
@@ -237,14 +281,14 @@ __device__ __forceinline__ uint32_t lane_decode_keys(const Src& src, const PT* p
             const int end = off + n + (last ? 0 : M);
             if (off >= lo + kLaneD) break;   // this and later stages start after the window
             if (end > lo) {
-                const PT* prow = pT + (size_t)k * pts;
-                uint32_t* sk = st + (size_t)off * 64 + lane;
+                const lds_ptr<PT> prow = pT + k * pts;
+                const lane_state sk = st + off * 64;
                 uint32_t cm = 0u;
                 switch (M) {
 #define FFS_LANE_CASE(MM)                                                                       \
     case MM:                                                                                    \
         if (MM <= MMAX)                                                                         \
-            cm = lane_stage_window<(MM <= MMAX ? MM : 1), F, PT>(r, sk, prow, lo, off, n, last, ujb, jmask, sh, cor); \
+            cm = lane_stage_window<(MM <= MMAX ? MM : 1), KEY, PT>(r, sk, prow, lo, off, n, last, ujb, jmask, over); \
         break;
                     FFS_LANE_CASE(1) FFS_LANE_CASE(2) FFS_LANE_CASE(3) FFS_LANE_CASE(4)
                     FFS_LANE_CASE(5) FFS_LANE_CASE(6) FFS_LANE_CASE(7) FFS_LANE_CASE(8)
@@ -259,35 +303,36 @@ __device__ __forceinline__ uint32_t lane_decode_keys(const Src& src, const PT* p
     return cmax;
 }
 
-// The two-field decode as a function of its own (the fallback of the
-// three-field one, whose code stays out of the kernel's main path).
+// The two-field decode as a function of its own, so that its code stays out
+// of the kernels' main path.
 template <int MMAX, typename PT, typename Src>
-__device__ __attribute__((noinline)) uint32_t lane_decode_twofield(const Src& src, const PT* pT, int pts,
-                                                                   const int* mach, int S, int n, int jb,
-                                                                   uint32_t* st, int lane)
+__device__ __attribute__((noinline)) uint32_t lane_decode_two(Src src, lds_ptr<PT> pT, int pts, const int* mach, int S,
+                                                              int n, int jb, lane_state st)
 {
-    uint32_t cor = 0u;
-    return lane_decode_keys<MMAX, false, PT>(src, pT, pts, mach, S, n, jb, 0u, st, lane, cor);
+    bool over = false;
+    return lane_decode_keys<MMAX, kKeyTwo, PT>(src, pT, pts, mach, S, n, jb, st, over);
 }
 
-// Makespan of one chromosome per lane.  With fsh > 0 (the instance's
-// completions can fit below 2^(32 - fsh), fsh = 2 jb) the three-field key
-// goes first; if any lane's completions outgrow it, the wave decodes again
-// with the two-field key and those lanes take that result.
+// Makespan of one chromosome per lane with the instance's key format; wst is
+// the wave's LDS state.  If completions outgrow the checked format on any
+// lane, the wave decodes again with the two-field key and those lanes take
+// that result.
 template <int MMAX, typename PT, typename Src>
-__device__ __forceinline__ uint32_t lane_decode(const Src& src, const PT* pT, int pts, const int* mach, int S, int n, int jb,
-                                int fsh, uint32_t* st, int lane)
+__device__ __forceinline__ uint32_t lane_decode(const Src& src, const PT* table, int pts, const InstDesc* I,
+                                                uint32_t* wst, int lane)
 {
-    uint32_t cor = 0u;
-    if (fsh > 0) {
-        const uint32_t cm = lane_decode_keys<MMAX, true, PT>(src, pT, pts, mach, S, n, jb, (uint32_t)fsh, st, lane, cor);
-        const bool redo = (cor >> (32 - fsh)) != 0u;
-        if (__ballot(redo) == 0ull) return cm;
-        // rare: out of line
-        const uint32_t cm2 = lane_decode_twofield<MMAX, PT>(src, pT, pts, mach, S, n, jb, st, lane);
-        return redo ? cm2 : cm;
+    const int *mach = I->mach, S = I->S, n = I->n, jb = I->jb, fmt = I->lkey;
+    const lds_ptr<PT> pT = as_lds(table);
+    const lane_state st = (lane_state)wst + lane;
+    bool over = false;
+    if (fmt == kKeyIdx) return lane_decode_keys<MMAX, kKeyIdx, PT>(src, pT, pts, mach, S, n, jb, st, over);
+    uint32_t cm = 0u;
+    if (fmt == kKeyIdxChecked) {
+        cm = lane_decode_keys<MMAX, kKeyIdxChecked, PT>(src, pT, pts, mach, S, n, jb, st, over);
+        if (__ballot(over) == 0ull) return cm;
     }
-    return lane_decode_keys<MMAX, false, PT>(src, pT, pts, mach, S, n, jb, 0u, st, lane, cor);
+    const uint32_t two = lane_decode_two<MMAX, PT>(src, pT, pts, mach, S, n, jb, st);
+    return fmt == kKeyTwo || over ? two : cm;
 }
 
 // ---- one generation (mode 0) or generation 0 (mode 1), lane mapping --------
@@ -346,7 +391,7 @@ __global__ void __launch_bounds__(512) k_generation_lane(const InstDesc* __restr
         dcount = rhi - rlo + 1;
         if (dcount <= 0) return;
     }
-    const int n = I->n, S = I->S, n_pad = I->n_pad, jb = I->jb;
+    const int n = I->n, S = I->S, n_pad = I->n_pad;
 
     PT* pT = reinterpret_cast<PT*>(ffs_smem);
     stage_pt<PT>(pT, I->pT, S, n_pad);
@@ -465,8 +510,8 @@ __global__ void __launch_bounds__(512) k_generation_lane(const InstDesc* __restr
     unsigned long long wkey = ~0ull;
     if (wcount > 0) {
         const GenesU16 src{L->genes[nxt] + (size_t)slot * n_pad};
-        const uint32_t cm = lane_decode<MMAX, PT>(src, pT, pt_stride<PT>(n_pad), I->mach, S, n, jb, I->fsh,
-                                                  reinterpret_cast<uint32_t*>(wbase), lane);
+        const uint32_t cm = lane_decode<MMAX, PT>(src, pT, pt_stride<PT>(n_pad), I, reinterpret_cast<uint32_t*>(wbase),
+                                                  lane);
         bool keep_old = false;
         if (active) {
             int mk_new = (int)cm;
@@ -531,7 +576,7 @@ template <int MMAX, typename PT>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k_evaluate_lane(const InstDesc* __restrict__ I, const int* __restrict__ perms,
                                                        int count, int* __restrict__ out, Control* ctl)
 {
-    const int n = I->n, S = I->S, n_pad = I->n_pad, jb = I->jb;
+    const int n = I->n, S = I->S, n_pad = I->n_pad;
     PT* pT = reinterpret_cast<PT*>(ffs_smem);
     stage_pt<PT>(pT, I->pT, S, n_pad);
     __syncthreads();
@@ -563,7 +608,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
     }
     wave_sync();
     const GenesI32 src{row, n};
-    const uint32_t cm = lane_decode<MMAX, PT>(src, pT, pt_stride<PT>(n_pad), I->mach, S, n, jb, I->fsh, wbase, lane);
+    const uint32_t cm = lane_decode<MMAX, PT>(src, pT, pt_stride<PT>(n_pad), I, wbase, lane);
     if (active) out[idx] = bad ? -1 : (int)cm;
     if (active && bad) atomicOr(&ctl->err, 1);
 }
