@@ -85,6 +85,7 @@ static DecodeKeys decode_keys(int n, int S, const int* m, const int* p, int jb, 
     };
     DecodeKeys d;
     d.lkey = format(1ll << (32 - jb - kLaneIndexBits));
+    if (d.lkey == kKeyIdx && (jb > kLaneJB || UB >= (1ll << (32 - kLaneJB - kLaneIndexBits)))) d.lkey = kKeyIdxChecked;
     d.pkey = format((1ll << (32 - jb - pipe_index_bits(mmax))) - 1);
     return d;
 }

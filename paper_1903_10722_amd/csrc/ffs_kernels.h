@@ -227,12 +227,12 @@ __device__ __forceinline__ uint32_t from_prev_lane(uint32_t x)
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x13C /* wave_ror:1 */, 0xF, 0xF, true);
 }
 
-// Median of three unsigned words (one VALU operation).
+// Median of three unsigned words (one VALU operation, v_med3_u32).
 __device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c)
 {
-    uint32_t r;
-    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
+    const uint32_t lo = a < b ? a : b, hi = a < b ? b : a;
+    const uint32_t m = hi < c ? hi : c;
+    return lo > m ? lo : m;
 }
 
 // Key formats of the decodes (InstDesc::pkey, lkey), both with the completion

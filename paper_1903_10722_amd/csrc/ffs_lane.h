@@ -63,19 +63,17 @@ __host__ __device__ inline size_t lane_eval_wave_lds(int n, int msum)
 // the index kLaneFirst + i.
 constexpr int kLaneFirst = 8;       // >= machines per stage
 constexpr int kLaneIndexBits = 5;   // kLaneFirst + kLaneD <= 32
+// kKeyIdx is the lane decode's format for up to 512 jobs whose completions fit
+// beside nine job bits (18 bits: 262143); others take the checked one with
+// the instance's own job bits.
+constexpr int kLaneJB = 9;
 
-// (x & m) | o and (m & x) | (~m & y), one VALU operation each.
+// (x & m) | o in one VALU operation (opaque, so that the compiler does not
+// take the and apart from the or where the masked value would serve too).
 __device__ __forceinline__ uint32_t and_or(uint32_t x, uint32_t m, uint32_t o)
 {
     uint32_t r;
     asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(m), "s"(o));
-    return r;
-}
-
-__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t x, uint32_t y)
-{
-    uint32_t r;
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(m), "v"(x), "v"(y));
     return r;
 }
 
@@ -111,7 +109,12 @@ __device__ __forceinline__ void lane_insert(uint32_t (&key)[M], uint32_t nk)
 // larger (or equal) time in its high bits --, the new key from the start's
 // time and that word, plus the shifted processing time, and M for the list.
 // `over` collects the carries out of the completion field (kKeyIdxChecked).
-template <int M, bool GUARD, int KEY, typename PT>
+//
+// With two or three waves per SIMD a wave issues one instruction per four
+// cycles, so scalar instructions cost what vector ones do: JB > 0 (at most
+// 2^JB jobs, the job field that wide) makes the table addresses' index part
+// an immediate offset instead of a scalar subtraction per slot.
+template <int M, bool GUARD, int KEY, int JB, typename PT>
 __device__ __forceinline__ void lane_stage(uint32_t (&r)[kLaneD], uint32_t (&key)[M], lds_ptr<PT> prow, uint32_t jb,
                                            uint32_t jmask, uint32_t act, uint32_t fl, uint32_t nmax, bool& over)
 {
@@ -129,10 +132,17 @@ __device__ __forceinline__ void lane_stage(uint32_t (&r)[kLaneD], uint32_t (&key
     } else {
 #pragma unroll
         for (int i = 0; i < kLaneD; ++i) low[i] = and_or(r[i], jmask, (uint32_t)(kLaneFirst + i) << jb);
+        if (JB > 0) {
+            // prow - index of slot i = (prow - the last slot's) + an offset
+            const lds_ptr<PT> at = prow - ((kLaneFirst + kLaneD - 1) << JB);
 #pragma unroll
-        for (int i = 0; i < kLaneD; ++i) {
-            const lds_ptr<PT> at = prow - ((uint32_t)(kLaneFirst + i) << jb);   // uniform
-            pj[i] = (uint32_t)at[low[i]];
+            for (int i = 0; i < kLaneD; ++i) pj[i] = (uint32_t)(at + low[i])[(kLaneD - 1 - i) << JB];
+        } else {
+#pragma unroll
+            for (int i = 0; i < kLaneD; ++i) {
+                const lds_ptr<PT> at = prow - ((uint32_t)(kLaneFirst + i) << jb);   // uniform
+                pj[i] = (uint32_t)at[low[i]];
+            }
         }
     }
 #pragma unroll
@@ -141,7 +151,7 @@ __device__ __forceinline__ void lane_stage(uint32_t (&r)[kLaneD], uint32_t (&key
             const uint32_t o = key[0];
             const uint32_t mx = o > r[i] ? o : r[i];
             if (KEY != kKeyTwo) {
-                const uint32_t y = bit_select(himask, mx, GUARD ? low[i] | ((uint32_t)(kLaneFirst + i) << jb) : low[i]);
+                const uint32_t y = (mx & himask) | (GUARD ? low[i] | ((uint32_t)(kLaneFirst + i) << jb) : low[i]);
                 const uint32_t nk = (pj[i] << sh) + y;
                 if (KEY == kKeyIdxChecked) over |= nk < y;
                 lane_insert<M>(key, nk);
@@ -184,18 +194,29 @@ typedef __attribute__((address_space(3))) uint32_t* lane_state;
 // that spans two windows, the entries not yet written, first at q = 0), and
 // take their places' indices when a window begins.  Returns the makespan on
 // the last window of the last stage, else 0.
-template <int M, int KEY, typename PT>
+template <int M, int KEY, int JB, typename PT>
 __device__ __forceinline__ uint32_t lane_stage_window(uint32_t (&r)[kLaneD], lane_state st, lds_ptr<PT> prow, int lo,
-                                                      int d0, int n, bool last, uint32_t jb, uint32_t jmask,
-                                                      bool& over)
+                                                      int d0, int n, bool last, bool full, uint32_t jb,
+                                                      uint32_t jmask, bool& over)
 {
-    const int d1 = d0 + n, end = last ? d1 : d1 + M;
+    const uint32_t field = ((1u << kLaneIndexBits) - 1u) << jb;
     uint32_t key[M];
+    if (full) {   // every stage dispatches in every slot
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            key[q] = st[q * 64];
+            if (KEY != kKeyTwo && M > 1) key[q] = (key[q] & ~field) | ((uint32_t)q << jb);
+        }
+        lane_stage<M, false, KEY, JB, PT>(r, key, prow, jb, jmask, 0u, 0u, 0u, over);
+#pragma unroll
+        for (int q = 0; q < M; ++q) st[q * 64] = key[q];
+        return 0u;
+    }
+    const int d1 = d0 + n, end = last ? d1 : d1 + M;
     if (d0 >= lo) {
 #pragma unroll
         for (int q = 0; q < M; ++q) key[q] = 0u;
     } else {
-        const uint32_t field = ((1u << kLaneIndexBits) - 1u) << jb;
 #pragma unroll
         for (int q = 0; q < M; ++q) {
             key[q] = st[q * 64];
@@ -203,7 +224,7 @@ __device__ __forceinline__ uint32_t lane_stage_window(uint32_t (&r)[kLaneD], lan
         }
     }
     if (d0 <= lo && lo + kLaneD <= d1) {
-        lane_stage<M, false, KEY, PT>(r, key, prow, jb, jmask, 0u, 0u, 0u, over);
+        lane_stage<M, false, KEY, JB, PT>(r, key, prow, jb, jmask, 0u, 0u, 0u, over);
     } else {
         const int a0 = d0 > lo ? d0 - lo : 0, a1 = (d1 < lo + kLaneD ? d1 : lo + kLaneD) - lo;
         const uint32_t act = (a1 > a0) ? ((0xFFFFFFFFu >> (32 - (a1 - a0))) << a0) : 0u;
@@ -212,7 +233,7 @@ __device__ __forceinline__ uint32_t lane_stage_window(uint32_t (&r)[kLaneD], lan
             const int f0 = (d1 > lo ? d1 : lo) - lo, f1 = (end < lo + kLaneD ? end : lo + kLaneD) - lo;
             fl = (f1 > f0) ? ((0xFFFFFFFFu >> (32 - (f1 - f0))) << f0) : 0u;
         }
-        lane_stage<M, true, KEY, PT>(r, key, prow, jb, jmask, act, fl, (uint32_t)(n - 1), over);
+        lane_stage<M, true, KEY, JB, PT>(r, key, prow, jb, jmask, act, fl, (uint32_t)(n - 1), over);
     }
     if (end <= lo + kLaneD) return last ? (key[M - 1] >> (KEY == kKeyTwo ? jb : jb + kLaneIndexBits)) : 0u;
 #pragma unroll
@@ -257,11 +278,11 @@ struct GenesI32 {
 // Makespan of one chromosome per lane with one key format.  pT is the LDS
 // table (row stride pts), mach the stage machine counts, st this lane's LDS
 // state (msum keys per lane, lane-interleaved).
-template <int MMAX, int KEY, typename PT, typename Src>
+template <int MMAX, int KEY, int JB, typename PT, typename Src>
 __device__ __forceinline__ uint32_t lane_decode_keys(const Src& src, lds_ptr<PT> pT, int pts, const int* mach, int S,
                                                      int n, int jb, lane_state st, bool& over)
 {
-    const uint32_t ujb = (uint32_t)jb, jmask = (1u << jb) - 1u;
+    const uint32_t ujb = (uint32_t)(JB > 0 ? JB : jb), jmask = (1u << ujb) - 1u;
     int off_last = 0;
     for (int k = 0; k + 1 < S; ++k) off_last += mach[k];
     const int nwin = (off_last + n + kLaneD - 1) / kLaneD;
@@ -274,13 +295,13 @@ __device__ __forceinline__ uint32_t lane_decode_keys(const Src& src, lds_ptr<PT>
 #pragma unroll
         for (int i = 0; i < kLaneD; ++i) r[i] = gnext[i];
         if (lo + kLaneD < n) src.load(lo + kLaneD, gnext);
+        const bool full = lo > off_last && lo + kLaneD <= n;
         int off = 0;
         for (int k = 0; k < S; ++k) {
             const int M = mach[k];
             const bool last = (k == S - 1);
-            const int end = off + n + (last ? 0 : M);
-            if (off >= lo + kLaneD) break;   // this and later stages start after the window
-            if (end > lo) {
+            if (!full && off >= lo + kLaneD) break;   // this and later stages start after the window
+            if (full || off + n + (last ? 0 : M) > lo) {
                 const lds_ptr<PT> prow = pT + k * pts;
                 const lane_state sk = st + off * 64;
                 uint32_t cm = 0u;
@@ -288,7 +309,8 @@ __device__ __forceinline__ uint32_t lane_decode_keys(const Src& src, lds_ptr<PT>
 #define FFS_LANE_CASE(MM)                                                                       \
     case MM:                                                                                    \
         if (MM <= MMAX)                                                                         \
-            cm = lane_stage_window<(MM <= MMAX ? MM : 1), KEY, PT>(r, sk, prow, lo, off, n, last, ujb, jmask, over); \
+            cm = lane_stage_window<(MM <= MMAX ? MM : 1), KEY, JB, PT>(r, sk, prow, lo, off, n, last, full, ujb,     \
+                                                                       jmask, over);                            \
         break;
                     FFS_LANE_CASE(1) FFS_LANE_CASE(2) FFS_LANE_CASE(3) FFS_LANE_CASE(4)
                     FFS_LANE_CASE(5) FFS_LANE_CASE(6) FFS_LANE_CASE(7) FFS_LANE_CASE(8)
@@ -310,7 +332,7 @@ __device__ __attribute__((noinline)) uint32_t lane_decode_two(Src src, lds_ptr<P
                                                               int n, int jb, lane_state st)
 {
     bool over = false;
-    return lane_decode_keys<MMAX, kKeyTwo, PT>(src, pT, pts, mach, S, n, jb, st, over);
+    return lane_decode_keys<MMAX, kKeyTwo, 0, PT>(src, pT, pts, mach, S, n, jb, st, over);
 }
 
 // Makespan of one chromosome per lane with the instance's key format; wst is
@@ -325,10 +347,10 @@ __device__ __forceinline__ uint32_t lane_decode(const Src& src, const PT* table,
     const lds_ptr<PT> pT = as_lds(table);
     const lane_state st = (lane_state)wst + lane;
     bool over = false;
-    if (fmt == kKeyIdx) return lane_decode_keys<MMAX, kKeyIdx, PT>(src, pT, pts, mach, S, n, jb, st, over);
+    if (fmt == kKeyIdx) return lane_decode_keys<MMAX, kKeyIdx, kLaneJB, PT>(src, pT, pts, mach, S, n, jb, st, over);
     uint32_t cm = 0u;
     if (fmt == kKeyIdxChecked) {
-        cm = lane_decode_keys<MMAX, kKeyIdxChecked, PT>(src, pT, pts, mach, S, n, jb, st, over);
+        cm = lane_decode_keys<MMAX, kKeyIdxChecked, 0, PT>(src, pT, pts, mach, S, n, jb, st, over);
         if (__ballot(over) == 0ull) return cm;
     }
     const uint32_t two = lane_decode_two<MMAX, PT>(src, pT, pts, mach, S, n, jb, st);
@@ -460,6 +482,11 @@ __global__ void __launch_bounds__(512) k_generation_lane(const InstDesc* __restr
                 row_l2g(L->genes[nxt] + (size_t)slot_of(sbase + c) * n_pad, A, n_pad, lane, kWave);
                 wave_sync();
             };
+            // Building a child is a chain of LDS round trips, the decode is bound
+            // by vector issue: the waves that build go first on their SIMD, so
+            // that their round trips pass under the others' decodes (a large
+            // generation 660 -> 586 us; the decode first instead: no gain).
+            __builtin_amdgcn_s_setprio(3);
             auto build = [&](auto vc) {
                 constexpr int VC = decltype(vc)::value;
                 u32x4 ra[VC], rb[VC];
@@ -510,6 +537,7 @@ __global__ void __launch_bounds__(512) k_generation_lane(const InstDesc* __restr
     unsigned long long wkey = ~0ull;
     if (wcount > 0) {
         const GenesU16 src{L->genes[nxt] + (size_t)slot * n_pad};
+        __builtin_amdgcn_s_setprio(0);
         const uint32_t cm = lane_decode<MMAX, PT>(src, pT, pt_stride<PT>(n_pad), I, reinterpret_cast<uint32_t*>(wbase),
                                                   lane);
         bool keep_old = false;

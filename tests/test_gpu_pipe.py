@@ -88,3 +88,31 @@ def test_pipe_decode_rejects_non_permutations(n):
     ok = np.setdiff1d(np.arange(90), bad)
     assert np.array_equal(got[ok], oracle.decode_many(m, p, perms[ok]))
     ctx.close()
+
+
+@pytest.mark.parametrize("n,S,m,p_hi", [(511, 3, [2, 1, 3], 99), (512, 3, [2, 1, 3], 99), (513, 3, [2, 1, 3], 99),
+                                        (512, 2, [8, 7], 2), (20, 20, [5] * 20, 65535), (600, 4, [4] * 4, 999)])
+def test_lane_decode_formats(n, S, m, p_hi):
+    """One lane per chromosome: the nine-bit job field and beyond it."""
+    ensure_built()
+    m, p = inputs.make_instance(n, S, 1, 1, p_hi=p_hi, seed=n + S, machines=m)
+    say(f"[lane formats] n={n} S={S} p<={p_hi}")
+    _check(m, p, inputs.random_perms(131, n, seed=n), mapping=1)
+
+
+@pytest.mark.parametrize("n,long,cap", [(1000, 200, 131071), (512, 800, 262143), (1000, 500, 131071)])
+def test_lane_decode_outgrows_the_index(n, long, cap):
+    """Three job types, each long on its own single-machine stage: rows sorted
+    by type outgrow the completion field beside the index, random rows do not
+    (last case: the lower bound itself is beyond it)."""
+    ensure_built()
+    S = 3
+    m = np.ones(S, dtype=np.int32)
+    p = np.ones((n, S), dtype=np.int32)
+    p[np.arange(n), np.arange(n) % S] = long
+    rng = np.random.default_rng(3)
+    by_type = np.argsort(np.arange(n) % S, kind="stable")
+    perms = np.asarray([by_type if r % 7 == 0 else rng.permutation(n) for r in range(150)], dtype=np.int32)
+    say(f"[lane formats] outgrows n={n} long={long}")
+    want = _check(m, p, perms, mapping=1)
+    assert (want[::7] > cap).all()
