@@ -130,11 +130,24 @@ const int kMmaxList[] = {2, 3, 4, 5, 6, 8, 16};
 // of k_generation is chosen when the mapping is automatic.
 constexpr long long kLaneAutoMin = 131072;
 constexpr long long kChainAutoMin = 131072;   // individuals per context for two launch chains
-// ffs_evaluate takes the lane mapping from this many rows of at least this
-// many stages (a million random rows: 1.45x and 1.65x faster at 10 and 20
-// stages, 2.3x slower at 5, where the per-stage groups fill the wave too)
-constexpr int kLaneEvalAutoMin = 65536;
-constexpr int kLaneEvalMinStages = 8;
+// The automatic mapping of ffs_evaluate.  Per row the pipelined decode issues
+// P = (n + sum (m + 1)) (10.5 + mmax) / G vector operations and keeps the
+// chip busy whatever the shape; the lane decode issues L = n (sum (m + 5) + 4)
+// / 64, about half of it, but is held by its LDS (keys and bit sets) to
+// `resident` waves per CU and reaches about a twentieth of the issue rate per
+// wave.  From 1.5 waves of rows per SIMD on (98304 rows) it takes over where
+// P resident > 20 L, from 524288 rows on, where its last round no longer
+// counts, where P resident > 17 L.  Microseconds per call, pipelined / lane,
+// at 98304, 262144 and 1048576 rows: 100 x 5 91 / 83, 151 / 105, 430 / 256;
+// 300 x 4 114 / 114, 224 / 163, 721 / 462; 500 x 10 320 / 412, 754 / 751,
+// 2780 / 2394; 500 x 20 650 / 579, 1539 / 1655, 6029 / 5939; 100 x 20
+// 289 / 199, 675 / 506, 2392 / 1572.
+bool lane_eval_auto(int count, int n, int S, int msum, int mmax, int G, int resident)
+{
+    if (count < 98304) return false;
+    const double P = (double)(n + msum + S) * (10.5 + mmax) / G, L = (double)n * (msum + 5 * S + 4) / 64.0;
+    return P * resident > (count >= 524288 ? 17.0 : 20.0) * L;
+}
 
 int round_mmax(int m)
 {
@@ -939,14 +952,16 @@ int launch_eval(ffs_ctx* c, int inst, const int32_t* perms, int count, int32_t* 
     const InstDesc* di = reinterpret_cast<const InstDesc*>(c->ws + c->off_insts) + inst;
     Control* ctl = reinterpret_cast<Control*>(c->ws + c->off_ctl);
     void* kl = I.lane_ok ? pick_eval_lane(c->mm, c->ptb) : nullptr;
-    const bool lane = kl && (c->mapping == 1 || (c->mapping < 0 && count >= kLaneEvalAutoMin &&
-                                                 I.S >= kLaneEvalMinStages));
-    const int per_block = c->wpb * (lane ? kWave : I.G);
+    const size_t table = align16((size_t)I.S * ((size_t)I.n_pad * c->ptb + 4));
+    int resident = 0;
+    const int lw = kl ? lane_eval_waves(table, I.lane_wlds_eval, (size_t)c->max_lds, resident) : 0;
+    const bool lane = lw > 0 && (c->mapping == 1 || (c->mapping < 0 && lane_eval_auto(count, I.n, I.S, I.msum, c->mm, I.G, resident)));
+    const int wpb = lane ? lw : c->wpb;
+    const int per_block = wpb * (lane ? kWave : I.G);
     const int blocks = (count + per_block - 1) / per_block;
-    const size_t lds = align16((size_t)I.S * ((size_t)I.n_pad * c->ptb + 4)) +
-                       (size_t)c->wpb * (lane ? I.lane_wlds_eval : (size_t)I.G * eval_stride(I.n_pad) * 2);
+    const size_t lds = table + (size_t)wpb * (lane ? I.lane_wlds_eval : (size_t)I.G * eval_stride(I.n_pad) * 2);
     void* args[] = {(void*)&di, (void*)&perms, (void*)&count, (void*)&out, (void*)&ctl};
-    HIP_TRY(c, hipLaunchKernel(lane ? kl : c->keval, dim3(blocks), dim3(64 * c->wpb), args, lds, c->stream));
+    HIP_TRY(c, hipLaunchKernel(lane ? kl : c->keval, dim3(blocks), dim3(64 * wpb), args, lds, c->stream));
     return FFS_OK;
 }
 
@@ -1200,7 +1215,7 @@ int ffs_create_instance(ffs_ctx* c, int32_t n, int32_t S, const int32_t* machine
     // lane mapping: the operators' rows of one child per wave, then the
     // decode's msum keys per lane, in LDS
     I.lane_wlds = lane_gen_wave_lds(I.n_pad, I.msum);
-    I.lane_wlds_eval = lane_eval_wave_lds(n, I.msum);
+    I.lane_wlds_eval = lane_eval_wave_lds(jb, I.msum);
     I.lane_ok = I.msum <= kLaneMaxMsum && I.mmax <= 8;
     for (int x = 0; x < n_islands; ++x) {
         if (!islands[x].sweep) continue;
@@ -2088,18 +2103,20 @@ int ffs_evaluate_noalloc(void* hip_stream, int32_t n, int32_t S, const int32_t* 
     d.G = std::min(kWave / S, std::max(1, 32768 / (2 * group_stride(n, n_pad, S))));
     d.msum = msum;
     for (int k = 0; k < S; ++k) d.mach[k] = machines[k];
-    d.lane_wlds_eval = (int)lane_eval_wave_lds(n, msum);
-    // the automatic choice of ffs_evaluate at four waves per workgroup
-    constexpr int wpb = 4;
-    void* kl = (msum <= kLaneMaxMsum && mmax <= 8) ? pick_eval_lane(mm, ptb) : nullptr;
-    const bool lane = kl && count >= kLaneEvalAutoMin && S >= kLaneEvalMinStages;
-    void* kern = lane ? kl : pick_eval(mm, ptb);
-    if (!kern) return FFS_EUNSUPPORTED;
-    const size_t lds = align16((size_t)S * ((size_t)n_pad * ptb + 4)) +
-                       (size_t)wpb * (lane ? (size_t)d.lane_wlds_eval : (size_t)d.G * eval_stride(n_pad) * 2);
+    d.lane_wlds_eval = (int)lane_eval_wave_lds(jb, msum);
+    // the automatic choice of ffs_evaluate, per-stage at four waves per workgroup
     int max_lds = 0;
     if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
         return FFS_EDEVICE;
+    const size_t table = align16((size_t)S * ((size_t)n_pad * ptb + 4));
+    void* kl = (msum <= kLaneMaxMsum && mmax <= 8) ? pick_eval_lane(mm, ptb) : nullptr;
+    int resident = 0;
+    const int lw = kl ? lane_eval_waves(table, (size_t)d.lane_wlds_eval, (size_t)max_lds, resident) : 0;
+    const bool lane = lw > 0 && lane_eval_auto(count, n, S, msum, mm, d.G, resident);
+    const int wpb = lane ? lw : 4;
+    void* kern = lane ? kl : pick_eval(mm, ptb);
+    if (!kern) return FFS_EUNSUPPORTED;
+    const size_t lds = table + (size_t)wpb * (lane ? (size_t)d.lane_wlds_eval : (size_t)d.G * eval_stride(n_pad) * 2);
     if (lds > (size_t)max_lds) return FFS_EUNSUPPORTED;
     if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return FFS_EDEVICE;

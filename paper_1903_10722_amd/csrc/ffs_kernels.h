@@ -1404,22 +1404,34 @@ __global__ void __launch_bounds__(512) k_evaluate(const InstDesc* __restrict__ I
     wave_sync();
     bool bad = false;
     if (active) {
-        constexpr int U = 8;
-        const auto* row = as_global(perms + idx * (long long)n);
-        for (int t0 = k; t0 < n; t0 += U * S) {
-            int x[U];
+        // four values per read, sixteen in flight per lane
+        constexpr int U = 4;
+        typedef int row_vec __attribute__((ext_vector_type(4), aligned(4)));
+        const int* row = perms + idx * (long long)n;
+        const auto* r4 = as_global(reinterpret_cast<const row_vec*>(row));
+        typedef uint16_t gene_vec __attribute__((ext_vector_type(4)));
+        gene_vec* a4 = reinterpret_cast<gene_vec*>(A);
+        auto take = [&](int x) {
+            const bool ob = (unsigned)x >= (unsigned)n;
+            bad |= ob;
+            if (!ob) atomicOr(&W[x >> 5], 1u << (x & 31));
+            return ob ? (uint16_t)0 : (uint16_t)x;
+        };
+        const int n4 = n >> 2;
+        for (int q0 = k; q0 < n4; q0 += U * S) {
+            row_vec x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) x[u] = row[t0 + u * S < n ? t0 + u * S : n - 1];
+            for (int u = 0; u < U; ++u) x[u] = r4[q0 + u * S < n4 ? q0 + u * S : n4 - 1];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (t0 + u * S < n) {
-                    const bool ob = (unsigned)x[u] >= (unsigned)n;
-                    bad |= ob;
-                    A[t0 + u * S] = ob ? (uint16_t)0 : (uint16_t)x[u];
-                    if (!ob) atomicOr(&W[x[u] >> 5], 1u << (x[u] & 31));
+            for (int u = 0; u < U; ++u)
+                if (q0 + u * S < n4) {
+                    gene_vec g;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) g[e] = take(x[u][e]);
+                    a4[q0 + u * S] = g;
                 }
-            }
         }
+        for (int t = 4 * n4 + k; t < n; t += S) A[t] = take(as_global(row)[t]);
     }
     wave_sync();
     if (active)
