@@ -21,6 +21,7 @@
 #include "ffs_kernels.h"
 #include "ffs_lane.h"
 #include "ffs_pick.h"
+#include "ffs_pinned.h"
 
 using namespace flowshop;
 
@@ -89,6 +90,45 @@ static DecodeKeys decode_keys(int n, int S, const int* m, const int* p, int jb, 
     d.pkey = format((1ll << (32 - jb - pipe_index_bits(mmax))) - 1);
     return d;
 }
+
+namespace flowshop {
+namespace {
+std::mutex g_pin_mu;
+std::vector<char*> g_pin_free;
+}  // namespace
+
+char* pin_take()
+{
+    {
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        if (!g_pin_free.empty()) {
+            char* p = g_pin_free.back();
+            g_pin_free.pop_back();
+            memset(p, 0, kPinWords);
+            return p;
+        }
+    }
+    void* p = nullptr;
+    if (hipHostMalloc(&p, kPinWords + kPinStage, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) !=
+        hipSuccess)
+        return nullptr;
+    memset(p, 0, kPinWords);
+    return static_cast<char*>(p);
+}
+
+void pin_give(char* p)
+{
+    if (!p) return;
+    {
+        std::lock_guard<std::mutex> lk(g_pin_mu);
+        if (g_pin_free.size() < kPinKept) {
+            g_pin_free.push_back(p);
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+}  // namespace flowshop
 
 namespace {
 
@@ -184,7 +224,9 @@ struct ffs_ctx {
     bool bound = false;
     char* ws = nullptr;
     size_t ws_bytes = 0;
+    char* pin = nullptr;         // pinned host block: the error word, then staging for small results
     int gen = 0;
+    int flushed = -1;            // generation that flush_best folded last (see there)
     std::string err;
     // layout
     size_t off_ctl = 0, off_insts = 0, off_isls = 0, off_work = 0, off_pairs = 0, off_counts = 0, total = 0;
@@ -546,19 +588,18 @@ int check_bound(ffs_ctx* c)
     return FFS_OK;
 }
 
-int read_ctl(ffs_ctx* c, Control* out)
+int wait_stream(ffs_ctx* c)
 {
-    HIP_TRY(c, hipMemcpyAsync(out, c->ws + c->off_ctl, sizeof(Control), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return FFS_OK;
 }
 
-int check_faults(ffs_ctx* c)
+// A device piece of at most kPinStage bytes into host memory (waits).
+int read_small(ffs_ctx* c, size_t off, size_t bytes, void* host)
 {
-    Control ctl;
-    int rc = read_ctl(c, &ctl);
-    if (rc) return rc;
-    if (ctl.err & 2) return fail(c, FFS_EDEVICE, "decode kernel exceeded its step bound");
+    HIP_TRY(c, hipMemcpyAsync(c->pin + kPinWords, c->ws + off, bytes, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    memcpy(host, c->pin + kPinWords, bytes);
     return FFS_OK;
 }
 
@@ -665,20 +706,23 @@ int launch_generation(ffs_ctx* c, int mode, int chain = -1)
 
 // Folds the completed generation into the best-ever records if the next
 // generation launch has not done so yet.
-int flush_best(ffs_ctx* c)
+int flush_best(ffs_ctx* c, bool capturing = false)
 {
     const InstDesc* di = reinterpret_cast<const InstDesc*>(c->ws + c->off_insts);
     const IslandDesc* dl = reinterpret_cast<const IslandDesc*>(c->ws + c->off_isls);
     Control* ctl = reinterpret_cast<Control*>(c->ws + c->off_ctl);
+    // nothing launched since the last flush: the records are up to date
+    if (!capturing && c->flushed == c->gen) return FFS_OK;
     hipLaunchKernelGGL(k_best_flush, dim3(1), dim3(256), 0, c->stream, di, dl, ctl, (int)c->inst.size(), c->ngroup);
     HIP_TRY(c, hipGetLastError());
+    if (!capturing) c->flushed = c->gen;
     return FFS_OK;
 }
 
-int launch_migration(ffs_ctx* c, int force_inst)
+int launch_migration(ffs_ctx* c, int force_inst, bool capturing = false)
 {
     // migration rewrites rows of the completed generation: record its best first
-    int frc = flush_best(c);
+    int frc = flush_best(c, capturing);
     if (frc) return frc;
     const InstDesc* di = reinterpret_cast<const InstDesc*>(c->ws + c->off_insts);
     const IslandDesc* dl = reinterpret_cast<const IslandDesc*>(c->ws + c->off_isls);
@@ -965,19 +1009,15 @@ int launch_eval(ffs_ctx* c, int inst, const int32_t* perms, int count, int32_t* 
     return FFS_OK;
 }
 
-// Waits for the decodes and turns the control block's flags into a status
-// (clearing the invalid-row flag for the next call).
+// Waits for the decodes and turns the error word, which they write in host
+// memory, into a status (cleared for the next call).
 int eval_status(ffs_ctx* c, int inst)
 {
-    Control h;
-    int rc = read_ctl(c, &h);
+    int rc = wait_stream(c);
     if (rc) return rc;
-    if (h.err & 2) return fail(c, FFS_EDEVICE, "decode kernel exceeded its step bound");
-    if (h.err & 1) {
-        h.err &= ~1;
-        HIP_TRY(c, hipMemcpyAsync(c->ws + c->off_ctl + offsetof(Control, err), &h.err, sizeof(int),
-                                  hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
+    volatile int* err = reinterpret_cast<volatile int*>(c->pin);
+    if (*err) {
+        *err = 0;
         return fail(c, FFS_EINVAL, "some rows are not permutations of 0..%d (makespan -1)", c->inst[inst].n - 1);
     }
     return FFS_OK;
@@ -1099,6 +1139,11 @@ int ffs_ctx_create(void* hip_stream, ffs_ctx** out)
         delete c;
         return FFS_EDEVICE;
     }
+    c->pin = pin_take();
+    if (!c->pin) {
+        delete c;
+        return FFS_ENOMEM;
+    }
     c->max_lds -= 256;   // the generation kernels' static LDS (generation number, wave minima)
     *out = c;
     return FFS_OK;
@@ -1107,7 +1152,7 @@ int ffs_ctx_create(void* hip_stream, ffs_ctx** out)
 void ffs_ctx_destroy(ffs_ctx* c)
 {
     if (!c) return;
-    if (c->bound) (void)hipStreamSynchronize(c->stream);
+    if (c->bound) (void)hipStreamSynchronize(c->stream);   // (also: no kernel writes the pinned block any more)
     drop_graph(c);
     for (auto e : c->ev_pool) (void)hipEventDestroy(e);
     for (auto e : c->fork_ev) (void)hipEventDestroy(e);
@@ -1116,6 +1161,7 @@ void ffs_ctx_destroy(ffs_ctx* c)
         (void)hipEventDestroy(pr.first);
         (void)hipEventDestroy(pr.second);
     }
+    pin_give(c->pin);
     delete c;
 }
 
@@ -1480,6 +1526,11 @@ int ffs_bind_workspace(ffs_ctx* c, void* dptr, size_t bytes)
     ctl.counts = reinterpret_cast<int*>(c->ws + c->off_counts);
     for (int gi = 0; gi < kMaxGroups; ++gi) ctl.best_gen[gi] = -1;
     {
+        void* dev = nullptr;
+        HIP_TRY(c, hipHostGetDevicePointer(&dev, c->pin, 0));
+        ctl.err = reinterpret_cast<int*>(dev);
+    }
+    {
         std::vector<int> zeros(c->max_work + 16, 0);
         HIP_TRY(c, hipMemcpy(c->ws + c->off_counts, zeros.data(), zeros.size() * sizeof(int), hipMemcpyHostToDevice));
     }
@@ -1573,11 +1624,11 @@ int ffs_bind_workspace(ffs_ctx* c, void* dptr, size_t bytes)
     }
     c->bound = true;
     c->gen = 0;
+    c->flushed = -1;
     int rc = launch_generation(c, 1);
     if (rc) return rc;
     HIP_TRY(c, hipGetLastError());
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    return check_faults(c);
+    return wait_stream(c);
 }
 
 int ffs_evaluate(ffs_ctx* c, int32_t inst, const int32_t* perms, int32_t count, int32_t* out)
@@ -1665,7 +1716,7 @@ int ffs_evolve(ffs_ctx* c, int32_t generations)
                         if (crc == FFS_OK && c->surr >= 0) crc = surrogate_train(c);
                     }
                 }
-                if (crc == FFS_OK && I > 0) crc = launch_migration(c, -1);
+                if (crc == FFS_OK && I > 0) crc = launch_migration(c, -1, true);
                 hipError_t ec = hipStreamEndCapture(c->stream, &graph);
                 if (crc) {
                     if (graph) (void)hipGraphDestroy(graph);
@@ -1724,13 +1775,15 @@ int ffs_best(ffs_ctx* c, int32_t inst, int32_t* out_mk, int32_t* out_gen, int32_
     const auto& I = c->inst[inst];
     rc = flush_best(c);
     if (rc) return rc;
-    // the chains' records: the better by (makespan, generation, island, slot)
-    int rec[4 * kChains];
-    std::vector<uint16_t> perm((size_t)kChains * I.n_pad);
-    HIP_TRY(c, hipMemcpyAsync(rec, c->ws + I.off_best_rec, sizeof rec, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(perm.data(), c->ws + I.off_best_perm, perm.size() * 2, hipMemcpyDeviceToHost, c->stream));
-    rc = check_faults(c);
+    // the chains' records: the better by (makespan, generation, island, slot);
+    // permutations and records are adjacent in the workspace
+    static_assert((size_t)kChains * 4096 * 2 + 256 + 4 * kChains * sizeof(int) <= kPinStage, "records fit the staging");
+    const size_t span = I.off_best_rec - I.off_best_perm + 4 * kChains * sizeof(int);
+    HIP_TRY(c, hipMemcpyAsync(c->pin + kPinWords, c->ws + I.off_best_perm, span, hipMemcpyDeviceToHost, c->stream));
+    rc = wait_stream(c);
     if (rc) return rc;
+    const uint16_t* perm = reinterpret_cast<const uint16_t*>(c->pin + kPinWords);
+    const int* rec = reinterpret_cast<const int*>(c->pin + kPinWords + (I.off_best_rec - I.off_best_perm));
     int b = 0;
     for (int ch = 1; ch < kChains; ++ch) {
         const int* x = rec + 4 * ch;
@@ -1758,12 +1811,15 @@ int ffs_get_population(ffs_ctx* c, int32_t inst, int32_t island, int32_t* genes,
         g.resize((size_t)L.size * I.n_pad);
         HIP_TRY(c, hipMemcpyAsync(g.data(), c->ws + L.off_genes[par], g.size() * 2, hipMemcpyDeviceToHost, c->stream));
     }
-    if (mk) HIP_TRY(c, hipMemcpyAsync(mk, c->ws + L.off_mk[par], (size_t)L.size * 4, hipMemcpyDeviceToHost, c->stream));
-    rc = check_faults(c);
+    static_assert((size_t)16384 * 4 <= kPinStage, "an island's makespans fit the staging");
+    rc = mk ? read_small(c, L.off_mk[par], (size_t)L.size * 4, mk) : wait_stream(c);
     if (rc) return rc;
     if (genes)
-        for (int s = 0; s < L.size; ++s)
-            for (int j = 0; j < I.n; ++j) genes[(size_t)s * I.n + j] = g[(size_t)s * I.n_pad + j];
+        for (int s = 0; s < L.size; ++s) {
+            const uint16_t* row = g.data() + (size_t)s * I.n_pad;
+            int32_t* out = genes + (size_t)s * I.n;
+            for (int j = 0; j < I.n; ++j) out[j] = row[j];
+        }
     return FFS_OK;
 }
 
@@ -1780,8 +1836,8 @@ int ffs_migration_counters(ffs_ctx* c, int32_t inst, int64_t* migrations, int64_
     if (rc) return rc;
     if (inst < 0 || inst >= (int)c->inst.size()) return fail(c, FFS_EINVAL, "no instance %d", inst);
     long long v[2];
-    HIP_TRY(c, hipMemcpyAsync(v, c->ws + c->inst[inst].off_counters, sizeof v, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    rc = read_small(c, c->inst[inst].off_counters, sizeof v, v);
+    if (rc) return rc;
     if (migrations) *migrations = v[0];
     if (migrants) *migrants = v[1];
     return FFS_OK;
@@ -1978,7 +2034,7 @@ int ffs_checkpoint_save(ffs_ctx* c, void* host, size_t bytes)
         HIP_TRY(c, hipMemcpyAsync(out + pos, c->ws + pc.off, pc.bytes, hipMemcpyDeviceToHost, c->stream));
         pos += pc.bytes;
     }
-    rc = check_faults(c);   // waits for the copies
+    rc = wait_stream(c);   // for the copies
     if (rc) return rc;
     pos = sizeof h;
     for (const auto& pc : pieces) {
@@ -2008,6 +2064,7 @@ int ffs_checkpoint_load(ffs_ctx* c, const void* host, size_t bytes)
     if (h.generation < 0) return fail(c, FFS_EINVAL, "bad generation in checkpoint");
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->gen = h.generation;
+    c->flushed = -1;
     const unsigned char* in = static_cast<const unsigned char*>(host);
     size_t pos = sizeof h;
     for (const auto& pc : ckpt_pieces(c)) {
@@ -2029,7 +2086,6 @@ int ffs_checkpoint_load(ffs_ctx* c, const void* host, size_t bytes)
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     ctl.base = c->gen;
     for (int gi = 0; gi < kMaxGroups; ++gi) ctl.best_gen[gi] = c->gen;
-    ctl.err = 0;
     HIP_TRY(c, hipMemcpyAsync(c->ws + c->off_ctl, &ctl, sizeof ctl, hipMemcpyHostToDevice, c->stream));
     const unsigned long long gk[2] = {~0ull, ~0ull};
     for (const auto& I : c->inst)
@@ -2074,7 +2130,11 @@ int ffs_evaluate_noalloc(void* hip_stream, int32_t n, int32_t S, const int32_t* 
     if (count == 0) return FFS_OK;
     const int n_pad = (n + 31) & ~31, ptb = maxP <= 255 ? 1 : 2;
     // scratch layout: control block, descriptor, processing times, table
-    const size_t o_ctl = 0, o_desc = al256(sizeof(Control)), o_p = o_desc + al256(sizeof(InstDesc));
+    struct Head {
+        Control ctl;
+        InstDesc d;
+    };
+    const size_t o_err = 0, o_head = 256, o_p = o_head + al256(sizeof(Head));
     const size_t o_pt = o_p + al256((size_t)n * S * 4);
     if (o_pt + (size_t)S * n_pad * ptb > kScratchBytes) return FFS_EUNSUPPORTED;
     int dev = 0;
@@ -2090,8 +2150,10 @@ int ffs_evaluate_noalloc(void* hip_stream, int32_t n, int32_t S, const int32_t* 
         base = static_cast<char*>(g_scratch_dev[dev]);
     }
     const int mm = round_mmax(mmax);
-    InstDesc d;
-    memset(&d, 0, sizeof d);
+    Head head;
+    memset(&head, 0, sizeof head);
+    head.ctl.err = reinterpret_cast<int*>(base + o_err);
+    InstDesc& d = head.d;
     d.pT = base + o_pt;
     d.n = n;
     d.S = S;
@@ -2122,28 +2184,25 @@ int ffs_evaluate_noalloc(void* hip_stream, int32_t n, int32_t S, const int32_t* 
         return FFS_EDEVICE;
     // the previous call's contents stay in scratch: descriptor, times and
     // table are rewritten, the error word cleared by a kernel
-    if (hipMemcpyAsync(base + o_desc, &d, sizeof d, hipMemcpyHostToDevice, stream) != hipSuccess) return FFS_EDEVICE;
+    if (hipMemcpyAsync(base + o_head, &head, sizeof head, hipMemcpyHostToDevice, stream) != hipSuccess)
+        return FFS_EDEVICE;
     if (hipMemcpyAsync(base + o_p, p, (size_t)n * S * 4, hipMemcpyHostToDevice, stream) != hipSuccess)
         return FFS_EDEVICE;
-    uint32_t* ctlw = reinterpret_cast<uint32_t*>(base + o_ctl);
-    const size_t ctl_words = sizeof(Control) / 4;
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(256), 0, stream, ctlw, ctl_words);
+    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(base + o_err), (size_t)1);
     hipLaunchKernelGGL(k_build_table, dim3((S * n_pad + 255) / 256), dim3(256), 0, stream,
                        reinterpret_cast<const int*>(base + o_p), n, S, n_pad, ptb, (void*)(base + o_pt));
-    const InstDesc* di = reinterpret_cast<const InstDesc*>(base + o_desc);
-    Control* ctl = reinterpret_cast<Control*>(base + o_ctl);
+    const InstDesc* di = reinterpret_cast<const InstDesc*>(base + o_head + offsetof(Head, d));
+    Control* ctl = reinterpret_cast<Control*>(base + o_head + offsetof(Head, ctl));
     const int per_block = wpb * (lane ? kWave : d.G);
     const int blocks = (count + per_block - 1) / per_block;
     void* args[] = {(void*)&di, (void*)&perms, (void*)&count, (void*)&out, (void*)&ctl};
     if (hipLaunchKernel(kern, dim3(blocks), dim3(64 * wpb), args, lds, stream) != hipSuccess) return FFS_EDEVICE;
     int err = 0;
-    if (hipMemcpyAsync(&err, base + o_ctl + offsetof(Control, err), sizeof err, hipMemcpyDeviceToHost, stream) !=
+    if (hipMemcpyAsync(&err, base + o_err, sizeof err, hipMemcpyDeviceToHost, stream) !=
         hipSuccess)
         return FFS_EDEVICE;
     if (hipStreamSynchronize(stream) != hipSuccess) return FFS_EDEVICE;
-    if (err & 2) return FFS_EDEVICE;
-    if (err & 1) return FFS_EINVAL;
-    return FFS_OK;
+    return err ? FFS_EINVAL : FFS_OK;
 }
 
 }  // extern "C"

@@ -98,8 +98,13 @@ struct Control {
     int* counts;                 // [workgroups per generation launch]
     int base;                    // completed generation when the counts were zero
     int best_gen[kMaxGroups];    // per fold group: last generation folded into the records
-    int err;                     // bit 0: invalid permutation, bit 1: decode fault
+    int* err;                    // set to 1 by a decode of an invalid row (host memory, or noalloc scratch)
 };
+
+__device__ __forceinline__ void flag_invalid(const Control* c)
+{
+    __hip_atomic_store(c->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 
 __device__ __forceinline__ int completed_gen(const Control* c)
 {
@@ -1447,7 +1452,7 @@ __global__ void __launch_bounds__(512) k_evaluate(const InstDesc* __restrict__ I
     const uint32_t cm = decode_pipelined<MMAX, PT>(
         pipe_lane<PT>(gbase, stride, pT, n_pad, lane, g, k, S, G, groups), I, active);
     if (active && k == S - 1) out[idx] = gbad ? -1 : (int)cm;
-    if (active && k == 0 && gbad) atomicOr(&ctl->err, 1);
+    if (active && k == 0 && gbad) flag_invalid(ctl);
 }
 
 // ---- candidates of the learned pre-screen ----------------------------------

@@ -653,8 +653,8 @@ __global__ void __launch_bounds__(512) k_generation_lane(const InstDesc* __restr
 // ---- decode of caller-supplied permutations, lane mapping ------------------
 // One row per lane.  Each window of a row is read once, as four 16-byte
 // vectors, decoded, and marked in the lane's bit set (LDS atomics without
-// return, which nothing waits for); an invalid row gets makespan -1 and bit 0
-// of the control block's error word is set.  Bound by vector issue (M + 5
+// return, which nothing waits for); an invalid row gets makespan -1 and
+// sets the control block's error word.  Bound by vector issue (M + 5
 // operations per job and stage, four more per job for the check), by latency
 // where its LDS holds few waves.  Against the version that read every row
 // twice, value by value, with an atomic that returns per value: a
@@ -687,7 +687,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k
         bad |= seen[q * 64] != (left >= 32 ? 0xFFFFFFFFu : (left > 0 ? (1u << left) - 1u : 0u));
     }
     if (active) out[idx] = bad ? -1 : (int)cm;
-    if (active && bad) atomicOr(&ctl->err, 1);
+    if (active && bad) flag_invalid(ctl);
 }
 
 }  // namespace flowshop

@@ -33,6 +33,7 @@
 #include <string>
 #include <vector>
 
+#include "ffs_pinned.h"
 #include "ffs_tt.h"
 #include "philox.h"
 
@@ -869,6 +870,7 @@ struct ffs_tt_ctx {
     // workspace
     char* ws = nullptr;
     size_t ws_bytes = 0;
+    char* pin = nullptr;   // pinned host block (ffs_pinned.h): staging for small results
     bool bound = false;
     int gen = 0;
     TtDesc desc{};
@@ -1046,6 +1048,11 @@ int ffs_tt_create(void* stream, ffs_tt_ctx** out)
         delete c;
         return FFS_EDEVICE;
     }
+    c->pin = flowshop::pin_take();
+    if (!c->pin) {
+        delete c;
+        return FFS_ENOMEM;
+    }
     *out = c;
     return FFS_OK;
 }
@@ -1055,6 +1062,7 @@ int ffs_tt_destroy(ffs_tt_ctx* c)
     if (!c) return FFS_EINVAL;
     if (c->stream || c->bound) (void)hipStreamSynchronize(c->stream);
     for (auto e : c->ev) (void)hipEventDestroy(e);
+    flowshop::pin_give(c->pin);
     delete c;
     return FFS_OK;
 }
@@ -1373,13 +1381,20 @@ int ffs_tt_best(ffs_tt_ctx* c, int32_t run, int64_t* objective, int32_t* gen, in
     int rc = check_ready(c);
     if (rc != FFS_OK) return rc;
     if (run < 0 || run >= c->runs) return fail(c, FFS_EINVAL, "run %d", run);
-    long long rec[4];
-    std::vector<uint8_t> g(c->Lp);
-    TT_HIP(c, hipMemcpyAsync(rec, c->desc.best + (size_t)run * 4, sizeof rec, hipMemcpyDeviceToHost, c->stream));
-    TT_HIP(c, hipMemcpyAsync(g.data(), c->desc.best_genes + (size_t)run * c->Lp, c->Lp, hipMemcpyDeviceToHost, c->stream));
-    int err = 0;
-    TT_HIP(c, hipMemcpyAsync(&err, c->desc.err, 4, hipMemcpyDeviceToHost, c->stream));
+    // record, error word and the row (at most 32 KB) through the pinned block
+    static_assert((size_t)kMaxJ * kMaxS + 256 <= flowshop::kPinStage, "a row fits the staging");
+    char* stage = c->pin + flowshop::kPinWords;
+    TT_HIP(c, hipMemcpyAsync(stage, c->desc.best + (size_t)run * 4, 32, hipMemcpyDeviceToHost, c->stream));
+    TT_HIP(c, hipMemcpyAsync(stage + 32, c->desc.err, 4, hipMemcpyDeviceToHost, c->stream));
+    if (genes)
+        TT_HIP(c, hipMemcpyAsync(stage + 64, c->desc.best_genes + (size_t)run * c->Lp, c->Lp, hipMemcpyDeviceToHost,
+                                 c->stream));
     TT_HIP(c, hipStreamSynchronize(c->stream));
+    long long rec[4];
+    int err = 0;
+    std::memcpy(rec, stage, sizeof rec);
+    std::memcpy(&err, stage + 32, sizeof err);
+    const uint8_t* g = reinterpret_cast<const uint8_t*>(stage + 64);
     if (err) return fail(c, FFS_EDEVICE, "a kernel met an out-of-range gene");
     if (objective) *objective = rec[0];
     if (gen) *gen = (int32_t)rec[1];
