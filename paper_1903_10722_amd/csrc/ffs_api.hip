@@ -787,12 +787,13 @@ int prepare_classes(ffs_ctx* c)
         if (!c->sweep_kern) return fail(c, FFS_EUNSUPPORTED, "the line sweep needs at most 8 machines per stage");
         HIP_TRY(c, hipFuncSetAttribute(c->sweep_kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->lds_gen));
     }
-    while ((int)c->aux.size() < std::max(c->n_cls, c->nchain) - 1) {
+    const int lanes = std::max(std::max(c->n_cls, c->nchain), c->surr >= 0 ? 2 : 1);   // streams side by side
+    while ((int)c->aux.size() < lanes - 1) {
         hipStream_t st = nullptr;
         HIP_TRY(c, hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
         c->aux.push_back(st);
     }
-    while ((int)c->fork_ev.size() < std::max(c->n_cls, c->nchain)) {
+    while ((int)c->fork_ev.size() < lanes) {
         hipEvent_t e = nullptr;
         HIP_TRY(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
         c->fork_ev.push_back(e);
@@ -962,9 +963,9 @@ int surrogate_train(ffs_ctx* c)
     return mlp_adam(c);
 }
 
-// Candidates of every cell for the next generation: features (and exact
-// targets when Tout), predictions, and the chosen stream per cell.
-int surrogate_score(ffs_ctx* c, float* Tout)
+// Candidates of every cell for the next generation, on stream st: features
+// (and exact targets when Tout).
+int surrogate_features(ffs_ctx* c, float* Tout, hipStream_t st)
 {
     const auto& I = c->inst[c->surr];
     const InstDesc* di = reinterpret_cast<const InstDesc*>(c->ws + c->off_insts);
@@ -978,15 +979,54 @@ int surrogate_score(ffs_ctx* c, float* Tout)
         const int wv = c->cand_waves;
         void* args[] = {(void*)&di, (void*)&dl, (void*)&inst, (void*)&ctl, (void*)&cells, (void*)&X};
         HIP_TRY(c, hipLaunchKernel(c->kcandf, dim3((cells + wv - 1) / wv), dim3(64 * wv), args,
-                                   cand_lds_bytes(I.n, I.n_pad, c->cand_rsb, wv), c->stream));
+                                   cand_lds_bytes(I.n, I.n_pad, c->cand_rsb, wv), st));
     } else {
         const int per_block = I.wpb_eff * I.G;
         const int blocks = (c->surr_Nc + per_block - 1) / per_block;
         void* args[] = {(void*)&di, (void*)&dl, (void*)&inst, (void*)&ctl, (void*)&Nc, (void*)&X, (void*)&Tout};
-        HIP_TRY(c, hipLaunchKernel(c->kcand, dim3(blocks), dim3(64 * I.wpb_eff), args, I.lds, c->stream));
+        HIP_TRY(c, hipLaunchKernel(c->kcand, dim3(blocks), dim3(64 * I.wpb_eff), args, I.lds, st));
     }
-    return mlp_forward(c, X, c->surr_Ncp, at<uint16_t>(c, c->o_H1all), at<uint16_t>(c, c->o_H2all),
+    return FFS_OK;
+}
+
+// Predictions of the candidates and the chosen stream per cell.
+int surrogate_choose(ffs_ctx* c)
+{
+    return mlp_forward(c, at<const uint16_t>(c, c->o_Xall), c->surr_Ncp, at<uint16_t>(c, c->o_H1all), at<uint16_t>(c, c->o_H2all),
                        at<float>(c, c->o_yall), c->surr_K, at<int>(c, c->o_choice), c->surr_Nc);
+}
+
+int surrogate_score(ffs_ctx* c, float* Tout)
+{
+    int rc = surrogate_features(c, Tout, c->stream);
+    return rc ? rc : surrogate_choose(c);
+}
+
+// `gens` screened generations into the stream that is being captured.  The
+// next generation's candidates and their features need the population alone,
+// not the weights: they run beside the training step (twelve launches that
+// fill a small part of the chip: 94 us at 4096 rows; the features of 4096
+// cells x 8 candidates of 1000 jobs 128 us; a screened generation 440 ->
+// 408 us), joined before the predictions.
+int capture_screened(ffs_ctx* c, int gens)
+{
+    int rc = surrogate_features(c, nullptr, c->stream);
+    for (int t = 0; t < gens && rc == FFS_OK; ++t) {
+        rc = surrogate_choose(c);
+        if (rc == FFS_OK) rc = launch_generation(c, 0);
+        if (rc != FFS_OK) break;
+        const bool more = t + 1 < gens;
+        if (more) {
+            HIP_TRY(c, hipEventRecord(c->fork_ev[0], c->stream));
+            HIP_TRY(c, hipStreamWaitEvent(c->aux[0], c->fork_ev[0], 0));
+            rc = surrogate_features(c, nullptr, c->aux[0]);
+            HIP_TRY(c, hipEventRecord(c->fork_ev[1], c->aux[0]));
+        }
+        const int trc = surrogate_train(c);
+        if (more) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->fork_ev[1], 0));
+        if (rc == FFS_OK) rc = trc;
+    }
+    return rc;
 }
 
 // Decode `count` device rows of `perms` (int32 [count][n]) into out (int32 [count]).
@@ -1709,12 +1749,10 @@ int ffs_evolve(ffs_ctx* c, int32_t generations)
                         HIP_TRY(c, hipEventRecord(c->fork_ev[k], c->aux[k - 1]));
                         HIP_TRY(c, hipStreamWaitEvent(c->stream, c->fork_ev[k], 0));
                     }
+                } else if (c->surr >= 0) {
+                    crc = capture_screened(c, L);
                 } else {
-                    for (int t = 0; t < L && crc == FFS_OK; ++t) {
-                        if (c->surr >= 0) crc = surrogate_score(c, nullptr);
-                        if (crc == FFS_OK) crc = launch_generation(c, 0);
-                        if (crc == FFS_OK && c->surr >= 0) crc = surrogate_train(c);
-                    }
+                    for (int t = 0; t < L && crc == FFS_OK; ++t) crc = launch_generation(c, 0);
                 }
                 if (crc == FFS_OK && I > 0) crc = launch_migration(c, -1, true);
                 hipError_t ec = hipStreamEndCapture(c->stream, &graph);
