@@ -274,7 +274,7 @@ struct ffs_ctx {
     size_t o_w = 0, o_wb = 0, o_m = 0, o_v = 0, o_g = 0;
     size_t o_Xall = 0, o_H1all = 0, o_H2all = 0, o_yall = 0, o_Tall = 0, o_choice = 0;
     size_t o_idx = 0, o_Xb = 0, o_tb = 0, o_H1b = 0, o_H2b = 0, o_yb = 0, o_dy = 0, o_dZ2 = 0, o_dZ1 = 0;
-    size_t o_part = 0, o_cpart = 0, o_dpart = 0, o_ringX = 0, o_ringT = 0;
+    size_t o_part = 0, o_part1 = 0, o_cpart = 0, o_dpart = 0, o_ringX = 0, o_ringT = 0;
     size_t o_adam = 0, o_bc = 0;     // Adam step count (int64) + its corrections; correction table
     // graph of one migration epoch (or a fixed chunk when nothing migrates)
     bool use_graphs = true;
@@ -567,6 +567,7 @@ void layout(ffs_ctx* c)
         c->o_dZ2 = take(Bt * kHidden * 2);
         c->o_dZ1 = take(Bt * kHidden * 2);
         c->o_part = take((size_t)(kBatch / 128) * kHidden * kHidden * 4);
+        c->o_part1 = take((size_t)(kBatch / 128) * kHidden * kFeat * 4);
         c->o_cpart = take((size_t)(kBatch / 64) * 3 * kHidden * 4);
         c->o_dpart = take((size_t)(kBatch / 64) * 4);
         c->o_ringX = take((size_t)kRing * kFeat * 2);
@@ -845,10 +846,15 @@ template <bool TA, bool TB, int EPI>
 int gemm(ffs_ctx* c, const uint16_t* A, const uint16_t* B, int M, int N, int K, int lda, int ldb, float* Cf,
          uint16_t* Cb, int ldc, const float* bias, const uint16_t* mask, int splits)
 {
-    if (M % GBM || N % GBN || K % (GBK * splits))
+    if (M % GBT || N % GBT || K % (GBK * splits))
         return fail(c, FFS_EINVAL, "gemm shape %dx%dx%d (splits %d) not tiled", M, N, K, splits);
-    hipLaunchKernelGGL((k_gemm<TA, TB, EPI>), dim3(N / GBN, M / GBM, splits), dim3(256), 0, c->stream, A, B, M, N, K,
-                       lda, ldb, Cf, Cb, ldc, bias, mask);
+    // 64 x 64 tiles below two 128 x 128 tiles per CU
+    if ((N / GBT) * (M / GBT) * splits < 512)
+        hipLaunchKernelGGL((k_gemm<TA, TB, EPI, 64>), dim3(N / 64, M / 64, splits), dim3(256), 0, c->stream, A, B, M, N,
+                           K, lda, ldb, Cf, Cb, ldc, bias, mask);
+    else
+        hipLaunchKernelGGL((k_gemm<TA, TB, EPI, GBT>), dim3(N / GBT, M / GBT, splits), dim3(256), 0, c->stream, A, B, M,
+                           N, K, lda, ldb, Cf, Cb, ldc, bias, mask);
     return FFS_OK;
 }
 
@@ -900,8 +906,6 @@ int mlp_gradients(ffs_ctx* c, const uint16_t* X, const float* t, int rows, float
     rc = gemm<true, false, EPI_F32>(c, dZ2, H1, kHidden, kHidden, rows, kHidden, kHidden, part, nullptr, kHidden,
                                     nullptr, nullptr, splits);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_sum_splits, dim3(kHidden * kHidden / 256), dim3(256), 0, c->stream, part, splits,
-                       (size_t)kHidden * kHidden, grad + kP_W2);
     rc = gemm<false, false, EPI_MASK_BF16>(c, dZ2, wb + kP_W2, rows, kHidden, kHidden, kHidden, kHidden, nullptr, dZ1,
                                            kHidden, nullptr, H1, 1);
     if (rc) return rc;
@@ -919,22 +923,31 @@ int mlp_gradients(ffs_ctx* c, const uint16_t* X, const float* t, int rows, float
         float* dpart = at<float>(c, c->o_dpart);
         const int chunks = rows / 64;
         hipLaunchKernelGGL(k_colsum3, dim3(1, chunks, 3), dim3(256), 0, c->stream, cs, (const float*)dy, cpart, dpart);
-        hipLaunchKernelGGL(k_colsum3_sum, dim3((3 * kHidden + 1 + 255) / 256), dim3(256), 0, c->stream, cs,
-                           (const float*)cpart, chunks, (const float*)dpart, grad + kP_b3,
-                           step ? at<long long>(c, c->o_adam) : nullptr, at<const float2>(c, c->o_bc), kBcSteps,
-                           reinterpret_cast<float*>(c->ws + c->o_adam + 8));
+        rc = gemm<true, false, EPI_F32>(c, dZ1, X, kHidden, kFeat, rows, kHidden, kFeat, at<float>(c, c->o_part1),
+                                        nullptr, kFeat, nullptr, nullptr, splits);
+        if (rc) return rc;
+        GradSums gs;
+        gs.part2 = part;
+        gs.part1 = at<float>(c, c->o_part1);
+        gs.part = cpart;
+        gs.dpart = dpart;
+        gs.gW2 = grad + kP_W2;
+        gs.gW1 = grad + kP_W1;
+        gs.dsum = grad + kP_b3;
+        gs.splits = splits;
+        gs.chunks = chunks;
+        gs.step = step ? at<long long>(c, c->o_adam) : nullptr;
+        gs.table = at<const float2>(c, c->o_bc);
+        gs.steps = kBcSteps;
+        gs.bc = reinterpret_cast<float*>(c->ws + c->o_adam + 8);
+        hipLaunchKernelGGL(k_grad_sums, dim3((kGradSums + 255) / 256), dim3(256), 0, c->stream, cs, gs);
     }
-    rc = gemm<true, false, EPI_F32>(c, dZ1, X, kHidden, kFeat, rows, kHidden, kFeat, part, nullptr, kFeat, nullptr,
-                                    nullptr, splits);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_sum_splits, dim3(kHidden * kFeat / 256), dim3(256), 0, c->stream, part, splits,
-                       (size_t)kHidden * kFeat, grad + kP_W1);
     HIP_TRY(c, hipGetLastError());
     return FFS_OK;
 }
 
 // One Adam step; the step count and its bias corrections were advanced by
-// the gradients' column-sum kernel (mlp_gradients with `step` set).
+// the gradients' last kernel (mlp_gradients with `step` set).
 int mlp_adam(ffs_ctx* c)
 {
     hipLaunchKernelGGL(k_adam, dim3((kParams + 255) / 256), dim3(256), 0, c->stream, at<float>(c, c->o_w),

@@ -31,7 +31,11 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_floa
 // C[M x N] = opA[M x K] * opB[K x N], BF16 operands, FP32 accumulation.
 //   TA = false: A stored [M][K] (row stride lda);  true: stored [K][M].
 //   TB = false: B stored [K][N] (row stride ldb);  true: stored [N][K].
-// Block tile 128 x 128, K step 64, four waves of 64 x 64 (2 x 2 MFMA 32x32x16).
+// Block tile T x T (T = 128, or 64 where 128 would leave CUs without one: 4096
+// rows are 128 tiles of 128 x 128), K step 64, four waves of T/2 x T/2 in MFMA
+// 32x32x16 tiles; an element's sum runs over k in the same order for every T.
+// 4096 x 512 x 512, T = 128 -> 64: bias + ReLU 9.7 -> 8.0 us, masked 14.2 ->
+// 11.3 us.
 // v_mfma_f32_32x32x16_bf16 lane layout: lane l supplies row (l % 32) of A and
 // column (l % 32) of B for k = 8 (l / 32) .. + 7; it receives column (l % 32)
 // of D at rows 8 (r / 4) + 4 (l / 32) + r % 4, r = 0..15.
@@ -40,11 +44,11 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_floa
 // one.  A K-contiguous operand is read as 16-byte rows (four per thread); an
 // operand stored k-major ([K][M] or [K][N]) is read by half the workgroup as
 // 8 x 8 blocks (eight 16-byte rows of k), transposed in registers with byte
-// permutes and written as eight 16-byte rows of i.
+// permutes (T threads per operand) and written as eight 16-byte rows of i.
 // blockIdx.z splits K into gridDim.z equal ranges (EPI_F32 writes each
 // split's partial product to its own M x N slice).
 enum GemmEpi { EPI_F32 = 0, EPI_BIAS_RELU_BF16 = 1, EPI_MASK_BF16 = 2 };
-constexpr int GBM = 128, GBN = 128, GBK = 64, GLD = GBK + 8;
+constexpr int GBT = 128, GBK = 64, GLD = GBK + 8;
 
 // Transpose of an 8 x 8 block of 16-bit values: x[r] holds row r (element c
 // in half c % 2 of word c / 2); y[c] receives column c.
@@ -63,24 +67,24 @@ __device__ __forceinline__ void transpose8x8_u16(const gu32x4_t (&x)[8], gu32x4_
 }
 
 // One operand's share of a K tile, HBM -> registers -> LDS ([x][k] rows of
-// GLD).  KM = false: the operand is k-contiguous per row, 1024 16-byte rows
-// of 8 k, four per thread.  KM = true: stored k-major, one 8 x 8 block per
-// thread of the half `half` of the workgroup, transposed in registers.
-template <bool KM>
+// GLD).  KM = false: the operand is k-contiguous per row, 8 T 16-byte rows of
+// 8 k, T / 32 per thread.  KM = true: stored k-major, one 8 x 8 block per
+// thread of threads [T half, T half + T), transposed in registers.
+template <bool KM, int T>
 struct GemmStage {
-    gu32x4_t r[KM ? 8 : 4];
+    gu32x4_t r[KM ? 8 : T / 32];
 
     __device__ __forceinline__ void load(const uint16_t* __restrict__ X, int ld, int x0, int k0, int tid, int half)
     {
         if constexpr (!KM) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < T / 32; ++u) {
                 const int v = tid + 256 * u, x = v >> 3, kk = (v & 7) * 8;
                 r[u] = *reinterpret_cast<const gu32x4_t*>(&X[(size_t)(x0 + x) * ld + k0 + kk]);
             }
         } else {
-            if ((tid >> 7) == half) {
-                const int q = tid & 127, kb = (q & 7) * 8, xb = (q >> 3) * 8;
+            if (tid / T == half) {
+                const int q = tid % T, kb = (q & 7) * 8, xb = (q >> 3) * 8;
 #pragma unroll
                 for (int t = 0; t < 8; ++t)
                     r[t] = *reinterpret_cast<const gu32x4_t*>(&X[(size_t)(k0 + kb + t) * ld + x0 + xb]);
@@ -92,15 +96,15 @@ struct GemmStage {
     {
         if constexpr (!KM) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < T / 32; ++u) {
                 const int v = tid + 256 * u, x = v >> 3, kk = (v & 7) * 8;
                 *reinterpret_cast<gu32x4_t*>(&Xs[x * GLD + kk]) = r[u];
             }
         } else {
-            if ((tid >> 7) == half) {
+            if (tid / T == half) {
                 // eight consecutive threads fill the eight 16-byte k-chunks of
                 // one LDS row: no bank conflicts
-                const int q = tid & 127, kb = (q & 7) * 8, xb = (q >> 3) * 8;
+                const int q = tid % T, kb = (q & 7) * 8, xb = (q >> 3) * 8;
                 gu32x4_t y[8];
                 transpose8x8_u16(r, y);
 #pragma unroll
@@ -110,44 +114,45 @@ struct GemmStage {
     }
 };
 
-template <bool TA, bool TB, int EPI>
+template <bool TA, bool TB, int EPI, int T>
 __global__ void __launch_bounds__(256) k_gemm(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                               int M, int N, int K, int lda, int ldb, float* __restrict__ Cf,
                                               uint16_t* __restrict__ Cb, int ldc, const float* __restrict__ bias,
                                               const uint16_t* __restrict__ mask)
 {
-    __shared__ __align__(16) uint16_t As[GBM * GLD];
-    __shared__ __align__(16) uint16_t Bs[GBN * GLD];
+    constexpr int MT = T / 64;   // MFMA tiles of a wave per direction
+    __shared__ __align__(16) uint16_t As[T * GLD];
+    __shared__ __align__(16) uint16_t Bs[T * GLD];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int bm = blockIdx.y * GBM, bn = blockIdx.x * GBN;
-    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+    const int bm = blockIdx.y * T, bn = blockIdx.x * T;
+    const int wm = (wave >> 1) * (T / 2), wn = (wave & 1) * (T / 2);
     const int ks = K / gridDim.z, kbeg = blockIdx.z * ks, kend = kbeg + ks;
-    f32x16_t acc[2][2];
+    f32x16_t acc[MT][MT];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < MT; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < MT; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
     // the mask of this thread's outputs, read before the K loop so that its
     // latency hides behind the MFMAs
-    uint32_t mk[EPI == EPI_MASK_BF16 ? 64 : 1];
+    uint32_t mk[EPI == EPI_MASK_BF16 ? 16 * MT * MT : 1];
     if constexpr (EPI == EPI_MASK_BF16) {
 #pragma unroll
-        for (int ti = 0; ti < 2; ++ti)
+        for (int ti = 0; ti < MT; ++ti)
 #pragma unroll
-            for (int tj = 0; tj < 2; ++tj)
+            for (int tj = 0; tj < MT; ++tj)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int i = bm + wm + ti * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
                     const int j = bn + wn + tj * 32 + (lane & 31);
-                    mk[(ti * 2 + tj) * 16 + r] = mask[(size_t)i * ldc + j];
+                    mk[(ti * MT + tj) * 16 + r] = mask[(size_t)i * ldc + j];
                 }
     }
-    // k-major operands: A by threads 0..127, B by threads 128..255
-    GemmStage<TA> sa;
-    GemmStage<!TB> sb;
+    // k-major operands: A by threads 0..T-1, B by the next T
+    GemmStage<TA, T> sa;
+    GemmStage<!TB, T> sb;
     sa.load(A, lda, bm, kbeg, tid, 0);
     sb.load(B, ldb, bn, kbeg, tid, 1);
     sa.store(As, tid, 0);
@@ -156,16 +161,16 @@ __global__ void __launch_bounds__(256) k_gemm(const uint16_t* __restrict__ A, co
     auto mfma_tile = [&]() {
 #pragma unroll
         for (int kk = 0; kk < GBK; kk += 16) {
-            bf16x8_t a[2], b[2];
+            bf16x8_t a[MT], b[MT];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < MT; ++t) {
                 a[t] = *reinterpret_cast<const bf16x8_t*>(&As[(wm + t * 32 + (lane & 31)) * GLD + kk + 8 * (lane >> 5)]);
                 b[t] = *reinterpret_cast<const bf16x8_t*>(&Bs[(wn + t * 32 + (lane & 31)) * GLD + kk + 8 * (lane >> 5)]);
             }
 #pragma unroll
-            for (int ti = 0; ti < 2; ++ti)
+            for (int ti = 0; ti < MT; ++ti)
 #pragma unroll
-                for (int tj = 0; tj < 2; ++tj)
+                for (int tj = 0; tj < MT; ++tj)
                     acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ti], b[tj], acc[ti][tj], 0, 0, 0);
         }
     };
@@ -184,9 +189,9 @@ __global__ void __launch_bounds__(256) k_gemm(const uint16_t* __restrict__ A, co
     mfma_tile();
     float* Cz = (EPI == EPI_F32) ? Cf + (size_t)blockIdx.z * M * ldc : nullptr;
 #pragma unroll
-    for (int ti = 0; ti < 2; ++ti)
+    for (int ti = 0; ti < MT; ++ti)
 #pragma unroll
-        for (int tj = 0; tj < 2; ++tj)
+        for (int tj = 0; tj < MT; ++tj)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int i = bm + wm + ti * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
@@ -199,7 +204,7 @@ __global__ void __launch_bounds__(256) k_gemm(const uint16_t* __restrict__ A, co
                     const float z = v + bias[j];
                     Cb[o] = f32_to_bf16(z > 0.f ? z : 0.f);
                 } else {
-                    Cb[o] = (bf16_to_f32((uint16_t)mk[(ti * 2 + tj) * 16 + r]) > 0.f) ? f32_to_bf16(v) : (uint16_t)0;
+                    Cb[o] = (bf16_to_f32((uint16_t)mk[(ti * MT + tj) * 16 + r]) > 0.f) ? f32_to_bf16(v) : (uint16_t)0;
                 }
             }
 }
@@ -219,15 +224,6 @@ __device__ __forceinline__ float sum_strided(const float* __restrict__ x, size_t
     }
     for (; y < n; ++y) s += x[(size_t)y * stride];
     return s;
-}
-
-// out[i] = sum over splits s of part[s][i]  (fixed order: deterministic)
-static __global__ void __launch_bounds__(256) k_sum_splits(const float* __restrict__ part, int splits, size_t count,
-                                                    float* __restrict__ out)
-{
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    out[i] = sum_strided(part + i, count, splits);
 }
 
 // ---- output layer --------------------------------------------------------
@@ -302,7 +298,7 @@ static __global__ void __launch_bounds__(256) k_mlp_out_dz2(const uint16_t* __re
 // for columns 8 g .. 8 g + 7 (16-byte reads), the four row groups are added
 // in order through LDS, and part[y][m * 512 + j] receives the chunk's sum.
 // Matrix 0 is weighted by dy[i]; block y of matrix 0 also writes
-// dpart[y] = sum of dy over its rows.  k_colsum3_sum adds the chunks.
+// dpart[y] = sum of dy over its rows.  k_grad_sums adds the chunks.
 struct Colsum3 {
     const uint16_t* X[3];
     float* out[3];
@@ -341,35 +337,57 @@ static __global__ void __launch_bounds__(256) k_colsum3(Colsum3 a, const float* 
     }
 }
 
-// out_m[j] = sum over chunks y (in order) of part[y][m * 512 + j]; dsum =
-// sum of dpart in order.  With step non-null (a training step follows) one
-// thread also advances the Adam step count t kept in device memory (so a
-// captured graph can replay training steps without the host knowing their
-// number) and writes step t + 1's bias corrections 1 - beta^(t+1) to bc,
-// from `table` (computed on the host in FP64 and rounded to FP32; entry t for
-// t < steps, both exactly 1 beyond).
-static __global__ void __launch_bounds__(256) k_colsum3_sum(Colsum3 a, const float* __restrict__ part, int chunks,
-                                                     const float* __restrict__ dpart, float* __restrict__ dsum,
-                                                     long long* step, const float2* __restrict__ table, int steps,
-                                                     float* __restrict__ bc)
+// The fixed-order sums that end a backward pass, in one launch (three before:
+// the split-K partial products of two weight gradients and the column sums'
+// chunks; a pass was 114 us of ten launches):
+//   e < nW2:              W2's gradient, sum over splits of part2[s][e]
+//   then nW1:             W1's gradient, the same from part1
+//   then 3 * 512:         out_m[j] = sum over chunks y of part[y][m * 512 + j]
+//   then one:             dsum = sum of dpart.
+// With step non-null (a training step follows) the last one also advances the
+// Adam step count t kept in device memory (so a captured graph can replay
+// training steps without the host knowing their number) and writes step
+// t + 1's bias corrections 1 - beta^(t+1) to bc, from `table` (computed on
+// the host in FP64 and rounded to FP32; entry t for t < steps, both exactly 1
+// beyond).
+struct GradSums {
+    const float *part2, *part1, *part, *dpart;
+    float *gW2, *gW1, *dsum;
+    int splits, chunks;
+    long long* step;
+    const float2* table;
+    int steps;
+    float* bc;
+};
+
+constexpr int kGradSums = kHidden * kHidden + kHidden * kFeat + 3 * kHidden + 1;
+
+static __global__ void __launch_bounds__(256) k_grad_sums(Colsum3 a, GradSums g)
 {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < 3 * kHidden) a.out[e / kHidden][e % kHidden] = sum_strided(part + e, (size_t)3 * kHidden, chunks);
-    if (e == 3 * kHidden) {
-        *dsum = sum_strided(dpart, 1, chunks);
-        if (step) {
-            const long long t = *step + 1;
-            *step = t;
-            const float2 b = (t <= steps) ? table[t - 1] : make_float2(1.f, 1.f);
-            bc[0] = b.x;
-            bc[1] = b.y;
+    constexpr int nW2 = kHidden * kHidden, nW1 = kHidden * kFeat;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < nW2) {
+        g.gW2[i] = sum_strided(g.part2 + i, nW2, g.splits);
+    } else if (i < nW2 + nW1) {
+        g.gW1[i - nW2] = sum_strided(g.part1 + (i - nW2), nW1, g.splits);
+    } else if (i < nW2 + nW1 + 3 * kHidden) {
+        const int e = i - nW2 - nW1;
+        a.out[e / kHidden][e % kHidden] = sum_strided(g.part + e, (size_t)3 * kHidden, g.chunks);
+    } else if (i == nW2 + nW1 + 3 * kHidden) {
+        *g.dsum = sum_strided(g.dpart, 1, g.chunks);
+        if (g.step) {
+            const long long t = *g.step + 1;
+            *g.step = t;
+            const float2 b = (t <= g.steps) ? g.table[t - 1] : make_float2(1.f, 1.f);
+            g.bc[0] = b.x;
+            g.bc[1] = b.y;
         }
     }
 }
 
 // Adam (Kingma & Ba) on FP32 master weights; writes the BF16 copy when given.
 // One Adam step on every parameter with the bias corrections bc[0] =
-// 1 - beta1^t, bc[1] = 1 - beta2^t of step t, which k_colsum3_sum looked up
+// 1 - beta1^t, bc[1] = 1 - beta2^t of step t, which k_grad_sums looked up
 // when it advanced the step count kept in device memory.
 static __global__ void __launch_bounds__(256) k_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
                                               const float* __restrict__ g, uint16_t* __restrict__ wb, int count,
