@@ -17,7 +17,7 @@ HIPCC_FLAGS = [
 ]
 
 
-PICK_PARTS = 6   # kernel families of csrc/ffs_pick.hip, one object each
+PICK_PARTS = 7   # kernel families of csrc/ffs_pick.hip, one object each
 PROBE_LIB = os.path.join(BUILD, "liblds_probe.so")
 
 

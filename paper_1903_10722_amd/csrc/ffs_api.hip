@@ -138,7 +138,7 @@ struct HostIsland {
     int cell_base;
     int chain = 0;                // fold group of its generations
     int rec = 0;                  // its instance's record slot
-    size_t off_genes[2], off_mk[2], off_genkey, off_minmax, off_sorted, off_sortbest;
+    size_t off_genes[2], off_mk[2], off_genkey, off_minmax, off_sorted, off_sortbest, off_ep;
 };
 
 struct HostInstance {
@@ -259,6 +259,11 @@ struct ffs_ctx {
     // with several launch classes, each class is a fold group whose
     // generations of an epoch run as one branch of the epoch graph
     bool class_groups = false;
+    // every island is one workgroup's work (per-stage mapping, one class, no
+    // sweep, no pre-screen, what k_epoch is compiled for): captured epochs run
+    // as one launch
+    bool resident = false;
+    void* epoch_kern = nullptr;
     int ngroup = 1;                // fold groups
     int sweep_diags = 0;
     size_t off_sweep = 0, sweep_lds = 0;
@@ -478,6 +483,13 @@ void layout(ffs_ctx* c)
         }
     }
     c->ngroup = c->class_groups ? c->n_cls : c->nchain;
+    c->resident = c->n_cls == 1 && c->nchain == 1 && c->n_work == c->n_isl && c->sweep.empty();
+    for (auto& I : c->inst)
+        if (I.map_eff || I.cfg.surrogate_k > 1 || ox_vectors(I.n, I.S) > kOxSmall ||
+            decode_keys(I.n, I.S, I.m.data(), I.p.data(), I.jb, c->mm).pkey != kKeyIdx)
+            c->resident = false;
+    c->epoch_kern = c->resident ? pick_epoch(c->mm, c->ptb) : nullptr;
+    if (!c->epoch_kern) c->resident = false;
     // one launch per class: its work range, LDS bytes and launch-count slots
     // (the first class's launch also carries the best-ever workgroup)
     c->cls_w0.assign(c->n_cls + 1, 0);
@@ -526,6 +538,7 @@ void layout(ffs_ctx* c)
             L.off_minmax = take(16);
             L.off_sorted = take((size_t)L.size * sizeof(int));
             L.off_sortbest = take(sizeof(int));
+            L.off_ep = take(16 + (size_t)I.n_pad * 2);   // record, then the row
         }
         c->lds_gen = std::max(c->lds_gen, I.lds);
     }
@@ -705,6 +718,25 @@ int launch_generation(ffs_ctx* c, int mode, int chain = -1)
     return FFS_OK;
 }
 
+// `gens` generations of a resident context in one launch (the generation
+// before must have been folded), and the fold of their records unless the
+// migration that follows carries it.
+int launch_epoch(ffs_ctx* c, int gens, bool fold)
+{
+    const InstDesc* di = reinterpret_cast<const InstDesc*>(c->ws + c->off_insts);
+    const IslandDesc* dl = reinterpret_cast<const IslandDesc*>(c->ws + c->off_isls);
+    const WorkItem* dw = reinterpret_cast<const WorkItem*>(c->ws + c->off_work);
+    Control* ctl = reinterpret_cast<Control*>(c->ws + c->off_ctl);
+    void* args[] = {(void*)&di, (void*)&dl, (void*)&dw, (void*)&ctl, (void*)&gens};
+    HIP_TRY(c, hipLaunchKernel(c->epoch_kern, dim3((unsigned)c->n_work), dim3(64 * c->cls_wpb[0]), args, c->cls_lds[0],
+                               c->stream));
+    if (fold)
+        hipLaunchKernelGGL(k_epoch_fold, dim3(1), dim3(256), 0, c->stream, di, dl, ctl, (int)c->inst.size(),
+                           c->n_work);
+    HIP_TRY(c, hipGetLastError());
+    return FFS_OK;
+}
+
 // Folds the completed generation into the best-ever records if the next
 // generation launch has not done so yet.
 int flush_best(ffs_ctx* c, bool capturing = false)
@@ -722,20 +754,23 @@ int flush_best(ffs_ctx* c, bool capturing = false)
 
 int launch_migration(ffs_ctx* c, int force_inst, bool capturing = false)
 {
-    // migration rewrites rows of the completed generation: record its best first
-    int frc = flush_best(c, capturing);
+    // migration rewrites rows of the completed generation: record its best
+    // first (a captured resident epoch keeps its own rows, and the first
+    // k_mig_sort folds them)
+    const bool fold = capturing && c->resident;
+    int frc = fold ? FFS_OK : flush_best(c, capturing);
     if (frc) return frc;
     const InstDesc* di = reinterpret_cast<const InstDesc*>(c->ws + c->off_insts);
     const IslandDesc* dl = reinterpret_cast<const IslandDesc*>(c->ws + c->off_isls);
     const PairDesc* dp = reinterpret_cast<const PairDesc*>(c->ws + c->off_pairs);
-    const Control* ctl = reinterpret_cast<const Control*>(c->ws + c->off_ctl);
+    Control* ctl = reinterpret_cast<Control*>(c->ws + c->off_ctl);
     if (c->any_ring) {
         hipLaunchKernelGGL(k_mig_minmax, dim3(c->n_isl), dim3(256), 0, c->stream, di, dl, ctl, force_inst);
         hipLaunchKernelGGL(k_mig_ring, dim3(c->n_isl), dim3(256), 0, c->stream, di, dl, ctl, force_inst);
     }
     const int chunks = (c->max_size + kMigRows - 1) / kMigRows;
-    hipLaunchKernelGGL(k_mig_sort, dim3(c->n_isl), dim3(kSortThreads), c->lds_sort, c->stream, di, dl, ctl, force_inst,
-                       -1);
+    hipLaunchKernelGGL(k_mig_sort, dim3(c->n_isl + (fold ? 1 : 0)), dim3(kSortThreads), c->lds_sort, c->stream, di, dl,
+                       ctl, force_inst, -1, fold ? (int)c->inst.size() : 0, c->n_work);
     if (c->n_pairs > 0)
         hipLaunchKernelGGL(k_mig_adapt, dim3(c->n_pairs, chunks), dim3(256), 0, c->stream, di, dl, dp, ctl,
                            force_inst);
@@ -747,7 +782,7 @@ int launch_migration(ffs_ctx* c, int force_inst, bool capturing = false)
         for (int e = 0; e < I.n_edges; ++e) {
             if (e > 0)
                 hipLaunchKernelGGL(k_mig_sort, dim3(c->n_isl), dim3(kSortThreads), c->lds_sort, c->stream, di, dl, ctl,
-                                   force_inst, (int)ii);
+                                   force_inst, (int)ii, 0, 0);
             hipLaunchKernelGGL(k_mig_adapt, dim3(1, chunks), dim3(256), 0, c->stream, di, dl, dp + I.edge0 + e, ctl,
                                force_inst);
         }
@@ -784,6 +819,8 @@ int prepare_classes(ffs_ctx* c)
         if (!c->cls_kern[k]) return fail(c, FFS_EUNSUPPORTED, "no kernel for %d machines", c->mm);
         HIP_TRY(c, hipFuncSetAttribute(c->cls_kern[k], hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->lds_gen));
     }
+    if (c->epoch_kern)
+        HIP_TRY(c, hipFuncSetAttribute(c->epoch_kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->lds_gen));
     if (!c->sweep.empty()) {
         if (!c->sweep_kern) return fail(c, FFS_EUNSUPPORTED, "the line sweep needs at most 8 machines per stage");
         HIP_TRY(c, hipFuncSetAttribute(c->sweep_kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->lds_gen));
@@ -1570,6 +1607,8 @@ int ffs_bind_workspace(ffs_ctx* c, void* dptr, size_t bytes)
             e.sweep = L.spec.kind == 0 ? L.spec.sweep : 0;
             e.chain = L.chain;
             e.rec = L.rec;
+            e.ep_rec = reinterpret_cast<int*>(c->ws + L.off_ep);
+            e.ep_perm = reinterpret_cast<uint16_t*>(c->ws + L.off_ep + 16);
             hl.push_back(e);
         }
         isl_base += (int)I.isl.size();
@@ -1762,6 +1801,8 @@ int ffs_evolve(ffs_ctx* c, int32_t generations)
                         HIP_TRY(c, hipEventRecord(c->fork_ev[k], c->aux[k - 1]));
                         HIP_TRY(c, hipStreamWaitEvent(c->stream, c->fork_ev[k], 0));
                     }
+                } else if (c->resident) {
+                    crc = launch_epoch(c, L, I == 0);
                 } else if (c->surr >= 0) {
                     crc = capture_screened(c, L);
                 } else {
@@ -1782,8 +1823,14 @@ int ffs_evolve(ffs_ctx* c, int32_t generations)
                 }
                 c->epoch_len = L;
             }
+            // a resident epoch folds only its own generations
+            if (c->resident) {
+                rc = flush_best(c);
+                if (rc) return rc;
+            }
             HIP_TRY(c, hipGraphLaunch(c->epoch_exec, c->stream));
             c->gen += L;
+            if (c->resident) c->flushed = c->gen;
             left -= L;
             continue;
         }

@@ -79,6 +79,8 @@ struct IslandDesc {
     int sweep;                   // cellular update: 0 synchronous, 1 line sweep
     int chain;                   // fold group of the island's generations
     int rec;                     // its instance's record slot for that group
+    uint16_t* ep_perm;           // resident epochs: the epoch's best row [n_pad] and its record
+    int* ep_rec;                 // [3]: makespan, generation, slot
 };
 
 struct WorkItem {
@@ -140,6 +142,7 @@ __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~(size_t
 // most that the register path of the crossover holds.
 __host__ __device__ inline int ox_vectors(int n, int S) { return ((n + 7) / 8 + S - 1) / S; }
 constexpr int kOxVec = 13;
+constexpr int kOxSmall = 3;   // its smallest tier
 
 // LDS of one group: the child's row of n_pad uint16 and 16 bytes of padding,
 // so that the groups of a wave start 4 banks apart and same-offset accesses of
@@ -820,10 +823,15 @@ __device__ __attribute__((noinline)) void ox_wave_long(uint16_t* A, uint16_t* M,
     ox_group_long<2>(A, M, P1, P2, o, ox_vectors(o.n, kWave), 0, lane, kWave, true);
 }
 
+template <bool SMALL>   // at most kOxSmall vectors per lane
 __device__ __forceinline__ void ox_group_rows(uint16_t* A, int n_pad, const uint16_t* P1, const uint16_t* P2,
                                               const OxCut& o, int g, int k, int S, bool active)
 {
     const int vpl = ox_vectors(o.n, S);
+    if (SMALL) {
+        ox_group_regs<kOxSmall>(A, P1, P2, o, vpl, g, k, S, active);
+        return;
+    }
     if (vpl <= 3) ox_group_regs<3>(A, P1, P2, o, vpl, g, k, S, active);
     else if (vpl <= 7) ox_group_regs<7>(A, P1, P2, o, vpl, g, k, S, active);
     else if (vpl <= kOxVec) ox_group_regs<kOxVec>(A, P1, P2, o, vpl, g, k, S, active);
@@ -976,7 +984,7 @@ __device__ __forceinline__ CellMeta cellular_offspring(const InstDesc* I, const 
     const int n = I->n, n_pad = I->n_pad;
     const CellPlan pl = cell_plan(I, L, slot, sub, gen, cur);
     const uint16_t* gp = L->genes[cur];
-    ox_group_rows(A, n_pad, gp + (size_t)pl.p1 * n_pad, gp + (size_t)pl.p2 * n_pad,
+    ox_group_rows<false>(A, n_pad, gp + (size_t)pl.p1 * n_pad, gp + (size_t)pl.p2 * n_pad,
                   ox_cut(n, pl.meta.cx, pl.meta.a, pl.meta.b, false, false), g, k, S, active);
     swap_genes(A, pl.meta.mx && active && k == 0, pl.meta.mi, pl.meta.mj);
     return pl.meta;
@@ -1130,6 +1138,7 @@ __device__ __forceinline__ void initial_row(const InstDesc* I, const IslandDesc*
 // S lanes (lane k): generation 0 (mode 1) draws it; a cellular cell gets the
 // child of its neighbourhood's two best from candidate stream `sub`; a pseudo
 // slot gets its pair's complementary child.
+template <bool SMALL>
 __device__ __forceinline__ CellMeta make_child(const InstDesc* I, const IslandDesc* L, int slot, uint32_t sub,
                                                int gen, int cur, int mode, uint16_t* A, int g, int k, int S,
                                                bool active)
@@ -1163,7 +1172,7 @@ __device__ __forceinline__ CellMeta make_child(const InstDesc* I, const IslandDe
         mj = pl.mj;
     }
     const uint16_t* gp = L->genes[cur];
-    ox_group_rows(A, n_pad, gp + (size_t)p1 * n_pad, gp + (size_t)p2 * n_pad, o, g, k, S, active);
+    ox_group_rows<SMALL>(A, n_pad, gp + (size_t)p1 * n_pad, gp + (size_t)p2 * n_pad, o, g, k, S, active);
     swap_genes(A, mx && active && k == 0, mi, mj);
     return meta;
 }
@@ -1311,7 +1320,7 @@ __global__ void __launch_bounds__(512) k_generation(const InstDesc* __restrict__
 
     const bool screened = mode == 0 && L->kind == 0 && I->surr_k > 1 && gen > I->surr_warmup;
     const uint32_t sub = screened ? (uint32_t)I->surr_choice[L->cell_base + slot] : 0u;
-    const CellMeta meta = make_child(I, L, slot, sub, gen, cur, mode, A, g, k, S, active);
+    const CellMeta meta = make_child<false>(I, L, slot, sub, gen, cur, mode, A, g, k, S, active);
 
     // waves past the work item's chromosomes have nothing to decode
     const int groups = wi.count - wave * G;
@@ -1375,6 +1384,158 @@ __global__ void __launch_bounds__(512) k_generation(const InstDesc* __restrict__
         for (int x = 0; x < (int)(blockDim.x >> 6); ++x) mn = s_wmin[x] < mn ? s_wmin[x] : mn;
         if (mn != ~0ull) atomicMin(L->genkey + (gen & 1), mn);
     }
+}
+
+// ---- a migration epoch of small islands in one launch ------------------------
+// `gens` generations of islands that are one workgroup's work each (rows of at
+// most kOxSmall vectors per lane, kKeyIdx).  Islands are independent between
+// migration epochs, so a workgroup needs nothing but its own barrier between
+// generations; it keeps its epoch's best row and record, which k_epoch_fold
+// folds afterwards.  A generation of the tiny workload (two islands of 64, 20
+// jobs) is a chain of latencies: 6.1 us in here, 9.4 us with a launch of its
+// own, of which the rest is the launch, the time table's way to LDS and the
+// records' fold; the workload's 100 generations 1264 -> 826 us.  Longer rows
+// would put the crossover's larger register tiers inside the loop (256
+// registers and spills), and there a launch is a small part of a generation.
+template <int MMAX, typename PT>
+__global__ void __launch_bounds__(512) k_epoch(const InstDesc* __restrict__ insts, const IslandDesc* __restrict__ isls,
+                                               const WorkItem* __restrict__ work, Control* ctl, int gens)
+{
+    __shared__ int s_gen;
+    __shared__ unsigned long long s_wmin[8];
+    __shared__ int s_best[4];   // makespan, generation, slot; improved in this generation
+    if (threadIdx.x == 0) {
+        int* cnt = ctl->counts + blockIdx.x;
+        const int t = *cnt;
+        *cnt = t + gens;
+        s_gen = ctl->base + 1 + t;
+        s_best[0] = 0x7FFFFFFF;
+    }
+    const WorkItem wi = work[blockIdx.x];
+    const InstDesc* I = insts + wi.inst;
+    const IslandDesc* L = isls + wi.island;
+    const int n = I->n, S = I->S, n_pad = I->n_pad, G = I->G, kind = L->kind;
+    PT* pT = reinterpret_cast<PT*>(ffs_smem);
+    stage_pt<PT>(pT, I->pT, S, n_pad);
+    __syncthreads();
+    const int gen0 = s_gen;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int stride = group_stride(n, n_pad, S);
+    uint16_t* gbase = reinterpret_cast<uint16_t*>(ffs_smem + pt_lds_bytes<PT>(S, n_pad)) + (size_t)wave * G * stride;
+    const int g = lane / S, k = lane - g * S;
+    const int local = wave * G + g;
+    const bool active = (g < G) && (local < wi.count);
+    uint16_t* A = gbase + (size_t)(active ? g : 0) * stride;
+    if (active)
+        for (int t = n + k; t < n_pad; t += S) A[t] = 0;   // the row's padding
+    const int slot = wi.slot0 + (active ? local : 0);
+    const int groups = wi.count - wave * G;
+    const PipeLane<PT> pl = pipe_lane<PT>(gbase, stride, pT, n_pad, lane, g, k, S, G, groups);
+    const int src = active ? (g * S + S - 1) : lane;
+#pragma clang loop unroll(disable)
+    for (int gen = gen0; gen < gen0 + gens; ++gen) {
+        const int cur = (gen + 1) & 1, nxt = gen & 1;
+        make_child<true>(I, L, slot, 0u, gen, cur, 0, A, g, k, S, active);
+        uint32_t cm = 0u, cmx = 0u;
+        if (groups > 0) cm = decode_pipe<MMAX, kKeyIdx, PT>(pl, I->mach, S, n, n_pad, I->jb, cmx);
+        const int cmg = __shfl((int)cm, src, 64);
+        unsigned long long wkey = ~0ull;
+        if (active) {
+            uint16_t* dstrow = L->genes[nxt] + (size_t)slot * n_pad;
+            int mk_new = cmg;
+            bool rep = true;
+            if (kind == 0) {
+                const int mk_old = as_global(L->mk[cur])[slot];
+                rep = cmg < mk_old;
+                mk_new = rep ? cmg : mk_old;
+            }
+            if (rep) row_l2g(dstrow, A, n_pad, k, S);
+            else row_g2g(dstrow, L->genes[cur] + (size_t)slot * n_pad, n_pad, k, S);
+            if (k == 0) {
+                L->mk[nxt][slot] = mk_new;
+                wkey = ((unsigned long long)(unsigned)mk_new << 32) | (unsigned)slot;
+            }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const unsigned long long o = __shfl_xor(wkey, off, 64);
+            wkey = o < wkey ? o : wkey;
+        }
+        if (lane == 0) s_wmin[wave] = wkey;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            unsigned long long mn = ~0ull;
+            for (int x = 0; x < (int)(blockDim.x >> 6); ++x) mn = s_wmin[x] < mn ? s_wmin[x] : mn;
+            const int mk = (int)(mn >> 32);
+            s_best[3] = mk < s_best[0] ? 1 : 0;
+            if (s_best[3]) {
+                s_best[0] = mk;
+                s_best[1] = gen;
+                s_best[2] = (int)(mn & 0xFFFFFFFFu);
+            }
+        }
+        // the generation's rows, makespans and best: visible to the whole
+        // workgroup from here on
+        __syncthreads();
+        if (s_best[3]) {
+            const auto* s4 = as_global(reinterpret_cast<const u32x4*>(L->genes[nxt] + (size_t)s_best[2] * n_pad));
+            auto* d4 = as_global(reinterpret_cast<u32x4*>(L->ep_perm));
+            for (int v = threadIdx.x; v < (n_pad >> 3); v += blockDim.x) d4[v] = s4[v];
+        }
+    }
+    if (threadIdx.x == 0)
+        for (int q = 0; q < 3; ++q) L->ep_rec[q] = s_best[q];
+}
+
+// Folds an epoch's island records (k_epoch) into the best-ever records (one
+// workgroup): per instance the least (makespan, generation, island, slot) of
+// the epoch, which is the record that folding generation by generation ends
+// with, if its makespan is strictly lower than the record's.
+// One workgroup; the migration's first launch carries it (k_mig_sort), and
+// k_epoch_fold where nothing migrates.
+__device__ __forceinline__ void epoch_fold(const InstDesc* __restrict__ insts, const IslandDesc* __restrict__ isls,
+                                           Control* ctl, int n_inst, int n_work)
+{
+    __shared__ int s_isl;
+    for (int ii = 0; ii < n_inst; ++ii) {
+        const InstDesc* J = insts + ii;
+        if (threadIdx.x == 0) {
+            int b = -1, mk = J->best_rec[0], gen = 0;
+            for (int x = 0; x < J->n_islands; ++x) {
+                const int* r = isls[J->island0 + x].ep_rec;
+                if (r[0] < mk || (b >= 0 && r[0] == mk && r[1] < gen)) {
+                    mk = r[0];
+                    gen = r[1];
+                    b = x;
+                }
+            }
+            if (b >= 0) {
+                J->best_rec[0] = mk;
+                J->best_rec[1] = gen;
+                J->best_rec[2] = b;
+                J->best_rec[3] = isls[J->island0 + b].ep_rec[2];
+            }
+            s_isl = b;
+        }
+        __syncthreads();
+        if (s_isl >= 0) {
+            const uint4* s4 = reinterpret_cast<const uint4*>(isls[J->island0 + s_isl].ep_perm);
+            uint4* d4 = reinterpret_cast<uint4*>(J->best_perm);
+            for (int v = threadIdx.x; v < (J->n_pad >> 3); v += blockDim.x) d4[v] = s4[v];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        ctl->counts[n_work] = ctl->counts[0];   // the launch count of k_generation's folding workgroup
+        ctl->best_gen[0] = completed_gen(ctl);
+    }
+}
+
+static __global__ void __launch_bounds__(256) k_epoch_fold(const InstDesc* __restrict__ insts,
+                                                           const IslandDesc* __restrict__ isls, Control* ctl,
+                                                           int n_inst, int n_work)
+{
+    epoch_fold(insts, isls, ctl, n_inst, n_work);
 }
 
 // ---- decode of caller-supplied permutations -------------------------------
@@ -1637,6 +1798,12 @@ static __global__ void __launch_bounds__(256) k_mig_ring(const InstDesc* __restr
 // that order, give every item its place; a pass is three block barriers, and
 // an island whose makespans span 2^b values needs ceil(b / 2) passes.
 // Padding items (i >= size) carry all ones and stay at the end.
+// Islands of at most kRankMax slots need no passes: every item's place is the
+// count of the items before it, taken by the threads / size lanes that share
+// the item.  For 64 slots the sort took 11.6 us by passes and takes 4.6 us
+// by counting.  At 256 a lane compares 64 items, which is still below one pass;
+// the compares grow with the square of the size.
+constexpr int kRankMax = 256;
 constexpr int kSortThreads = 1024;
 constexpr int kSortWaves = kSortThreads / 64;
 constexpr int kSortRMax = 16;
@@ -1650,9 +1817,14 @@ __host__ __device__ inline size_t sort_lds_bytes(int R)
 }
 
 static __global__ void __launch_bounds__(kSortThreads) k_mig_sort(const InstDesc* __restrict__ insts,
-                                                           const IslandDesc* __restrict__ isls,
-                                                           const Control* ctl, int force_inst, int only_inst)
+                                                           const IslandDesc* __restrict__ isls, Control* ctl,
+                                                           int force_inst, int only_inst, int fold_inst, int n_work)
 {
+    // after a launch of k_epoch: the last workgroup folds its records
+    if (fold_inst > 0 && blockIdx.x == gridDim.x - 1) {
+        epoch_fold(insts, isls, ctl, fold_inst, n_work);
+        return;
+    }
     const IslandDesc* L = isls + blockIdx.x;
     const InstDesc* I = insts + L->inst;
     const int gen = completed_gen(ctl);
@@ -1669,6 +1841,26 @@ static __global__ void __launch_bounds__(kSortThreads) k_mig_sort(const InstDesc
     uint32_t* zpre = zcnt + kSortEnt;                            // their exclusive prefix, same order
     uint32_t* misc = zpre + kSortEnt;                            // [0..15] wave minima, [16..31] maxima
     const int* mk = L->mk[gen & 1];
+    if (N <= kRankMax) {
+        int sh = 2;   // 2^sh lanes per item
+        while (sh < 6 && (N << (sh + 1)) <= kSortThreads) ++sh;
+        const int i = t >> sh;
+        if (t < N) dbuf[t] = (uint32_t)mk[t];
+        __syncthreads();
+        int rank = 0;
+        const uint32_t di = i < N ? dbuf[i] : 0u;
+        if (i < N)
+            for (int j = t & ((1 << sh) - 1); j < N; j += 1 << sh) {
+                const uint32_t dj = dbuf[j];
+                rank += (dj < di || (dj == di && j < i)) ? 1 : 0;
+            }
+        for (int o = 1; o < (1 << sh); o <<= 1) rank += __shfl_xor(rank, o, 64);
+        if (i < N && (t & ((1 << sh) - 1)) == 0) {
+            L->sorted[rank] = i;
+            if (rank == 0) L->sortbest[0] = (int)di;
+        }
+        return;
+    }
 
     uint32_t d[kSortRMax], sl[kSortRMax];
     uint32_t mn = 0xFFFFFFFFu, mx = 0u;

@@ -5,6 +5,7 @@
 namespace flowshop {
 
 void* pick_gen(int mmax, int ptb);            // k_generation, mmax 2, 3, 4, 5, 6, 8, 16
+void* pick_epoch(int mmax, int ptb);          // k_epoch, the same
 void* pick_cand(int mmax, int ptb);           // k_candidates, the same
 void* pick_eval(int mmax, int ptb);           // k_evaluate, the same
 void* pick_gen_lane(int mmax, int ptb);       // k_generation_lane, up to 8

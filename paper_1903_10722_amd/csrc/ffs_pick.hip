@@ -44,6 +44,12 @@ void* pick_eval_lane(int m, int ptb)
     FFS_UP_TO_8(k_evaluate_lane)
     return nullptr;
 }
+#elif FFS_PART == 5
+void* pick_epoch(int m, int ptb)
+{
+    FFS_UP_TO_8(k_epoch) FFS_PICK(16, k_epoch)
+    return nullptr;
+}
 #else
 void* pick_cand_features(int m, int ptb)
 {

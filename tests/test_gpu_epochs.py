@@ -1,0 +1,47 @@
+"""Epochs of small islands run as one launch each, against the oracle's
+trajectories and best-ever records (integers: equal): islands that fill one
+workgroup's tile and of a few slots, rows at the ends of the vector
+range, one and several stages per wave, both island kinds, intervals of one and
+of none, several instances, and eager generations between the epochs."""
+import pytest
+
+from gpu_util import assert_same_state, ensure_built, make_ctx, oracle_ga, say
+from paper_1903_10722_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+# jobs, stages, machines per stage, interval, waves per workgroup, islands
+CASES = [
+    (20, 3, 3, 5, None, [inputs.cellular(8, 8, 0.9, 0.5), inputs.pseudo(64, 0.8, 0.4)]),
+    (1, 1, 1, 1, None, [inputs.cellular(3, 3, 0.9, 0.5), inputs.pseudo(2, 0.8, 0.4)]),
+    (9, 2, 8, 3, 1, [inputs.cellular(5, 6, 0.9, 0.5), inputs.cellular(3, 4, 0.9, 0.5)]),
+    (72, 3, 2, 4, 8, [inputs.pseudo(160, 0.8, 0.4), inputs.cellular(4, 4, 0.9, 0.5)]),
+    (24, 1, 16, 3, None, [inputs.cellular(10, 10, 0.9, 0.5)]),
+    (300, 32, 2, 2, 8, [inputs.cellular(3, 5, 0.9, 0.5), inputs.pseudo(8, 0.8, 0.4)]),
+    (9, 2, 2, 2, None, [inputs.cellular(16, 16, 0.9, 0.5), inputs.pseudo(258, 0.8, 0.4)]),   # sorted by count, by passes
+    (20, 3, 3, 0, None, [inputs.cellular(8, 8, 0.9, 0.5)]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_epochs(case):
+    ensure_built()
+    n, S, mm, interval, wpb, isl = CASES[case]
+    ws = []
+    for i in range(2 if case in (0, 2) else 1):
+        m, p = inputs.make_instance(n, S, 1, mm, p_hi=20, seed=n + S + i)
+        ws.append(dict(m=m, p=p, islands=isl, interval=interval, theta=1.0, topology=0))
+    say(f"[epochs] n={n} S={S} interval={interval} waves={wpb}")
+    ctx = make_ctx(ws, waves_per_block=wpb, mapping=0)
+    gas = [oracle_ga(w, inst=i) for i, w in enumerate(ws)]
+    step = interval or 16
+    for g in (step, 2 * step + 1, step - 1, 1, step, 3 * step):
+        ctx.evolve(g)
+        for i, ga in enumerate(gas):
+            ga.evolve(g)
+            what = f"instance {i} generation {ctx.generation}"
+            b1, b2 = ctx.best(i), ga.best()
+            assert (b1["makespan"], b1["generation"]) == (b2["makespan"], b2["generation"]), what
+            assert b1["perm"].tolist() == b2["perm"].tolist(), what
+            assert_same_state(ctx, ga, i, len(isl), what)
+    ctx.close()
