@@ -13,7 +13,8 @@
 //     along the stage's order: job k on machine m finishes at
 //     max(free_m, ready_k) + p_k, and "wait for x, then run p" composes
 //     associatively: (A1, B1) then (A2, B2) is (max(A1, A2 - B1), B1 + B2)
-//     applied as x -> max(x, A) + B;
+//     applied as x -> max(x, A) + B (with at most two machines as the pair
+//     (completion from a free machine, B), see decode_two);
 //   - the next stage's order (first in, first out by completion, ties by
 //     this stage's order) merges the machines' lists, each already sorted by
 //     (completion, position) because a machine finishes its jobs in order:
@@ -119,7 +120,14 @@ __host__ __device__ inline TabOff tab_off(int J, int S, int MX, int Lp)
 
 // LDS bytes of the shared tables and of one wave's work area.
 __host__ __device__ inline int tables_bytes(int J, int S, int MX, int Lp) { return tab_off(J, S, MX, Lp).bytes; }
-__host__ __device__ inline int wave_bytes(int Lp, int Jp) { return Lp + Jp * 2 * 2 + Jp * 4 * 2 + Jp * 8; }
+// (MMX: the decode's machine bound.  With two machines only the lists are in
+// LDS: the keys, two sentinels, a cell for writes of idle positions and what
+// an idle lane's merge may read past the second sentinel.)
+constexpr int kListPad = 24;   // a multiple of 8, above 3 + the positions of a lane
+__host__ __device__ inline int wave_bytes(int Lp, int Jp, int MMX)
+{
+    return MMX == 2 ? Lp + (Jp + kListPad) * 8 : Lp + Jp * 2 * 2 + Jp * 4 * 2 + Jp * 8;
+}
 
 struct Smem {
     uint16_t* P;
@@ -239,10 +247,11 @@ __device__ __forceinline__ int top_pow2(int x)
 // the whole wave; -1 if a gene is out of range.  Work arrays in LDS:
 // ord/rdy (two buffers each, Jp entries) and keys (Jp entries).  A lane owns
 // K = ceil(J / 64) <= KMAX consecutive positions.
-template <int KMAX, int MMX>
+template <int KMAX>
 __device__ long long decode_wave(const TtDesc& d, const Smem& sm, const uint8_t* child, uint16_t* ordA,
                                  uint16_t* ordB, int* rdyA, int* rdyB, unsigned long long* keys, int lane)
 {
+    constexpr int MMX = kMaxM;
     const int J = d.J, S = d.S, MX = d.MX;
     const int K = (J + 63) >> 6;
     const int t0 = lane * K;
@@ -308,16 +317,9 @@ __device__ long long decode_wave(const TtDesc& d, const Smem& sm, const uint8_t*
                 scan_maxplus(Ai, Bi);
                 A[m] = from_lane_below(Ai, kNeg);   // exclusive prefix
                 B[m] = from_lane_below(Bi, 0);
-                if (MMX == 2 && m == 1) {
-                    // two machines: the lanes below hold min(t0, J) positions,
-                    // those not on machine 0 are on machine 1
-                    tot[1] = J - tot[0];
-                    cnt[1] = (t0 < J ? t0 : J) - cnt[0];
-                } else {
-                    const int ci = scan_add(cnt[m]);
-                    tot[m] = __builtin_amdgcn_readlane(ci, 63);
-                    cnt[m] = ci - cnt[m];   // exclusive: entries of machine m before this lane
-                }
+                const int ci = scan_add(cnt[m]);
+                tot[m] = __builtin_amdgcn_readlane(ci, 63);
+                cnt[m] = ci - cnt[m];   // exclusive: entries of machine m before this lane
                 run_off += tot[m];
             }
         }
@@ -349,92 +351,53 @@ __device__ long long decode_wave(const TtDesc& d, const Smem& sm, const uint8_t*
         }
         if (!more) break;
         wave_sync();
-        if constexpr (MMX == 2) {
-            // two lists (the second empty when M_s = 1): a merge path.  Lane
-            // l writes merged positions [l K, l K + K): a binary search on
-            // that diagonal finds how many of them come from the first list,
-            // then the lane merges its K outputs in order.
-            const unsigned long long* X = keys + off[0];
-            const unsigned long long* Y = keys + off[1];
-            const int nx = tot[0], ny = tot[1];
-            const int dg = t0 < J ? t0 : J;
-            int lo = dg - ny > 0 ? dg - ny : 0;
-            int hi = dg < nx ? dg : nx;
-            // the first list's share of positions [0, dg): the least i in
-            // [lo, hi] with X[i] > Y[dg - 1 - i] (i = hi if none); hi - lo is
-            // at most min(nx, ny), and every round halves the candidates
-            const int span = nx < ny ? nx : ny;
-            for (int step = span > 0 ? top_pow2(span) : 0; step > 0; step >>= 1) {
-                if (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    const bool x_first = X[mid] < Y[dg - 1 - mid];
-                    lo = x_first ? mid + 1 : lo;
-                    hi = x_first ? hi : mid;
-                }
-            }
-            int i = lo, jy = dg - lo;
+        // rank in the next stage's order: own index plus, in every other
+        // machine's list, the number of entries below the key -- a
+        // power-of-two search with a fixed step sequence, run for all of
+        // the lane's positions in lockstep so that their LDS reads overlap
+        unsigned long long key[KMAX];
+#pragma unroll
+        for (int u = 0; u < KMAX; ++u)
+            key[u] = order_key(mloc[u] >= 0 ? cloc[u] : 0, t0 + u, mloc[u] >= 0 ? jloc[u] : 0);
+        const int top = top_pow2(J) << 1;
+        for (int oi = 1; oi < Ms; ++oi) {
+            // position u searches machine (m_u + oi) mod Ms: each other machine once
+            int lb[KMAX], n[KMAX], pos[KMAX];
 #pragma unroll
             for (int u = 0; u < KMAX; ++u) {
-                if (u < K && dg + u < J) {
-                    const unsigned long long x = i < nx ? X[i] : ~0ull;
-                    const unsigned long long y = jy < ny ? Y[jy] : ~0ull;
-                    const bool tx = x < y;
-                    const unsigned long long kk = tx ? x : y;
-                    i += tx ? 1 : 0;
-                    jy += tx ? 0 : 1;
-                    ordB[dg + u] = (uint16_t)(kk & 0xFFFFull);
-                    rdyB[dg + u] = (int)(kk >> 32);
-                }
-            }
-        } else {
-            // rank in the next stage's order: own index plus, in every other
-            // machine's list, the number of entries below the key -- a
-            // power-of-two search with a fixed step sequence, run for all of
-            // the lane's positions in lockstep so that their LDS reads overlap
-            unsigned long long key[KMAX];
+                int om = (mloc[u] >= 0 ? mloc[u] : 0) + oi;
+                om = om >= Ms ? om - Ms : om;
+                int ob = 0, on = 0;
 #pragma unroll
-            for (int u = 0; u < KMAX; ++u)
-                key[u] = order_key(mloc[u] >= 0 ? cloc[u] : 0, t0 + u, mloc[u] >= 0 ? jloc[u] : 0);
-            const int top = top_pow2(J) << 1;
-            for (int oi = 1; oi < Ms; ++oi) {
-                // position u searches machine (m_u + oi) mod Ms: each other machine once
-                int lb[KMAX], n[KMAX], pos[KMAX];
+                for (int mm = 0; mm < MMX; ++mm)
+                    if (mm == om) {
+                        ob = off[mm];
+                        on = tot[mm];
+                    }
+                lb[u] = ob - 1;
+                n[u] = (mloc[u] >= 0) ? on : 0;
+                pos[u] = 0;
+            }
+            for (int step = top >> 1; step > 0; step >>= 1) {
 #pragma unroll
                 for (int u = 0; u < KMAX; ++u) {
-                    int om = (mloc[u] >= 0 ? mloc[u] : 0) + oi;
-                    om = om >= Ms ? om - Ms : om;
-                    int ob = 0, on = 0;
-#pragma unroll
-                    for (int mm = 0; mm < MMX; ++mm)
-                        if (mm == om) {
-                            ob = off[mm];
-                            on = tot[mm];
-                        }
-                    lb[u] = ob - 1;
-                    n[u] = (mloc[u] >= 0) ? on : 0;
-                    pos[u] = 0;
-                }
-                for (int step = top >> 1; step > 0; step >>= 1) {
-#pragma unroll
-                    for (int u = 0; u < KMAX; ++u) {
-                        if (u < K) {   // uniform
-                            const int at = pos[u] + step;
-                            // entries lst[0..at) all below the key: advance
-                            if (at <= n[u] && keys[lb[u] + at] < key[u]) pos[u] = at;
-                        }
+                    if (u < K) {   // uniform
+                        const int at = pos[u] + step;
+                        // entries lst[0..at) all below the key: advance
+                        if (at <= n[u] && keys[lb[u] + at] < key[u]) pos[u] = at;
                     }
                 }
-#pragma unroll
-                for (int u = 0; u < KMAX; ++u)
-                    if (mloc[u] >= 0) own[u] += pos[u];
             }
 #pragma unroll
             for (int u = 0; u < KMAX; ++u)
-                if (mloc[u] >= 0) {
-                    ordB[own[u]] = (uint16_t)jloc[u];
-                    rdyB[own[u]] = cloc[u];
-                }
+                if (mloc[u] >= 0) own[u] += pos[u];
         }
+#pragma unroll
+        for (int u = 0; u < KMAX; ++u)
+            if (mloc[u] >= 0) {
+                ordB[own[u]] = (uint16_t)jloc[u];
+                rdyB[own[u]] = cloc[u];
+            }
         wave_sync();
         uint16_t* to = ordA;
         ordA = ordB;
@@ -463,6 +426,167 @@ __device__ long long decode_wave(const TtDesc& d, const Smem& sm, const uint8_t*
     return anybad ? -1ll : d.WT * tard + (long long)cmax;
 }
 
+// One step of the two-machine decode's scan over (C, B): C is the completion
+// of a lane's positions on a machine that is free from 0, B their processing
+// times, and (C_l, B_l) then (C_r, B_r) is (max(C_l + B_r, C_r), B_l + B_r).
+// Every time is at least 0 and C at least B, so that (0, 0) is the identity,
+// which the shift reads for a lane without a source: both additions are one
+// instruction with the shift in it.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void complete_step(int& C, int& B)
+{
+    const int c2 = B + __builtin_amdgcn_update_dpp(0, C, CTRL, ROWS, 0xF, false);
+    C = C > c2 ? C : c2;
+    B = add_step<CTRL, ROWS>(B);
+}
+
+__device__ __forceinline__ void scan_complete(int& C, int& B)
+{
+    complete_step<0x111, 0xF>(C, B);
+    complete_step<0x112, 0xF>(C, B);
+    complete_step<0x114, 0xF>(C, B);
+    complete_step<0x118, 0xF>(C, B);
+    complete_step<0x142, 0xA>(C, B);
+    complete_step<0x143, 0xC>(C, B);
+}
+
+// The same objective where every stage has at most two machines.  A lane owns
+// K consecutive positions, exactly: positions past the last job run with
+// ready and processing time 0 on machine 0, which changes no lane's scan, so
+// that nothing branches.  Bound by the vector unit: a position costs two
+// passes (max, add and the machine's selects) around the scan, one list entry
+// and one merge step.  The merge leaves the lane's share of the next stage's
+// order, which is the same positions, in registers; only the two lists are in
+// LDS (X = machine 0's, a sentinel, Y = machine 1's, a sentinel).
+// One generation of fifty runs of 512 individuals (300 jobs, 4 stages) takes
+// 100 us, against 160 us with the next order and ready times in LDS, the
+// (A, B) pairs of the general decode and vector Philox blocks: 1780 vector
+// operations a wave, which keep the vector units busy for 73 % of it.  More
+// waves per workgroup (32 instead of 24 resident on a CU) took 104 us, a
+// raised wave priority while the child is built 107 us.
+template <int K>
+__device__ __forceinline__ long long decode_two(const TtDesc& d, const Smem& sm, const uint8_t* child,
+                                                unsigned long long* keys, int lane)
+{
+    static_assert(K + 3 <= kListPad, "an idle lane's merge stays inside the list area");
+    const int J = d.J, S = d.S, two = d.MX >> 1;   // MX is 1 or 2
+    const int t0 = lane * K;
+    const int tb = t0 < J ? t0 : J;   // positions of the lanes below
+    const int nv = J - t0;            // position u is a job's if u < nv
+    int j[K], r[K], c[K];
+    int over = -1;   // at least 0: a gene is out of range
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        const int jj = sm.ord0[t0 + u < J ? t0 + u : 0];
+        j[u] = u < nv ? jj : 0;
+        const int rr = sm.R[j[u]];
+        r[u] = u < nv ? rr : 0;
+    }
+    for (int s = 0; s < S; ++s) {
+        const int Ms = sm.M[s];
+        int p[K], m[K];
+        int C0 = 0, C1 = 0, B1 = 0, Ball = 0, n1 = 0;
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const int at = j[u] * S + s;
+            const int g = child[at];
+            over = g - Ms > over ? g - Ms : over;
+            m[u] = (u < nv && g < Ms) ? g : 0;
+            const int pp = sm.P[(at << two) + m[u]];
+            p[u] = u < nv ? pp : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const bool one = m[u] != 0;
+            const int f = one ? C1 : C0;
+            const int x = (f > r[u] ? f : r[u]) + p[u];
+            C0 = one ? C0 : x;
+            C1 = one ? x : C1;
+            Ball += p[u];
+            B1 += one ? p[u] : 0;
+            n1 += m[u];
+        }
+        int B0 = Ball - B1;
+        scan_complete(C0, B0);
+        scan_complete(C1, B1);
+        const int ni = scan_add(n1);
+        const int ny = __builtin_amdgcn_readlane(ni, 63), nx = J - ny;
+        // when each machine is free for the lane's first position
+        int F0 = from_lane_below(C0, 0), F1 = from_lane_below(C1, 0);
+        const int e1 = ni - n1;
+        int i0 = tb - e1, i1 = nx + 1 + e1;
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const bool one = m[u] != 0;
+            const int f = one ? F1 : F0;
+            c[u] = (f > r[u] ? f : r[u]) + p[u];
+            F0 = one ? F0 : c[u];
+            F1 = one ? c[u] : F1;
+        }
+        if (s + 1 == S) break;
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            int pos = m[u] != 0 ? i1 : i0;
+            pos = u < nv ? pos : J + 2;
+            i1 += m[u];
+            i0 += 1 - m[u];
+            keys[pos] = order_key(c[u], t0 + u, j[u]);
+        }
+        unsigned long long* X = keys;
+        unsigned long long* Y = keys + nx + 1;
+        if (lane == 0) {
+            X[nx] = ~0ull;
+            Y[ny] = ~0ull;
+        }
+        wave_sync();
+        // merge path: the lane's positions [tb, tb + K) of the merged order.
+        // The first list's share of [0, tb) is the least i in [lo, hi] with
+        // X[i] > Y[tb - 1 - i] (hi if none); hi - lo is at most min(nx, ny),
+        // and every round halves the candidates.
+        int lo = tb - ny > 0 ? tb - ny : 0;
+        int hi = tb < nx ? tb : nx;
+        const int span = nx < ny ? nx : ny;
+        for (int step = span > 0 ? top_pow2(span) : 0; step > 0; step >>= 1) {
+            if (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                const bool x_first = X[mid] < Y[tb - 1 - mid];
+                lo = x_first ? mid + 1 : lo;
+                hi = x_first ? hi : mid;
+            }
+        }
+        const unsigned long long* px = X + lo;
+        const unsigned long long* py = Y + (tb - lo);
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const unsigned long long x = *px, y = *py;
+            const bool tx = x < y;
+            const unsigned long long kk = tx ? x : y;
+            px += tx ? 1 : 0;
+            py += tx ? 0 : 1;
+            j[u] = u < nv ? (int)(kk & 0xFFFFull) : 0;
+            r[u] = u < nv ? (int)(kk >> 32) : 0;
+        }
+        wave_sync();
+    }
+    long long tard = 0;
+    int cmax = 0;
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        const int late = c[u] - sm.D[j[u]];
+        if (u < nv) {
+            if (late > 0) tard += late;
+            cmax = c[u] > cmax ? c[u] : cmax;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        tard += __shfl_xor(tard, o, 64);
+        const int c2 = __shfl_xor(cmax, o, 64);
+        cmax = c2 > cmax ? c2 : cmax;
+    }
+    return __any(over >= 0) ? -1ll : d.WT * tard + (long long)cmax;
+}
+
 struct WaveMem {
     uint8_t* child;
     uint16_t *ordA, *ordB;
@@ -470,11 +594,18 @@ struct WaveMem {
     unsigned long long* keys;
 };
 
+template <int MMX>
 __device__ __forceinline__ WaveMem wave_mem(unsigned char* base, int Lp, int Jp)
 {
     WaveMem w;
     w.child = base;
     base += Lp;
+    if (MMX == 2) {
+        w.ordA = w.ordB = nullptr;
+        w.rdyA = w.rdyB = nullptr;
+        w.keys = reinterpret_cast<unsigned long long*>(base);
+        return w;
+    }
     w.ordA = reinterpret_cast<uint16_t*>(base);
     base += Jp * 2;
     w.ordB = reinterpret_cast<uint16_t*>(base);
@@ -486,6 +617,37 @@ __device__ __forceinline__ WaveMem wave_mem(unsigned char* base, int Lp, int Jp)
     w.keys = reinterpret_cast<unsigned long long*>(base);
     return w;
 }
+
+template <int KMAX, int MMX>
+__device__ __forceinline__ long long decode_child(const TtDesc& d, const Smem& sm, const WaveMem& w, int lane)
+{
+    if constexpr (MMX == 2)
+        return decode_two<KMAX>(d, sm, w.child, w.keys, lane);
+    else
+        return decode_wave<KMAX>(d, sm, w.child, w.ordA, w.ordB, w.rdyA, w.rdyB, w.keys, lane);
+}
+
+// The wave of a thread, as a value the compiler knows to be uniform: all that
+// follows from it (the individual, its parents, its draws' Philox blocks) is
+// scalar work beside the vector unit's.
+__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(1))) T* global_of(const T* p)
+{
+    return (const __attribute__((address_space(1))) T*)p;   // global, not flat, reads
+}
+
+// Bits of the four bytes at i0 .. i0 + 3 that lie in [a, e]
+__device__ __forceinline__ uint32_t span_mask(int i0, int a, int e)
+{
+    const int lo = a - i0 < 0 ? 0 : (a - i0 > 4 ? 4 : a - i0);
+    const int hi = e + 1 - i0 < 0 ? 0 : (e + 1 - i0 > 4 ? 4 : e + 1 - i0);
+    return (uint32_t)((1ull << (8 * hi)) - 1) & ~(uint32_t)((1ull << (8 * lo)) - 1);
+}
+
+// Words of a gene string that a lane has in flight at once.
+constexpr int kRowU = 4;
 
 extern __shared__ __align__(16) unsigned char tt_smem[];
 
@@ -506,11 +668,12 @@ __global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mo
     const Smem sm = smem_tables(tt_smem, d);
     stage_tables(d, tt_smem);
     __syncthreads();
-    const int wpb = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const long long wg = (long long)blockIdx.x * wpb + wave;
-    const int per_run = (mode <= 1) ? d.N : count;
-    if (wg >= (long long)d.runs * per_run) return;
-    const int run = (int)(wg / per_run), q0 = (int)(wg - (long long)run * per_run);
+    const int wpb = blockDim.x >> 6, wave = wave_index(), lane = threadIdx.x & 63;
+    const uint32_t wg = blockIdx.x * (uint32_t)wpb + (uint32_t)wave;   // at most kMaxRuns kMaxIsl kMaxIslSize + 3
+    const uint32_t per_run = (uint32_t)((mode <= 1) ? d.N : count);
+    if (wg >= (uint32_t)d.runs * per_run) return;
+    const int run = __builtin_amdgcn_readfirstlane((int)(wg / per_run));   // the division is vector work
+    const int q0 = (int)(wg - (uint32_t)run * per_run);
     int isl = 0, slot = 0;
     if (mode <= 1) {
 #pragma unroll
@@ -538,9 +701,12 @@ __global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mo
             }
         }
     }
+    isl = __builtin_amdgcn_readfirstlane(isl);
+    slot = __builtin_amdgcn_readfirstlane(slot);
     const TtIsland I = island_at(d, isl);
     const int L = d.L, Lp = d.Lp, S = d.S;
-    const WaveMem w = wave_mem(tt_smem + tables_bytes(d.J, S, d.MX, d.Lp) + wave * wave_bytes(Lp, d.Jp), Lp, d.Jp);
+    const WaveMem w = wave_mem<MMX>(tt_smem + tables_bytes(d.J, S, d.MX, d.Lp) + wave * wave_bytes(Lp, d.Jp, MMX), Lp,
+                                    d.Jp);
     const int cur = (gen + 1) & 1, nxt = gen & 1;
     const long long rowbase = (long long)run * d.N + I.off;   // individual index of slot 0
     uint8_t* child = w.child;
@@ -575,7 +741,7 @@ __global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mo
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
             buf[q] = (mode == 2 && q > 0 && nd[q] < diag) ? nxt : cur;
-            v[q] = d.obj[buf[q]][rowbase + nb[q]];
+            v[q] = global_of(d.obj[buf[q]])[rowbase + nb[q]];
         }
         // the two best by (objective, neighbourhood order)
         int b = 0, p1 = nb[0], b1 = buf[0];
@@ -605,22 +771,25 @@ __global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mo
         const int a = u < v2 ? u : v2, e = u < v2 ? v2 : u;
         const uint8_t* P1 = d.genes[b1] + (rowbase + p1) * Lp;
         const uint8_t* P2 = d.genes[b2] + (rowbase + p2) * Lp;
-        for (int i0 = lane * 16; i0 < Lp; i0 += 64 * 16) {
-            const uint4 x1 = *reinterpret_cast<const uint4*>(P1 + i0);
-            const uint4 x2 = *reinterpret_cast<const uint4*>(P2 + i0);
-            uint32_t o[4];
+        const auto* w1 = global_of(reinterpret_cast<const uint32_t*>(P1));
+        const auto* w2 = global_of(reinterpret_cast<const uint32_t*>(P2));
+        uint32_t* cwords = reinterpret_cast<uint32_t*>(child);
+        const int nw = Lp >> 2;
+        const int ca = cx ? a : 0, ce2 = cx ? e : Lp;   // taken from P1; all of it without a crossover
+        for (int v0 = lane; v0 < nw; v0 += 64 * kRowU) {
+            uint32_t x1[kRowU], x2[kRowU];
 #pragma unroll
-            for (int wd = 0; wd < 4; ++wd) {
-                // byte mask of the positions taken from P1
-                uint32_t mask = 0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = i0 + wd * 4 + q;
-                    if (!cx || (i >= a && i <= e)) mask |= 0xFFu << (8 * q);
-                }
-                o[wd] = (word_of(x1, wd) & mask) | (word_of(x2, wd) & ~mask);
+            for (int q = 0; q < kRowU; ++q) {
+                const int v = v0 + 64 * q < nw ? v0 + 64 * q : nw - 1;   // past the end: the last word again
+                x1[q] = w1[v];
+                x2[q] = w2[v];
             }
-            *reinterpret_cast<uint4*>(child + i0) = make_uint4(o[0], o[1], o[2], o[3]);
+#pragma unroll
+            for (int q = 0; q < kRowU; ++q) {
+                const int v = v0 + 64 * q < nw ? v0 + 64 * q : nw - 1;
+                const uint32_t mask = span_mask(4 * v, ca, ce2);
+                cwords[v] = (x1[q] & mask) | (x2[q] & ~mask);
+            }
         }
         wave_sync();
         if (lane == 0 && (unsigned long long)draw32(bk, 3) < I.tm) {
@@ -629,7 +798,7 @@ __global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mo
             if (ms >= 2) child[i] = (uint8_t)((child[i] + 1 + (int)below(draw32(bk, 5), (uint32_t)(ms - 1))) % ms);
         }
     } else {
-        const long long* ob = d.obj[cur] + rowbase;
+        const auto* ob = global_of(d.obj[cur] + rowbase);
         const int q = slot >> 1;
         const bool odd = slot & 1;
         const int xs = (ob[2 * q] <= ob[2 * q + 1]) ? 2 * q : 2 * q + 1;
@@ -644,29 +813,28 @@ __global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mo
         const uint32_t di = odd ? draw32(b0, 7) : draw32(b0, 4);
         const uint32_t dr = odd ? draw32(b1, 0) : draw32(b0, 5);
         const uint8_t* X = d.genes[cur] + (rowbase + xs) * Lp;
-        for (int i0 = lane * 16; i0 < Lp; i0 += 64 * 16) {
-            const uint4 x1 = *reinterpret_cast<const uint4*>(X + i0);
-            const uint4 c1 = *reinterpret_cast<const uint4*>(sm.cb + i0);
-            uint32_t o[4];
+        // even child: X on [a, b], complement elsewhere (X if no crossover);
+        // odd child: the opposite
+        const auto* xw = global_of(reinterpret_cast<const uint32_t*>(X));
+        const uint32_t* bw = reinterpret_cast<const uint32_t*>(sm.cb);
+        uint32_t* cwords = reinterpret_cast<uint32_t*>(child);
+        const int nw = Lp >> 2;
+        const int ca = cx ? a : 0, ce2 = cx ? e : Lp;
+        const uint32_t flip = odd ? ~0u : 0u;
+        for (int v0 = lane; v0 < nw; v0 += 64 * kRowU) {
+            uint32_t x[kRowU];
 #pragma unroll
-            for (int wd = 0; wd < 4; ++wd) {
-                const uint32_t xw = word_of(x1, wd);
+            for (int q = 0; q < kRowU; ++q) x[q] = xw[v0 + 64 * q < nw ? v0 + 64 * q : nw - 1];
+#pragma unroll
+            for (int q = 0; q < kRowU; ++q) {
+                const int v = v0 + 64 * q < nw ? v0 + 64 * q : nw - 1;   // past the end: the last word again
                 // complement of four genes at once: every byte of the base is
                 // >= the gene below it, so the subtraction borrows only in the
                 // padding past the string (higher bytes)
-                const uint32_t yw = word_of(c1, wd) - xw;
-                uint32_t mask = 0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = i0 + wd * 4 + q;
-                    // even child: X on [a, b], complement elsewhere (X if no
-                    // crossover); odd child: the opposite
-                    const bool takex = cx ? ((i >= a && i <= e) != odd) : !odd;
-                    if (takex) mask |= 0xFFu << (8 * q);
-                }
-                o[wd] = (xw & mask) | (yw & ~mask);
+                const uint32_t y = bw[v] - x[q];
+                const uint32_t mask = span_mask(4 * v, ca, ce2) ^ flip;
+                cwords[v] = (x[q] & mask) | (y & ~mask);
             }
-            *reinterpret_cast<uint4*>(child + i0) = make_uint4(o[0], o[1], o[2], o[3]);
         }
         wave_sync();
         if (lane == 0 && (unsigned long long)dm < I.tm) {
@@ -676,20 +844,24 @@ __global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mo
         }
     }
     wave_sync();
-    const long long o = decode_wave<KMAX, MMX>(d, sm, child, w.ordA, w.ordB, w.rdyA, w.rdyB, w.keys, lane);
+    const long long o = decode_child<KMAX, MMX>(d, sm, w, lane);
     // replacement (cellular: only if strictly better) and write-out
     uint8_t* dst = d.genes[nxt] + (rowbase + slot) * Lp;
     long long onew = o;
-    const uint8_t* srow = child;
+    bool keep = false;
     if (mode != 1 && I.kind == 0) {
-        const long long oold = d.obj[cur][rowbase + slot];
-        if (!(o < oold)) {
-            onew = oold;
-            srow = d.genes[cur] + (rowbase + slot) * Lp;
-        }
+        const long long oold = global_of(d.obj[cur])[rowbase + slot];
+        keep = !(o < oold);
+        onew = keep ? oold : o;
     }
-    for (int i0 = lane * 16; i0 < Lp; i0 += 64 * 16)
-        *reinterpret_cast<uint4*>(dst + i0) = *reinterpret_cast<const uint4*>(srow + i0);
+    auto* d4 = (__attribute__((address_space(1))) tab_vec4*)dst;
+    if (keep) {
+        const auto* s4 = global_of(reinterpret_cast<const tab_vec4*>(d.genes[cur] + (rowbase + slot) * Lp));
+        for (int v = lane; v < (Lp >> 4); v += 64) d4[v] = s4[v];
+    } else {
+        const tab_vec4* s4 = reinterpret_cast<const tab_vec4*>(child);
+        for (int v = lane; v < (Lp >> 4); v += 64) d4[v] = s4[v];
+    }
     if (lane == 0) {
         d.obj[nxt][rowbase + slot] = onew;
         if (o < 0) atomicOr(d.err, 1);
@@ -833,14 +1005,15 @@ __global__ void __launch_bounds__(256) k_tt_evaluate(TtDesc d, const uint8_t* ge
     const Smem sm = smem_tables(tt_smem, d);
     stage_tables(d, tt_smem);
     __syncthreads();
-    const int wpb = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wpb = blockDim.x >> 6, wave = wave_index(), lane = threadIdx.x & 63;
     const long long row = (long long)blockIdx.x * wpb + wave;
     if (row >= count) return;
-    const WaveMem w = wave_mem(tt_smem + tables_bytes(d.J, d.S, d.MX, d.Lp) + wave * wave_bytes(d.Lp, d.Jp), d.Lp, d.Jp);
+    const WaveMem w = wave_mem<MMX>(
+        tt_smem + tables_bytes(d.J, d.S, d.MX, d.Lp) + wave * wave_bytes(d.Lp, d.Jp, MMX), d.Lp, d.Jp);
     const uint8_t* src = genes + row * d.L;
     for (int i = lane; i < d.L; i += 64) w.child[i] = src[i];
     wave_sync();
-    const long long o = decode_wave<KMAX, MMX>(d, sm, w.child, w.ordA, w.ordB, w.rdyA, w.rdyB, w.keys, lane);
+    const long long o = decode_child<KMAX, MMX>(d, sm, w, lane);
     if (lane == 0) out[row] = o;
 }
 
@@ -876,9 +1049,9 @@ struct ffs_tt_ctx {
     TtDesc desc{};
     int sweep = 0;   // cellular update: 0 synchronous, 1 line sweep
     int wpb = 4;
-    int kmax = 16;   // positions per lane bound of the decode (8 when J <= 512)
-    int mmx = 4;     // machines per stage bound of the decode (2 when every M_s <= 2)
     size_t lds_gen = 0;
+    const void* kgen = nullptr;    // generation and evaluate kernels of the instance (pick_kernels)
+    const void* keval = nullptr;
     // timing
     bool timing = false;
     std::vector<hipEvent_t> ev;
@@ -948,23 +1121,44 @@ int check_ready(ffs_tt_ctx* c)
     return FFS_OK;
 }
 
+// The kernels of the instance.  With at most two machines per stage a lane's
+// positions K = ceil(J / 64) are compiled in (one more, three or four more for
+// K of 7, 9-12 and 13-16: idle lanes, no other cost); with more machines the
+// bound is 8 or 16 and K runs.
+void pick_kernels(ffs_tt_ctx* c)
+{
+#define TT_PICK(N, MMX)                                                       \
+    {                                                                         \
+        c->kgen = reinterpret_cast<const void*>(&k_tt_generation<N, MMX>);    \
+        c->keval = reinterpret_cast<const void*>(&k_tt_evaluate<N, MMX>);     \
+    }
+    const int K = (c->J + 63) / 64;
+    if (c->MX > 2) {
+        if (K <= 8) TT_PICK(8, kMaxM) else TT_PICK(16, kMaxM)
+        return;
+    }
+    switch (K) {
+    case 1: TT_PICK(1, 2) break;
+    case 2: TT_PICK(2, 2) break;
+    case 3: TT_PICK(3, 2) break;
+    case 4: TT_PICK(4, 2) break;
+    case 5: TT_PICK(5, 2) break;
+    case 6: TT_PICK(6, 2) break;
+    case 7:
+    case 8: TT_PICK(8, 2) break;
+    default:
+        if (K <= 12) TT_PICK(12, 2) else TT_PICK(16, 2)
+    }
+#undef TT_PICK
+}
+
 int launch_one(ffs_tt_ctx* c, int gen, int mode, int sel, int diag, int count, long long waves)
 {
     if (waves <= 0) return FFS_OK;
     const unsigned blocks = (unsigned)((waves + c->wpb - 1) / c->wpb);
     const TtDesc& d = c->desc;
-    if (c->kmax == 8 && c->mmx == 2)
-        hipLaunchKernelGGL((k_tt_generation<8, 2>), dim3(blocks), dim3(64 * c->wpb), c->lds_gen, c->stream, d, gen,
-                           mode, sel, diag, count);
-    else if (c->kmax == 8)
-        hipLaunchKernelGGL((k_tt_generation<8, 4>), dim3(blocks), dim3(64 * c->wpb), c->lds_gen, c->stream, d, gen,
-                           mode, sel, diag, count);
-    else if (c->mmx == 2)
-        hipLaunchKernelGGL((k_tt_generation<16, 2>), dim3(blocks), dim3(64 * c->wpb), c->lds_gen, c->stream, d, gen,
-                           mode, sel, diag, count);
-    else
-        hipLaunchKernelGGL((k_tt_generation<16, 4>), dim3(blocks), dim3(64 * c->wpb), c->lds_gen, c->stream, d, gen,
-                           mode, sel, diag, count);
+    void* args[] = {(void*)&d, (void*)&gen, (void*)&mode, (void*)&sel, (void*)&diag, (void*)&count};
+    TT_HIP(c, hipLaunchKernel(c->kgen, dim3(blocks), dim3(64 * c->wpb), args, c->lds_gen, c->stream));
     TT_HIP(c, hipGetLastError());
     return FFS_OK;
 }
@@ -1177,25 +1371,16 @@ int ffs_tt_bind_workspace(ffs_tt_ctx* c, void* ptr, size_t bytes)
     const Layout l = layout_of(c);
     if (bytes < l.total) return fail(c, FFS_ENOMEM, "workspace %zu < %zu", bytes, l.total);
     // LDS: tables + waves; up to 4 waves per workgroup, fewer if that does not fit
-    const size_t tb = (size_t)tables_bytes(c->J, c->S, c->MX, c->Lp), wb = (size_t)wave_bytes(c->Lp, c->Jp);
+    const size_t tb = (size_t)tables_bytes(c->J, c->S, c->MX, c->Lp);
+    const size_t wb = (size_t)wave_bytes(c->Lp, c->Jp, c->MX <= 2 ? 2 : kMaxM);
     int wpb = 4;
     while (wpb > 1 && tb + wpb * wb > 160 * 1024) --wpb;
     if (tb + wpb * wb > 160 * 1024) return fail(c, FFS_EUNSUPPORTED, "instance tables need %zu bytes of LDS", tb + wb);
     c->wpb = wpb;
     c->lds_gen = tb + wpb * wb;
-    c->kmax = (c->J <= 512) ? 8 : 16;
-    c->mmx = (c->MX <= 2) ? 2 : 4;
-    const void* kg[4] = {reinterpret_cast<const void*>(&k_tt_generation<8, 2>),
-                         reinterpret_cast<const void*>(&k_tt_generation<8, 4>),
-                         reinterpret_cast<const void*>(&k_tt_generation<16, 2>),
-                         reinterpret_cast<const void*>(&k_tt_generation<16, 4>)};
-    const void* ke[4] = {reinterpret_cast<const void*>(&k_tt_evaluate<8, 2>),
-                         reinterpret_cast<const void*>(&k_tt_evaluate<8, 4>),
-                         reinterpret_cast<const void*>(&k_tt_evaluate<16, 2>),
-                         reinterpret_cast<const void*>(&k_tt_evaluate<16, 4>)};
-    const int kv = (c->kmax == 8 ? 0 : 2) + (c->mmx == 2 ? 0 : 1);
-    TT_HIP(c, hipFuncSetAttribute(kg[kv], hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->lds_gen));
-    TT_HIP(c, hipFuncSetAttribute(ke[kv], hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->lds_gen));
+    pick_kernels(c);
+    TT_HIP(c, hipFuncSetAttribute(c->kgen, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->lds_gen));
+    TT_HIP(c, hipFuncSetAttribute(c->keval, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->lds_gen));
     TT_HIP(c, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tt_migrate),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, 2 * kMaxIslSize * 8));
     c->ws = reinterpret_cast<char*>(ptr);
@@ -1427,18 +1612,8 @@ int ffs_tt_evaluate(ffs_tt_ctx* c, const void* genes, int32_t count, void* out)
     const unsigned blocks = (unsigned)((count + c->wpb - 1) / c->wpb);
     const uint8_t* g = reinterpret_cast<const uint8_t*>(genes);
     long long* o = reinterpret_cast<long long*>(out);
-    if (c->kmax == 8 && c->mmx == 2)
-        hipLaunchKernelGGL((k_tt_evaluate<8, 2>), dim3(blocks), dim3(64 * c->wpb), c->lds_gen, c->stream, c->desc, g,
-                           count, o);
-    else if (c->kmax == 8)
-        hipLaunchKernelGGL((k_tt_evaluate<8, 4>), dim3(blocks), dim3(64 * c->wpb), c->lds_gen, c->stream, c->desc, g,
-                           count, o);
-    else if (c->mmx == 2)
-        hipLaunchKernelGGL((k_tt_evaluate<16, 2>), dim3(blocks), dim3(64 * c->wpb), c->lds_gen, c->stream, c->desc, g,
-                           count, o);
-    else
-        hipLaunchKernelGGL((k_tt_evaluate<16, 4>), dim3(blocks), dim3(64 * c->wpb), c->lds_gen, c->stream, c->desc, g,
-                           count, o);
+    void* args[] = {(void*)&c->desc, (void*)&g, (void*)&count, (void*)&o};
+    TT_HIP(c, hipLaunchKernel(c->keval, dim3(blocks), dim3(64 * c->wpb), args, c->lds_gen, c->stream));
     TT_HIP(c, hipGetLastError());
     return FFS_OK;
 }
