@@ -651,6 +651,51 @@ constexpr int kRowU = 4;
 
 extern __shared__ __align__(16) unsigned char tt_smem[];
 
+// Best-ever record of every run after generation `gen`, one wave per run:
+// the minimum (objective, island, slot) of the generation replaces the
+// record if its objective is strictly lower; the generation's keys are
+// reset.  Every lane reads the keys and the record and takes the same
+// decision; the wave copies the row, and lane 0 writes the keys and the
+// record after the reads they depend on.
+// Between two generations of one call the second one's launch carries it
+// (its first workgroups; the rows and keys of the other parity are only read
+// there), which saves a launch of 4.6 us; otherwise it is k_tt_fold.
+__device__ __forceinline__ void fold_run(const TtDesc& d, int gen, int run, int lane)
+{
+    if (run >= d.runs) return;
+    const int par = gen & 1;
+    unsigned long long* gk = d.genkey + (long long)run * d.n_isl * 2 + par;   // island i at gk[2 i]
+    long long bo = 0;
+    int bi = -1, bs = 0;
+    for (int i = 0; i < d.n_isl; ++i) {
+        const unsigned long long v = gk[2 * i];
+        const long long oi = (long long)(v >> 13);
+        // every island posts a key each generation; an unset key is skipped
+        if (v != ~0ull && (bi < 0 || oi < bo)) {
+            bo = oi;
+            bi = i;
+            bs = (int)(v & 8191u);
+        }
+    }
+    long long* rec = d.best + (long long)run * 4;
+    const bool better = bi >= 0 && (rec[2] < 0 || bo < rec[0]);
+    if (better) {
+        const uint4* s4 =
+            reinterpret_cast<const uint4*>(d.genes[par] + ((long long)run * d.N + island_at(d, bi).off + bs) * d.Lp);
+        uint4* d4 = reinterpret_cast<uint4*>(d.best_genes + (long long)run * d.Lp);
+        for (int v = lane; v < d.Lp / 16; v += 64) d4[v] = s4[v];
+    }
+    if (lane == 0) {
+        for (int i = 0; i < d.n_isl; ++i) gk[2 * i] = ~0ull;
+        if (better) {
+            rec[0] = bo;
+            rec[1] = gen;
+            rec[2] = bi;
+            rec[3] = bs;
+        }
+    }
+}
+
 // Generation `gen` of every run:
 //   mode 1: generation 0 (random assignments; a pseudo pair = X and its
 //           complement), every individual;
@@ -663,13 +708,18 @@ extern __shared__ __align__(16) unsigned char tt_smem[];
 //           the diagonals run in order, one launch each;
 //   mode 3: the individuals of the pseudo islands only (`count` per run).
 template <int KMAX, int MMX>
-__global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mode, int sel, int diag, int count)
+__global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mode, int sel, int diag, int count,
+                                                       int fold_blocks)
 {
+    if ((int)blockIdx.x < fold_blocks) {
+        fold_run(d, gen - 1, (int)blockIdx.x * (int)(blockDim.x >> 6) + wave_index(), (int)threadIdx.x & 63);
+        return;
+    }
     const Smem sm = smem_tables(tt_smem, d);
     stage_tables(d, tt_smem);
     __syncthreads();
     const int wpb = blockDim.x >> 6, wave = wave_index(), lane = threadIdx.x & 63;
-    const uint32_t wg = blockIdx.x * (uint32_t)wpb + (uint32_t)wave;   // at most kMaxRuns kMaxIsl kMaxIslSize + 3
+    const uint32_t wg = (blockIdx.x - (uint32_t)fold_blocks) * (uint32_t)wpb + (uint32_t)wave;   // at most kMaxRuns kMaxIsl kMaxIslSize + 3
     const uint32_t per_run = (uint32_t)((mode <= 1) ? d.N : count);
     if (wg >= (uint32_t)d.runs * per_run) return;
     const int run = __builtin_amdgcn_readfirstlane((int)(wg / per_run));   // the division is vector work
@@ -870,48 +920,7 @@ __global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mo
     }
 }
 
-// Best-ever record of every run after generation `gen`, one wave per run:
-// the minimum (objective, island, slot) of the generation replaces the
-// record if its objective is strictly lower; the generation's keys are
-// reset.  Every lane reads the keys and the record and takes the same
-// decision; the wave copies the row, and lane 0 writes the keys and the
-// record after the reads they depend on.
-__global__ void __launch_bounds__(64) k_tt_fold(TtDesc d, int gen)
-{
-    const int run = blockIdx.x, lane = threadIdx.x;
-    if (run >= d.runs) return;
-    const int par = gen & 1;
-    unsigned long long* gk = d.genkey + (long long)run * d.n_isl * 2 + par;   // island i at gk[2 i]
-    long long bo = 0;
-    int bi = -1, bs = 0;
-    for (int i = 0; i < d.n_isl; ++i) {
-        const unsigned long long v = gk[2 * i];
-        const long long oi = (long long)(v >> 13);
-        // every island posts a key each generation; an unset key is skipped
-        if (v != ~0ull && (bi < 0 || oi < bo)) {
-            bo = oi;
-            bi = i;
-            bs = (int)(v & 8191u);
-        }
-    }
-    long long* rec = d.best + (long long)run * 4;
-    const bool better = bi >= 0 && (rec[2] < 0 || bo < rec[0]);
-    if (better) {
-        const uint4* s4 =
-            reinterpret_cast<const uint4*>(d.genes[par] + ((long long)run * d.N + island_at(d, bi).off + bs) * d.Lp);
-        uint4* d4 = reinterpret_cast<uint4*>(d.best_genes + (long long)run * d.Lp);
-        for (int v = lane; v < d.Lp / 16; v += 64) d4[v] = s4[v];
-    }
-    if (lane == 0) {
-        for (int i = 0; i < d.n_isl; ++i) gk[2 * i] = ~0ull;
-        if (better) {
-            rec[0] = bo;
-            rec[1] = gen;
-            rec[2] = bi;
-            rec[3] = bs;
-        }
-    }
-}
+__global__ void __launch_bounds__(64) k_tt_fold(TtDesc d, int gen) { fold_run(d, gen, (int)blockIdx.x, (int)threadIdx.x); }
 
 // Slots of one island by (objective, slot) ascending into keys[0..size):
 // bitonic sort of objective << 13 | slot over a power-of-two span.
@@ -1152,12 +1161,13 @@ void pick_kernels(ffs_tt_ctx* c)
 #undef TT_PICK
 }
 
-int launch_one(ffs_tt_ctx* c, int gen, int mode, int sel, int diag, int count, long long waves)
+int launch_one(ffs_tt_ctx* c, int gen, int mode, int sel, int diag, int count, long long waves, bool fold = false)
 {
     if (waves <= 0) return FFS_OK;
-    const unsigned blocks = (unsigned)((waves + c->wpb - 1) / c->wpb);
+    const int nf = fold ? (c->runs + c->wpb - 1) / c->wpb : 0;
+    const unsigned blocks = (unsigned)((waves + c->wpb - 1) / c->wpb) + (unsigned)nf;
     const TtDesc& d = c->desc;
-    void* args[] = {(void*)&d, (void*)&gen, (void*)&mode, (void*)&sel, (void*)&diag, (void*)&count};
+    void* args[] = {(void*)&d, (void*)&gen, (void*)&mode, (void*)&sel, (void*)&diag, (void*)&count, (void*)&nf};
     TT_HIP(c, hipLaunchKernel(c->kgen, dim3(blocks), dim3(64 * c->wpb), args, c->lds_gen, c->stream));
     TT_HIP(c, hipGetLastError());
     return FFS_OK;
@@ -1165,8 +1175,9 @@ int launch_one(ffs_tt_ctx* c, int gen, int mode, int sel, int diag, int count, l
 
 // One generation (mode 1: generation 0; mode 0: a step, synchronous or as a
 // line sweep: the pseudo islands in one launch, then every cellular island
-// one anti-diagonal per launch), then the best-ever fold.
-int launch_gen(ffs_tt_ctx* c, int gen, int mode)
+// one anti-diagonal per launch), then the best-ever fold (fold_after).
+// fold_before: a synchronous step's launch folds the generation before.
+int launch_gen(ffs_tt_ctx* c, int gen, int mode, bool fold_before = false, bool fold_after = true)
 {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c->timing) {
@@ -1182,7 +1193,7 @@ int launch_gen(ffs_tt_ctx* c, int gen, int mode)
     int rc = FFS_OK;
     const TtDesc& d = c->desc;
     if (mode == 1 || !c->sweep) {
-        rc = launch_one(c, gen, mode, 0, 0, 0, (long long)c->runs * d.N);
+        rc = launch_one(c, gen, mode, 0, 0, 0, (long long)c->runs * d.N, fold_before);
     } else {
         int np = 0;
         for (int i = 0; i < d.n_isl; ++i)
@@ -1199,7 +1210,7 @@ int launch_gen(ffs_tt_ctx* c, int gen, int mode)
     }
     if (rc != FFS_OK) return rc;
     if (c->timing) TT_HIP(c, hipEventRecord(e1, c->stream));
-    hipLaunchKernelGGL(k_tt_fold, dim3((unsigned)c->runs), dim3(64), 0, c->stream, c->desc, gen);
+    if (fold_after) hipLaunchKernelGGL(k_tt_fold, dim3((unsigned)c->runs), dim3(64), 0, c->stream, c->desc, gen);
     TT_HIP(c, hipGetLastError());
     return FFS_OK;
 }
@@ -1464,11 +1475,15 @@ int ffs_tt_evolve(ffs_tt_ctx* c, int32_t generations)
     int rc = check_ready(c);
     if (rc != FFS_OK) return rc;
     if (generations < 0) return fail(c, FFS_EINVAL, "generations < 0");
+    bool open = false;   // the generation before is left for this one's launch to fold
     for (int it = 0; it < generations; ++it) {
         const int g = c->gen + 1;
-        if ((rc = launch_gen(c, g, 0)) != FFS_OK) return rc;
+        const bool migrate = c->interval > 0 && g % c->interval == 0;
+        const bool now = migrate || c->sweep || it + 1 == generations;
+        if ((rc = launch_gen(c, g, 0, open, now)) != FFS_OK) return rc;
+        open = !now;
         c->gen = g;
-        if (c->interval > 0 && g % c->interval == 0)
+        if (migrate)
             if ((rc = launch_migrate(c, g)) != FFS_OK) return rc;
     }
     return FFS_OK;
