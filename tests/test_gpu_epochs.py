@@ -45,3 +45,22 @@ def test_epochs(case):
             assert b1["perm"].tolist() == b2["perm"].tolist(), what
             assert_same_state(ctx, ga, i, len(isl), what)
     ctx.close()
+
+
+def test_epochs_between_tiles():
+    """Tiles that make an island one workgroup's work and several's, in turn,
+    and an eager start inside an epoch after each change."""
+    ensure_built()
+    w = inputs.workload("tiny", seed=9)
+    ctx, ga = make_ctx([w], waves_per_block=8), oracle_ga(w)
+    for waves, g in ((8, 20), (1, 10), (8, 13), (1, 7), (4, 25), (8, 15), (8, 20)):
+        ctx.set_waves_per_block(waves)
+        ctx.evolve(g)
+        ga.evolve(g)
+        say(f"[epochs] waves={waves} generation {ctx.generation}")
+        b1, b2 = ctx.best(0), ga.best()
+        assert (b1["makespan"], b1["generation"]) == (b2["makespan"], b2["generation"]), ctx.generation
+        assert b1["perm"].tolist() == b2["perm"].tolist()
+        assert ctx.migration_counters(0) == ga.counters()
+        assert_same_state(ctx, ga, 0, 2, f"generation {ctx.generation}")
+    ctx.close()
