@@ -18,7 +18,9 @@ CASES = [
     (72, 3, 2, 4, 8, [inputs.pseudo(160, 0.8, 0.4), inputs.cellular(4, 4, 0.9, 0.5)]),
     (24, 1, 16, 3, None, [inputs.cellular(10, 10, 0.9, 0.5)]),
     (300, 32, 2, 2, 8, [inputs.cellular(3, 5, 0.9, 0.5), inputs.pseudo(8, 0.8, 0.4)]),
-    (9, 2, 2, 2, None, [inputs.cellular(16, 16, 0.9, 0.5), inputs.pseudo(258, 0.8, 0.4)]),   # sorted by count, by passes
+    (9, 2, 2, 2, None, [inputs.cellular(16, 16, 0.9, 0.5), inputs.pseudo(258, 0.8, 0.4)]),   # counted on one workgroup, over several
+    (9, 2, 2, 1, None, [inputs.cellular(37, 28, 0.9, 0.5), inputs.pseudo(4096, 0.8, 0.4)]),   # counted, over workgroups
+    (9, 2, 2, 1, None, [inputs.cellular(4, 4, 0.9, 0.5), inputs.pseudo(4098, 0.8, 0.4)]),     # one too large for that
     (20, 3, 3, 0, None, [inputs.cellular(8, 8, 0.9, 0.5)]),
 ]
 
