@@ -221,7 +221,7 @@ __device__ __forceinline__ uint32_t lane_stage_window(uint32_t (&r)[kLaneD], lan
 {
     const uint32_t field = ((1u << kLaneIndexBits) - 1u) << jb;
     uint32_t key[M];
-    if (full) {   // every stage dispatches in every slot
+    if (full) {   // every stage dispatches in every slot, and none ends
 #pragma unroll
         for (int q = 0; q < M; ++q) {
             key[q] = st[q * 64];
@@ -331,6 +331,9 @@ __device__ __forceinline__ uint32_t lane_decode_keys(Src& src, lds_ptr<PT> pT, i
     int off_last = 0;
     for (int k = 0; k + 1 < S; ++k) off_last += mach[k];
     const int nwin = (off_last + n + kLaneD - 1) / kLaneD;
+    // a full window ends no stage: of one stage alone the last window, whose
+    // list gives the makespan, may hold nothing but dispatches
+    const int nfull = off_last > 0 ? n : n - 1;
     uint32_t cmax = 0u;
     uint32_t gnext[kLaneD];
     src.load(0, gnext);
@@ -341,7 +344,7 @@ __device__ __forceinline__ uint32_t lane_decode_keys(Src& src, lds_ptr<PT> pT, i
         for (int i = 0; i < kLaneD; ++i) r[i] = gnext[i];
         if (lo + kLaneD < n) src.load(lo + kLaneD, gnext);
         src.mark(lo, r);
-        const bool full = lo > off_last && lo + kLaneD <= n;
+        const bool full = lo > off_last && lo + kLaneD <= nfull;
         int off = 0;
         for (int k = 0; k < S; ++k) {
             const int M = mach[k];
