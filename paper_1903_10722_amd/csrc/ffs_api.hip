@@ -189,6 +189,13 @@ bool lane_eval_auto(int count, int n, int S, int msum, int mmax, int G, int resi
     return P * resident > (count >= 524288 ? 17.0 : 20.0) * L;
 }
 
+// Chromosomes per wave of the per-stage mapping: one lane per stage, the
+// wave's LDS rows within 32 KB.
+int wave_groups(int n, int n_pad, int S)
+{
+    return std::min(kWave / S, std::max(1, 32768 / (2 * group_stride(n, n_pad, S))));
+}
+
 int round_mmax(int m)
 {
     for (int v : kMmaxList)
@@ -348,9 +355,13 @@ void layout(ffs_ctx* c)
         const int want = I.tile_map >= 0 ? I.tile_map : (c->lane ? 1 : 0);
         I.map_eff = (want == 1 && I.lane_ok && c->mm <= 8 && I.cfg.surrogate_k <= 1) ? 1 : 0;
         I.wpb_eff = I.tile_wpb > 0 ? I.tile_wpb : c->wpb;
+        const size_t table = align16((size_t)I.S * ((size_t)I.n_pad * c->ptb + 4));
+        // where even one wave's rows do not fit beside the table (long rows of
+        // 17 to 26 stages with two-byte processing times), fewer per wave
+        I.G = wave_groups(I.n, I.n_pad, I.S);
+        while (I.G > 1 && table + wave_lds_bytes(I.G, I.n, I.n_pad, I.S) > (size_t)c->max_lds) --I.G;
         for (;;) {
-            I.lds = align16((size_t)I.S * ((size_t)I.n_pad * c->ptb + 4)) +
-                    (size_t)I.wpb_eff * (I.map_eff ? I.lane_wlds : wave_lds_bytes(I.G, I.n, I.n_pad, I.S));
+            I.lds = table + (size_t)I.wpb_eff * (I.map_eff ? I.lane_wlds : wave_lds_bytes(I.G, I.n, I.n_pad, I.S));
             if (I.lds <= (size_t)c->max_lds || I.wpb_eff == 1) break;
             I.wpb_eff >>= 1;
         }
@@ -1308,8 +1319,9 @@ int ffs_create_instance(ffs_ctx* c, int32_t n, int32_t S, const int32_t* machine
                     I.E, (1ll << (32 - jb)) - 1);
     I.n_pad = (n + 31) & ~31;
     // chromosomes per wave: one lane per stage, capped so that a wave's LDS
-    // rows stay within 32 KB
-    I.G = std::min(kWave / S, std::max(1, 32768 / (2 * group_stride(n, I.n_pad, S))));
+    // rows stay within 32 KB (layout lowers it where a workgroup of one wave
+    // would not fit in LDS)
+    I.G = wave_groups(n, I.n_pad, S);
     for (int x = 0; x < n_islands; ++x) {
         const ffs_island_spec& sp = islands[x];
         HostIsland L;
@@ -2266,7 +2278,7 @@ int ffs_evaluate_noalloc(void* hip_stream, int32_t n, int32_t S, const int32_t* 
     const DecodeKeys dk = decode_keys(n, S, machines, p, jb, mm);
     d.lkey = dk.lkey;
     d.pkey = dk.pkey;
-    d.G = std::min(kWave / S, std::max(1, 32768 / (2 * group_stride(n, n_pad, S))));
+    d.G = wave_groups(n, n_pad, S);
     d.msum = msum;
     for (int k = 0; k < S; ++k) d.mach[k] = machines[k];
     d.lane_wlds_eval = (int)lane_eval_wave_lds(jb, msum);
