@@ -234,6 +234,7 @@ struct ffs_ctx {
     char* pin = nullptr;         // pinned host block: the error word, then staging for small results
     int gen = 0;
     int flushed = -1;            // generation that flush_best folded last (see there)
+    bool replayed = false;       // the caller captured launches of this context into a graph of their own
     std::string err;
     // layout
     size_t off_ctl = 0, off_insts = 0, off_isls = 0, off_work = 0, off_pairs = 0, off_counts = 0, total = 0;
@@ -748,6 +749,21 @@ int launch_epoch(ffs_ctx* c, int gens, bool fold)
     return FFS_OK;
 }
 
+// Whether the caller is capturing the context's stream.  The graph may be
+// replayed later, without a call that the context sees, so from then on its
+// host-side generation says nothing about what has run on the device.
+bool user_capture(ffs_ctx* c)
+{
+    if (!c->stream) return false;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (st != hipStreamCaptureStatusNone) c->replayed = true;
+    return st != hipStreamCaptureStatusNone;
+}
+
 // Folds the completed generation into the best-ever records if the next
 // generation launch has not done so yet.
 int flush_best(ffs_ctx* c, bool capturing = false)
@@ -755,8 +771,9 @@ int flush_best(ffs_ctx* c, bool capturing = false)
     const InstDesc* di = reinterpret_cast<const InstDesc*>(c->ws + c->off_insts);
     const IslandDesc* dl = reinterpret_cast<const IslandDesc*>(c->ws + c->off_isls);
     Control* ctl = reinterpret_cast<Control*>(c->ws + c->off_ctl);
+    if (!capturing) capturing = user_capture(c);
     // nothing launched since the last flush: the records are up to date
-    if (!capturing && c->flushed == c->gen) return FFS_OK;
+    if (!capturing && !c->replayed && c->flushed == c->gen) return FFS_OK;
     hipLaunchKernelGGL(k_best_flush, dim3(1), dim3(256), 0, c->stream, di, dl, ctl, (int)c->inst.size(), c->ngroup);
     HIP_TRY(c, hipGetLastError());
     if (!capturing) c->flushed = c->gen;
@@ -1784,6 +1801,7 @@ int ffs_evolve(ffs_ctx* c, int32_t generations)
     int rc = check_bound(c);
     if (rc) return rc;
     if (generations < 0) return fail(c, FFS_EINVAL, "generations must be >= 0");
+    (void)user_capture(c);
     const int I = common_interval(c);
     // whole epochs replay one captured graph: the kernels read the generation
     // (and the pre-screen its Adam step) from device memory, so the same
