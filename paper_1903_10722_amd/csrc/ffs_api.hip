@@ -743,8 +743,8 @@ int launch_epoch(ffs_ctx* c, int gens, bool fold)
     HIP_TRY(c, hipLaunchKernel(c->epoch_kern, dim3((unsigned)c->n_work), dim3(64 * c->cls_wpb[0]), args, c->cls_lds[0],
                                c->stream));
     if (fold)
-        hipLaunchKernelGGL(k_epoch_fold, dim3(1), dim3(256), 0, c->stream, di, dl, ctl, (int)c->inst.size(),
-                           c->n_work);
+        hipLaunchKernelGGL(k_epoch_fold, dim3(((unsigned)c->inst.size() + 3) / 4), dim3(256), 0, c->stream, di, dl, ctl,
+                           (int)c->inst.size(), c->n_work);
     HIP_TRY(c, hipGetLastError());
     return FFS_OK;
 }
@@ -803,8 +803,9 @@ int launch_migration(ffs_ctx* c, int force_inst, bool capturing = false)
     const int items = (c->max_size + kRankItems - 1) / kRankItems;
     const bool split = c->max_size > kRankMax && c->max_size <= kRankSplitMax && (long long)c->n_isl * items <= 512;
     const int sy = split ? items : 1;
-    hipLaunchKernelGGL(k_mig_sort, dim3(c->n_isl + (fold ? 1 : 0), sy), dim3(kSortThreads), c->lds_sort, c->stream, di, dl,
-                       ctl, force_inst, -1, fold ? (int)c->inst.size() : 0, c->n_work);
+    const int n_fold = fold ? (int)c->inst.size() : 0;
+    hipLaunchKernelGGL(k_mig_sort, dim3(c->n_isl + (n_fold + kSortWaves - 1) / kSortWaves, sy), dim3(kSortThreads),
+                       c->lds_sort, c->stream, di, dl, ctl, force_inst, -1, n_fold, c->n_work);
     if (c->n_pairs > 0)
         hipLaunchKernelGGL(k_mig_adapt, dim3(c->n_pairs, chunks), dim3(256), 0, c->stream, di, dl, dp, ctl,
                            force_inst);
