@@ -1122,10 +1122,9 @@ int launch_eval(ffs_ctx* c, int inst, const int32_t* perms, int count, int32_t* 
     Control* ctl = reinterpret_cast<Control*>(c->ws + c->off_ctl);
     void* kl = I.lane_ok ? pick_eval_lane(c->mm, c->ptb) : nullptr;
     const size_t table = align16((size_t)I.S * ((size_t)I.n_pad * c->ptb + 4));
-    int resident = 0;
-    const int lw = kl ? lane_eval_waves(table, I.lane_wlds_eval, (size_t)c->max_lds, resident) : 0;
-    const bool lane = lw > 0 && (c->mapping == 1 || (c->mapping < 0 && lane_eval_auto(count, I.n, I.S, I.msum, c->mm, I.G, resident)));
-    const int wpb = lane ? lw : c->wpb;
+    const LaneEval le = kl ? lane_eval_split(table, I.lane_wlds_eval, (size_t)c->max_lds) : LaneEval{};
+    const bool lane = le.waves > 0 && (c->mapping == 1 || (c->mapping < 0 && lane_eval_auto(count, I.n, I.S, I.msum, c->mm, I.G, le.resident)));
+    const int wpb = lane ? le.waves : c->wpb;
     const int per_block = wpb * (lane ? kWave : I.G);
     const int blocks = (count + per_block - 1) / per_block;
     const size_t lds = table + (size_t)wpb * (lane ? I.lane_wlds_eval : (size_t)I.G * eval_stride(I.n_pad) * 2);
@@ -2307,10 +2306,9 @@ int ffs_evaluate_noalloc(void* hip_stream, int32_t n, int32_t S, const int32_t* 
         return FFS_EDEVICE;
     const size_t table = align16((size_t)S * ((size_t)n_pad * ptb + 4));
     void* kl = (msum <= kLaneMaxMsum && mmax <= 8) ? pick_eval_lane(mm, ptb) : nullptr;
-    int resident = 0;
-    const int lw = kl ? lane_eval_waves(table, (size_t)d.lane_wlds_eval, (size_t)max_lds, resident) : 0;
-    const bool lane = lw > 0 && lane_eval_auto(count, n, S, msum, mm, d.G, resident);
-    const int wpb = lane ? lw : 4;
+    const LaneEval le = kl ? lane_eval_split(table, (size_t)d.lane_wlds_eval, (size_t)max_lds) : LaneEval{};
+    const bool lane = le.waves > 0 && lane_eval_auto(count, n, S, msum, mm, d.G, le.resident);
+    const int wpb = lane ? le.waves : 4;
     void* kern = lane ? kl : pick_eval(mm, ptb);
     if (!kern) return FFS_EUNSUPPORTED;
     const size_t lds = table + (size_t)wpb * (lane ? (size_t)d.lane_wlds_eval : (size_t)d.G * eval_stride(n_pad) * 2);

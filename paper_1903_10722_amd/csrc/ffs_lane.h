@@ -32,6 +32,7 @@
 // there, then writes back the parent's row of every cellular cell whose
 // child is not strictly better.
 #pragma once
+#include <algorithm>
 #include <type_traits>
 
 #include "ffs_kernels.h"
@@ -58,23 +59,39 @@ __host__ __device__ inline size_t lane_eval_wave_lds(int jb, int msum)
     return (size_t)64 * (msum + lane_seen_words(jb)) * 4;
 }
 
-// Waves per workgroup that leave the most waves resident in a CU's LDS
-// (`table` bytes per workgroup, `wave` bytes per wave; at most eight per
-// workgroup and sixteen per CU, the register limit) and their number; 0: not
-// even one fits.
-inline int lane_eval_waves(size_t table, size_t wave, size_t max_lds, int& resident)
+// How the lane decode of caller-supplied rows fills a CU: waves per workgroup
+// (0: not even one fits), waves resident, and the time of a round of them.
+struct LaneEval {
+    int waves, resident;
+    double round;
+};
+
+// Time of a SIMD's share of a round, in units that one wave alone takes 5 of.
+inline double lane_round(int share) { return std::max(5.0, 3.0 * share); }
+
+// The split with the most waves per unit of time (`table` bytes of LDS per
+// workgroup, `wave` bytes per wave; at most sixteen waves per CU, the register
+// limit).  A workgroup's waves are dealt to the four SIMDs from the first one
+// on, so that several workgroups of three, five, six or seven leave the SIMDs
+// unequal shares, and the fullest one's counts.  131072 rows of 500 x 10: two
+// workgroups of five waves 430 us, of four 348; of 500 x 20 with 30 machines:
+// two of six 834, two of four 546; a million rows of 20 x 10 with 41 machines:
+// three of five 321, seven of two 249; 262144 rows of 20 x 20 with 80
+// machines: one of seven 266, three of two 272.  Of equals the nearest to four:
+// eight are up to 5 % slower for short rows, one up to 14 % for long ones,
+// whose table every workgroup copies.
+inline LaneEval lane_eval_split(size_t table, size_t wave, size_t max_lds)
 {
-    int best = 0, most = 0;
-    for (int w = 1; w <= 8; ++w) {
+    static const int order[] = {4, 2, 1, 8, 7, 6, 5, 3};
+    LaneEval best{0, 0, 0.0};
+    for (int w : order) {
         const size_t lds = table + w * wave;
-        if (lds > max_lds) break;
-        const int per_cu = (int)(max_lds / lds) * w, res = per_cu < 16 ? per_cu : 16;
-        if (res >= most) {
-            most = res;
-            best = w;
-        }
+        if (lds > max_lds) continue;
+        const int groups = std::max(1, std::min((int)(max_lds / lds), 16 / w));
+        const int share = (w & (w - 1)) ? groups * ((w + 3) / 4) : (groups * w + 3) / 4;
+        const LaneEval e{w, groups * w, lane_round(share)};
+        if (best.waves == 0 || e.resident * best.round > best.resident * e.round) best = e;
     }
-    resident = most;
     return best;
 }
 
