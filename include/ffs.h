@@ -150,7 +150,7 @@ int ffs_set_waves_per_block(ffs_ctx *ctx, int32_t waves);
  *      lane per stage, jobs handed from stage to stage between lanes;
  *   1: per lane -- one lane decodes one chromosome through all stages;
  *  -1: automatic (the default): per lane when every instance fits it and the
- *      context holds at least 131072 individuals (ffs_evaluate: from 98304
+ *      context holds at least 131072 individuals (ffs_evaluate: from 65536
  *      rows on, where the shape's cost per row and the LDS of its waves make
  *      it the faster one), per stage otherwise.
  * The per-lane mapping needs at most 8 machines per stage, a sum of machine

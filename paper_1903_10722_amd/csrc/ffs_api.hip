@@ -171,22 +171,30 @@ const int kMmaxList[] = {2, 3, 4, 5, 6, 8, 16};
 constexpr long long kLaneAutoMin = 131072;
 constexpr long long kChainAutoMin = 131072;   // individuals per context for two launch chains
 // The automatic mapping of ffs_evaluate.  Per row the pipelined decode issues
-// P = (n + sum (m + 1)) (10.5 + mmax) / G vector operations and keeps the
-// chip busy whatever the shape; the lane decode issues L = n (sum (m + 5) + 4)
-// / 64, about half of it, but is held by its LDS (keys and bit sets) to
-// `resident` waves per CU and reaches about a twentieth of the issue rate per
-// wave.  From 1.5 waves of rows per SIMD on (98304 rows) it takes over where
-// P resident > 20 L, from 524288 rows on, where its last round no longer
-// counts, where P resident > 17 L.  Microseconds per call, pipelined / lane,
-// at 98304, 262144 and 1048576 rows: 100 x 5 91 / 83, 151 / 105, 430 / 256;
-// 300 x 4 114 / 114, 224 / 163, 721 / 462; 500 x 10 320 / 412, 754 / 751,
-// 2780 / 2394; 500 x 20 650 / 579, 1539 / 1655, 6029 / 5939; 100 x 20
-// 289 / 199, 675 / 506, 2392 / 1572.
-bool lane_eval_auto(int count, int n, int S, int msum, int mmax, int G, int resident)
+// P = (n + sum (m + 1)) (10.5 + mmax) / G vector operations and keeps the chip
+// busy whatever the shape.  The lane decode issues L = n (sum (m + 5) + 4) /
+// 64, about half of it, plus the stages' partial windows (16 slots), but runs
+// in rounds of the waves that its LDS (keys and bit sets) keeps resident.  It
+// is taken from 65536 rows (a wave per SIMD) on where P times the rows of a CU,
+// over L times the rounds' time, is above 1; above 1.7 below 163840 rows and 2
+// below 98304, where the call is one or two rounds that wait for memory.
+// Microseconds per call, pipelined / lane, at 65536, 131072, 262144 and 524288
+// rows: 512 x 1 191 / 68, 300 / 88, 577 / 162, 1074 / 275; 300 x 3 88 / 77,
+// 125 / 90, 200 / 135, 346 / 229; 100 x 5 61 / 64, 73 / 72, 107 / 94, 172 /
+// 136; 20 x 8 64 / 68, 73 / 65, 109 / 77, 180 / 111; 20 x 20 (80 machines) 150
+// / 106, 237 / 171, 441 / 243, 832 / 397; 500 x 10 223 / 254, 399 / 321, 722 /
+// 592; 700 x 15 382 / 621, 692 / 1205; 500 x 20 462 / 585, 856 / 1124.
+// Over 900 shapes and row counts (1 to 20 stages, 20 to 1000 jobs) the choice
+// costs 1.2 % on average against the better mapping of each.
+bool lane_eval_auto(int count, int n, int S, int msum, int mmax, int G, const LaneEval& e)
 {
-    if (count < 98304) return false;
-    const double P = (double)(n + msum + S) * (10.5 + mmax) / G, L = (double)n * (msum + 5 * S + 4) / 64.0;
-    return P * resident > (count >= 524288 ? 17.0 : 20.0) * L;
+    if (count < 65536) return false;
+    constexpr int kCus = 256;
+    const double P = (double)(n + msum + S) * (10.5 + mmax) / G, L = (double)(n + 16) * (msum + 5 * S + 4) / 64.0;
+    const double w = (double)count / (kWave * kCus);   // waves per CU
+    const int full = (int)(w / e.resident), rest = (int)std::ceil(w - (double)full * e.resident);
+    const double time = full * e.round + (rest > 0 ? lane_round((rest + 3) / 4) : 0.0);
+    return P * w > (count < 98304 ? 2.0 : count < 163840 ? 1.7 : 1.0) * L * time;
 }
 
 // Chromosomes per wave of the per-stage mapping: one lane per stage, the
@@ -1123,7 +1131,7 @@ int launch_eval(ffs_ctx* c, int inst, const int32_t* perms, int count, int32_t* 
     void* kl = I.lane_ok ? pick_eval_lane(c->mm, c->ptb) : nullptr;
     const size_t table = align16((size_t)I.S * ((size_t)I.n_pad * c->ptb + 4));
     const LaneEval le = kl ? lane_eval_split(table, I.lane_wlds_eval, (size_t)c->max_lds) : LaneEval{};
-    const bool lane = le.waves > 0 && (c->mapping == 1 || (c->mapping < 0 && lane_eval_auto(count, I.n, I.S, I.msum, c->mm, I.G, le.resident)));
+    const bool lane = le.waves > 0 && (c->mapping == 1 || (c->mapping < 0 && lane_eval_auto(count, I.n, I.S, I.msum, c->mm, I.G, le)));
     const int wpb = lane ? le.waves : c->wpb;
     const int per_block = wpb * (lane ? kWave : I.G);
     const int blocks = (count + per_block - 1) / per_block;
@@ -2307,7 +2315,7 @@ int ffs_evaluate_noalloc(void* hip_stream, int32_t n, int32_t S, const int32_t* 
     const size_t table = align16((size_t)S * ((size_t)n_pad * ptb + 4));
     void* kl = (msum <= kLaneMaxMsum && mmax <= 8) ? pick_eval_lane(mm, ptb) : nullptr;
     const LaneEval le = kl ? lane_eval_split(table, (size_t)d.lane_wlds_eval, (size_t)max_lds) : LaneEval{};
-    const bool lane = le.waves > 0 && lane_eval_auto(count, n, S, msum, mm, d.G, le.resident);
+    const bool lane = le.waves > 0 && lane_eval_auto(count, n, S, msum, mm, d.G, le);
     const int wpb = lane ? le.waves : 4;
     void* kern = lane ? kl : pick_eval(mm, ptb);
     if (!kern) return FFS_EUNSUPPORTED;

@@ -54,7 +54,8 @@ def test_lane_trajectory_one_stage(n, sweep):
 
 
 @pytest.mark.parametrize("n,machines,rows", [(256, [2], 98304), (48, [4], 524289), (100, [2, 5, 1, 4, 3], 100003),
-                                             (100, [2, 5, 1, 4, 3] * 4, 100003)])
+                                             (100, [2, 5, 1, 4, 3] * 4, 100003),
+                                             (20, [2, 3, 4, 5, 6] * 4, 65537), (500, [3, 3, 3, 5, 3, 5, 4, 5, 4, 5], 196609)])
 def test_automatic_choice_of_many_rows(n, machines, rows):
     """Row counts from which the lane kernel is the automatic choice."""
     import torch
