@@ -1675,7 +1675,7 @@ int ffs_bind_workspace(ffs_ctx* c, void* dptr, size_t bytes)
     if (c->n_work)
         HIP_TRY(c, hipMemcpy(c->ws + c->off_work, c->work.data(), sizeof(WorkItem) * c->work.size(),
                              hipMemcpyHostToDevice));
-    if (c->n_pairs)
+    if (!c->pairs.empty())   // the pairs, then the ring edges
         HIP_TRY(c, hipMemcpy(c->ws + c->off_pairs, c->pairs.data(), sizeof(PairDesc) * c->pairs.size(),
                              hipMemcpyHostToDevice));
     if (!c->sweep.empty())
