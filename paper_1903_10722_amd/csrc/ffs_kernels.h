@@ -115,6 +115,12 @@ __device__ __forceinline__ int completed_gen(const Control* c)
 
 extern __shared__ __align__(16) unsigned char ffs_smem[];
 
+// Four values of a caller's row, which is aligned as an int is.  (Pointers to
+// it are formed with this type: as a template's argument it would lose the
+// alignment, and the reads would claim 16 bytes.)
+typedef int row_vec __attribute__((ext_vector_type(4), aligned(4)));
+typedef const __attribute__((address_space(1))) row_vec* row_vec_ptr;
+
 // Global-memory views of generic pointers: accesses through them compile to
 // global (not flat) instructions, which the compiler may keep in flight
 // across LDS accesses.
@@ -1584,9 +1590,8 @@ __global__ void __launch_bounds__(512) k_evaluate(const InstDesc* __restrict__ I
     if (active) {
         // four values per read, sixteen in flight per lane
         constexpr int U = 4;
-        typedef int row_vec __attribute__((ext_vector_type(4), aligned(4)));
         const int* row = perms + idx * (long long)n;
-        const auto* r4 = as_global(reinterpret_cast<const row_vec*>(row));
+        const row_vec_ptr r4 = (row_vec_ptr)row;
         typedef uint16_t gene_vec __attribute__((ext_vector_type(4)));
         gene_vec* a4 = reinterpret_cast<gene_vec*>(A);
         auto take = [&](int x) {

@@ -308,9 +308,8 @@ struct GenesI32 {
     uint32_t bits;
     __device__ __forceinline__ void load(int lo, uint32_t (&g)[kLaneD]) const
     {
-        typedef int row_vec __attribute__((ext_vector_type(4), aligned(4)));
         if (lo + kLaneD <= n) {
-            const auto* v = as_global(reinterpret_cast<const row_vec*>(row + lo));
+            const row_vec_ptr v = (row_vec_ptr)(row + lo);
 #pragma unroll
             for (int q = 0; q < kLaneD / 4; ++q) {
                 const row_vec x = v[q];
