@@ -343,7 +343,9 @@ template <int MMAX, int KEY, int JB, typename PT, typename Src>
 __device__ __forceinline__ uint32_t lane_decode_keys(Src& src, lds_ptr<PT> pT, int pts, const int* mach, int S,
                                                      int n, int jb, lane_state st, bool& over)
 {
-    const uint32_t ujb = (uint32_t)(JB > 0 ? JB : jb), jmask = (1u << ujb) - 1u;
+    // the job field is JB wide, its mask the instance's own width: whatever a
+    // row holds, a look-up stays below 2^jb
+    const uint32_t ujb = (uint32_t)(JB > 0 ? JB : jb), jmask = (1u << jb) - 1u;
     int off_last = 0;
     for (int k = 0; k + 1 < S; ++k) off_last += mach[k];
     const int nwin = (off_last + n + kLaneD - 1) / kLaneD;
