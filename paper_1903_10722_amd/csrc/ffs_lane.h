@@ -114,6 +114,14 @@ __device__ __forceinline__ uint32_t and_or(uint32_t x, uint32_t m, uint32_t o)
     return r;
 }
 
+// The LDS address n entries below p, which may lie before the LDS: formed as a
+// number, mod 2^32, as the hardware adds what brings it back.
+template <typename T>
+__device__ __forceinline__ lds_ptr<T> lds_below(lds_ptr<T> p, uint32_t n)
+{
+    return (lds_ptr<T>)(uintptr_t)((uint32_t)(uintptr_t)p - n * (uint32_t)sizeof(T));
+}
+
 // sorted list key[0 .. M-1] without key[0] and with nk
 template <int M>
 __device__ __forceinline__ void lane_insert(uint32_t (&key)[M], uint32_t nk)
@@ -171,13 +179,13 @@ __device__ __forceinline__ void lane_stage(uint32_t (&r)[kLaneD], uint32_t (&key
         for (int i = 0; i < kLaneD; ++i) low[i] = and_or(r[i], jmask, (uint32_t)(kLaneFirst + i) << jb);
         if (JB > 0) {
             // prow - index of slot i = (prow - the last slot's) + an offset
-            const lds_ptr<PT> at = prow - ((kLaneFirst + kLaneD - 1) << JB);
+            const lds_ptr<PT> at = lds_below(prow, (uint32_t)(kLaneFirst + kLaneD - 1) << JB);
 #pragma unroll
             for (int i = 0; i < kLaneD; ++i) pj[i] = (uint32_t)(at + low[i])[(kLaneD - 1 - i) << JB];
         } else {
 #pragma unroll
             for (int i = 0; i < kLaneD; ++i) {
-                const lds_ptr<PT> at = prow - ((uint32_t)(kLaneFirst + i) << jb);   // uniform
+                const lds_ptr<PT> at = lds_below(prow, (uint32_t)(kLaneFirst + i) << jb);   // uniform
                 pj[i] = (uint32_t)at[low[i]];
             }
         }
