@@ -888,19 +888,20 @@ int apply_tile(ffs_ctx* c)
 {
     int max_lds = 0;
     HIP_TRY(c, hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device));
+    // the current generation's best individuals, by the fold groups it ran in
+    int rc = c->bound ? flush_best(c) : FFS_OK;
+    if (rc) return rc;
     layout(c);
     if (c->lds_gen > (size_t)max_lds)
         return fail(c, FFS_EUNSUPPORTED, "a workgroup needs %zu bytes of LDS (limit %d)", c->lds_gen, max_lds);
-    int rc = prepare_classes(c);
+    rc = prepare_classes(c);
     if (rc) return rc;
     if (c->n_work)
         HIP_TRY(c, hipMemcpy(c->ws + c->off_work, c->work.data(), sizeof(WorkItem) * c->work.size(),
                              hipMemcpyHostToDevice));
     if (c->bound) {
-        // new launch width: count launches afresh from the current generation
-        // (its best individuals folded first), and the islands' chains
-        rc = flush_best(c);
-        if (rc) return rc;
+        // new launch width: count launches afresh from the current generation,
+        // and the islands' chains
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         std::vector<int> zeros(c->max_work + 16, 0);
         HIP_TRY(c, hipMemcpy(c->ws + c->off_counts, zeros.data(), zeros.size() * sizeof(int), hipMemcpyHostToDevice));
