@@ -191,7 +191,8 @@ int ffs_get_chains(ffs_ctx *ctx, int32_t *used);
 int ffs_set_instance_tile(ffs_ctx *ctx, int32_t inst, int32_t mapping, int32_t waves);
 
 /* When a generation has several launches (instances of different tiles or
- * LDS needs), run them side by side on streams forked from and joined back
+ * LDS needs; with the pre-screen the training step and the next candidates'
+ * features), run them side by side on streams forked from and joined back
  * into the context's stream (parallel branches of the captured graph), or
  * one after another (enable = 0).  Default: side by side.  Results are
  * identical.                                                               */

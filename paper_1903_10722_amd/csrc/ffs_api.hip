@@ -1101,7 +1101,8 @@ int surrogate_score(ffs_ctx* c, float* Tout)
 // not the weights: they run beside the training step (twelve launches that
 // fill a small part of the chip: 94 us at 4096 rows; the features of 4096
 // cells x 8 candidates of 1000 jobs 128 us; a screened generation 440 ->
-// 408 us), joined before the predictions.
+// 408 us), joined before the predictions; in one stream if the context's
+// launches are to run one after another.
 int capture_screened(ffs_ctx* c, int gens)
 {
     int rc = surrogate_features(c, nullptr, c->stream);
@@ -1110,14 +1111,15 @@ int capture_screened(ffs_ctx* c, int gens)
         if (rc == FFS_OK) rc = launch_generation(c, 0);
         if (rc != FFS_OK) break;
         const bool more = t + 1 < gens;
-        if (more) {
+        const bool fork = more && c->concurrent;
+        if (fork) {
             HIP_TRY(c, hipEventRecord(c->fork_ev[0], c->stream));
             HIP_TRY(c, hipStreamWaitEvent(c->aux[0], c->fork_ev[0], 0));
-            rc = surrogate_features(c, nullptr, c->aux[0]);
-            HIP_TRY(c, hipEventRecord(c->fork_ev[1], c->aux[0]));
         }
+        if (more) rc = surrogate_features(c, nullptr, fork ? c->aux[0] : c->stream);
+        if (fork) HIP_TRY(c, hipEventRecord(c->fork_ev[1], c->aux[0]));
         const int trc = surrogate_train(c);
-        if (more) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->fork_ev[1], 0));
+        if (fork) HIP_TRY(c, hipStreamWaitEvent(c->stream, c->fork_ev[1], 0));
         if (rc == FFS_OK) rc = trc;
     }
     return rc;

@@ -48,3 +48,19 @@ def test_reads_between_replays(interval, gens):
     ctx.close()
     # records were found in replays that follow a read
     assert len(set(found)) > 4, found
+
+
+def test_screened_epochs_one_after_another():
+    """Pre-screened epochs with the context's launches one after another: the
+    whole state equals that of launches side by side."""
+    from test_gpu_surrogate import _ctx, _small
+    ensure_built()
+    say("[capture] pre-screened epochs, launches side by side and one after another")
+    a, b = (_ctx(_small(seed=8), warmup=3, seed=5) for _ in range(2))
+    b.set_concurrent(False)
+    for g in (10, 10, 7, 3, 20):
+        a.evolve(g)
+        b.evolve(g)
+        assert a.checkpoint() == b.checkpoint(), a.generation
+    a.close()
+    b.close()
