@@ -714,11 +714,19 @@ __device__ __forceinline__ int ox_group_first(const OxCut& o, int cnt, int g, in
 }
 
 // The group's crossover with every vector in registers: row A (marks, then
-// the child) is in LDS, the parents' rows in HBM.
+// the child) is in LDS, the parents' rows in HBM.  Above seven vectors a lane
+// reads parent 1 again, half at a time, for its place in the child: held
+// through the crossover, both parents took k_generation to 179 registers, two
+// waves per SIMD instead of three, whatever the length of its rows (8192
+// individuals of 20 jobs, 20 stages and 80 machines 31.9 -> 35.4 us a
+// generation, of 1000 x 20 133 -> 149; now 28.8 and 133, and rows of eight to
+// thirteen vectors within 1 % of before).
 template <int VC>
 __device__ __forceinline__ void ox_group_regs(uint16_t* A, const uint16_t* P1, const uint16_t* P2, const OxCut& o,
                                               int vpl, int g, int k, int S, bool active)
 {
+    constexpr bool kAgain = VC > 7;
+    constexpr int H = kAgain ? (VC + 1) / 2 : VC;
     const int nv = (o.n + 7) >> 3, v0 = k * vpl;
     const int lim = active ? o.n - 8 * v0 : 0;   // genes past vector vpl - 1 are not looked at
     u32x4 x1[VC], x2[VC];
@@ -730,7 +738,17 @@ __device__ __forceinline__ void ox_group_regs(uint16_t* A, const uint16_t* P1, c
     const int cnt = ox_keep<VC>(A, x2, keep, o, v0, vpl, lim);
     const int pos = ox_group_first(o, cnt, g, S);
     wave_sync();
-    ox_place1<VC>(A, x1, o, v0, vpl, lim);
+    if (kAgain) {
+#pragma unroll
+        for (int h = 0; h < VC; h += H) {
+            u32x4 y[H];
+            const int c = vpl - h < H ? vpl - h : H;
+            ox_load<H>(y, P1, v0 + h, c, nv);
+            ox_place1<H>(A, y, o, v0 + h, c, lim - 8 * h);
+        }
+    } else {
+        ox_place1<VC>(A, x1, o, v0, vpl, lim);
+    }
     wave_sync();
     ox_place2<VC>(A, x2, keep, o, vpl, pos);
     wave_sync();
@@ -1261,7 +1279,7 @@ static __global__ void __launch_bounds__(256) k_best_flush(const InstDesc* __res
 
 // ---- one generation (mode 0) or generation 0 (mode 1) of every island -----
 template <int MMAX, typename PT>
-__global__ void __launch_bounds__(512) k_generation(const InstDesc* __restrict__ insts,
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(3))) k_generation(const InstDesc* __restrict__ insts,
                                                     const IslandDesc* __restrict__ isls,
                                                     const WorkItem* __restrict__ work, Control* ctl, int n_inst,
                                                     int mode, int cnt_off, int has_extra)
