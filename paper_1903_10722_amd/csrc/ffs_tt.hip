@@ -627,10 +627,23 @@ __device__ __forceinline__ long long decode_child(const TtDesc& d, const Smem& s
         return decode_wave<KMAX>(d, sm, w.child, w.ordA, w.ordB, w.rdyA, w.rdyB, w.keys, lane);
 }
 
-// The wave of a thread, as a value the compiler knows to be uniform: all that
-// follows from it (the individual, its parents, its draws' Philox blocks) is
-// scalar work beside the vector unit's.
-__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+// A value that is the same on all lanes, known to be so by the compiler where
+// every stage has at most two machines: all that follows from a wave's index
+// (the individual, its parents, its draws' Philox blocks) is scalar work beside
+// the vector unit's.  The general decode holds so many scalars itself that
+// these push them out of registers: ten runs of 512 individuals, 64 jobs, four
+// stages of four machines 73.8 us without, 77.5 with them.
+template <int MMX>
+__device__ __forceinline__ int uniform(int x)
+{
+    return MMX == 2 ? __builtin_amdgcn_readfirstlane(x) : x;
+}
+
+template <int MMX>
+__device__ __forceinline__ int wave_index()
+{
+    return uniform<MMX>((int)threadIdx.x >> 6);
+}
 
 template <typename T>
 __device__ __forceinline__ const __attribute__((address_space(1))) T* global_of(const T* p)
@@ -712,17 +725,17 @@ __global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mo
                                                        int fold_blocks)
 {
     if ((int)blockIdx.x < fold_blocks) {
-        fold_run(d, gen - 1, (int)blockIdx.x * (int)(blockDim.x >> 6) + wave_index(), (int)threadIdx.x & 63);
+        fold_run(d, gen - 1, (int)blockIdx.x * (int)(blockDim.x >> 6) + wave_index<MMX>(), (int)threadIdx.x & 63);
         return;
     }
     const Smem sm = smem_tables(tt_smem, d);
     stage_tables(d, tt_smem);
     __syncthreads();
-    const int wpb = blockDim.x >> 6, wave = wave_index(), lane = threadIdx.x & 63;
+    const int wpb = blockDim.x >> 6, wave = wave_index<MMX>(), lane = threadIdx.x & 63;
     const uint32_t wg = (blockIdx.x - (uint32_t)fold_blocks) * (uint32_t)wpb + (uint32_t)wave;   // at most kMaxRuns kMaxIsl kMaxIslSize + 3
     const uint32_t per_run = (uint32_t)((mode <= 1) ? d.N : count);
     if (wg >= (uint32_t)d.runs * per_run) return;
-    const int run = __builtin_amdgcn_readfirstlane((int)(wg / per_run));   // the division is vector work
+    const int run = uniform<MMX>((int)(wg / per_run));   // the division is vector work
     const int q0 = (int)(wg - (uint32_t)run * per_run);
     int isl = 0, slot = 0;
     if (mode <= 1) {
@@ -751,8 +764,8 @@ __global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mo
             }
         }
     }
-    isl = __builtin_amdgcn_readfirstlane(isl);
-    slot = __builtin_amdgcn_readfirstlane(slot);
+    isl = uniform<MMX>(isl);
+    slot = uniform<MMX>(slot);
     const TtIsland I = island_at(d, isl);
     const int L = d.L, Lp = d.Lp, S = d.S;
     const WaveMem w = wave_mem<MMX>(tt_smem + tables_bytes(d.J, S, d.MX, d.Lp) + wave * wave_bytes(Lp, d.Jp, MMX), Lp,
@@ -1014,7 +1027,7 @@ __global__ void __launch_bounds__(256) k_tt_evaluate(TtDesc d, const uint8_t* ge
     const Smem sm = smem_tables(tt_smem, d);
     stage_tables(d, tt_smem);
     __syncthreads();
-    const int wpb = blockDim.x >> 6, wave = wave_index(), lane = threadIdx.x & 63;
+    const int wpb = blockDim.x >> 6, wave = wave_index<MMX>(), lane = threadIdx.x & 63;
     const long long row = (long long)blockIdx.x * wpb + wave;
     if (row >= count) return;
     const WaveMem w = wave_mem<MMX>(
