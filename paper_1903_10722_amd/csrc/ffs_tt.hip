@@ -672,7 +672,13 @@ extern __shared__ __align__(16) unsigned char tt_smem[];
 // record after the reads they depend on.
 // Between two generations of one call the second one's launch carries it
 // (its first workgroups; the rows and keys of the other parity are only read
-// there), which saves a launch of 4.6 us; otherwise it is k_tt_fold.
+// there), which saves a launch of 4.6 us; otherwise it is k_tt_fold.  Not in
+// the general decode of more than 512 jobs, whose launches hold few workgroups
+// at a time and got longer by more than that (ten runs of 600 jobs, four stages
+// of four machines 490 -> 512 us).
+template <int KMAX, int MMX>
+constexpr bool carries_fold() { return MMX == 2 || KMAX <= 8; }
+
 __device__ __forceinline__ void fold_run(const TtDesc& d, int gen, int run, int lane)
 {
     if (run >= d.runs) return;
@@ -724,7 +730,7 @@ template <int KMAX, int MMX>
 __global__ void __launch_bounds__(256) k_tt_generation(TtDesc d, int gen, int mode, int sel, int diag, int count,
                                                        int fold_blocks)
 {
-    if ((int)blockIdx.x < fold_blocks) {
+    if (carries_fold<KMAX, MMX>() && (int)blockIdx.x < fold_blocks) {
         fold_run(d, gen - 1, (int)blockIdx.x * (int)(blockDim.x >> 6) + wave_index<MMX>(), (int)threadIdx.x & 63);
         return;
     }
@@ -1074,6 +1080,7 @@ struct ffs_tt_ctx {
     size_t lds_gen = 0;
     const void* kgen = nullptr;    // generation and evaluate kernels of the instance (pick_kernels)
     const void* keval = nullptr;
+    bool carry = false;            // a generation's launch can fold the one before
     // timing
     bool timing = false;
     std::vector<hipEvent_t> ev;
@@ -1153,6 +1160,7 @@ void pick_kernels(ffs_tt_ctx* c)
     {                                                                         \
         c->kgen = reinterpret_cast<const void*>(&k_tt_generation<N, MMX>);    \
         c->keval = reinterpret_cast<const void*>(&k_tt_evaluate<N, MMX>);     \
+        c->carry = carries_fold<N, MMX>();                                    \
     }
     const int K = (c->J + 63) / 64;
     if (c->MX > 2) {
@@ -1492,7 +1500,7 @@ int ffs_tt_evolve(ffs_tt_ctx* c, int32_t generations)
     for (int it = 0; it < generations; ++it) {
         const int g = c->gen + 1;
         const bool migrate = c->interval > 0 && g % c->interval == 0;
-        const bool now = migrate || c->sweep || it + 1 == generations;
+        const bool now = migrate || c->sweep || !c->carry || it + 1 == generations;
         if ((rc = launch_gen(c, g, 0, open, now)) != FFS_OK) return rc;
         open = !now;
         c->gen = g;
