@@ -754,24 +754,89 @@ __device__ __forceinline__ void ox_group_regs(uint16_t* A, const uint16_t* P1, c
     wave_sync();
 }
 
-// The crossover of a whole wave on one row of up to 512 VC genes: lane l
-// holds vectors [VC l, VC l + VC) of both parents, already in registers.  The
-// kept genes of each vector entry are one wave mask, so the counts below a
-// lane come from mask bit counts instead of a scan over the lanes.  About 170
-// VALU and 26 to 33 LDS instructions a child at 500 jobs (from 240 and 50 to
-// 80, with a reversed copy for pseudo pairs): a large generation 724 -> 690 us,
-// the pre-screen's candidates of 1000 jobs 145 -> 125 us.
-template <int VC>
-__device__ __forceinline__ void ox_wave(uint16_t* A, const u32x4 (&x1)[VC], const u32x4 (&x2)[VC], const OxCut& o,
+// A row shared by a whole wave: lane l holds genes [C l, C l + C), as many as
+// the row needs (C = 1, 2, 4, 8, 16).
+template <int C>
+struct LaneGenes {
+    uint32_t w[C > 1 ? C / 2 : 1];
+    __device__ __forceinline__ uint32_t gene(int e) const
+    {
+        return C == 1 ? w[0] : ((e & 1) ? w[e >> 1] >> 16 : w[e >> 1] & 0xFFFFu);
+    }
+};
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// The lane's genes of a row of n_pad entries (past its end: its last ones).
+template <int C>
+__device__ __forceinline__ void lane_genes_load(LaneGenes<C>& x, const uint16_t* row, int lane, int n_pad)
+{
+    const uint16_t* p = row + (C * lane < n_pad ? C * lane : n_pad - C);
+    if constexpr (C == 1) {
+        x.w[0] = as_global(p)[0];
+    } else if constexpr (C == 2) {
+        x.w[0] = as_global(reinterpret_cast<const uint32_t*>(p))[0];
+    } else if constexpr (C == 4) {
+        const u32x2 v = as_global(reinterpret_cast<const u32x2*>(p))[0];
+        x.w[0] = v.x;
+        x.w[1] = v.y;
+    } else {
+#pragma unroll
+        for (int q = 0; q < C / 8; ++q) {
+            const u32x4 v = as_global(reinterpret_cast<const u32x4*>(p))[q];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x.w[4 * q + e] = v[e];
+        }
+    }
+}
+
+// The lane's genes at their positions of an LDS row.
+template <int C>
+__device__ __forceinline__ void lane_genes_store(uint16_t* A, const LaneGenes<C>& x, int lane)
+{
+    uint16_t* p = A + C * lane;
+    if constexpr (C == 1) {
+        p[0] = (uint16_t)x.w[0];
+    } else if constexpr (C == 2) {
+        *reinterpret_cast<uint32_t*>(p) = x.w[0];
+    } else if constexpr (C == 4) {
+        *reinterpret_cast<u32x2*>(p) = u32x2{x.w[0], x.w[1]};
+    } else {
+#pragma unroll
+        for (int q = 0; q < C / 8; ++q)
+            reinterpret_cast<u32x4*>(p)[q] = u32x4{x.w[4 * q], x.w[4 * q + 1], x.w[4 * q + 2], x.w[4 * q + 3]};
+    }
+}
+
+// The crossover of a whole wave on one row of up to 64 C genes, both parents
+// already in registers.  The kept genes of each entry are one wave mask, so
+// the counts below a lane come from mask bit counts instead of a scan over the
+// lanes.  About 170 VALU and 26 to 33 LDS instructions a child at 500 jobs (C =
+// 8; from 240 and 50 to 80, with a reversed copy for pseudo pairs): a large
+// generation 724 -> 690 us, the pre-screen's candidates of 1000 jobs 145 -> 125
+// us.  The cost goes with C, not with the row: eight genes a lane for every row
+// took generations of 20 and 60 jobs 10 % longer than a scan over single genes
+// had (147456 individuals, one lane per chromosome: 20 jobs x 3 stages 142 ->
+// 155 us, 86 with C = 1; 60 x 3 150 -> 165, 97; 100 x 5 189 -> 197, 136 with
+// C = 2; the uneven batch of 256 instances 157.6 -> 136.4 ms).
+template <int C>
+__device__ __forceinline__ void ox_wave(uint16_t* A, const LaneGenes<C>& x1, const LaneGenes<C>& x2, const OxCut& o,
                                         int lane)
 {
-    constexpr int C = 8 * VC;
     const int lim = o.n - C * lane;
-    ox_mark<VC>(A, x1, o, VC * lane, VC, lim);
+    {
+        const int st = o.rev1 ? -1 : 1;
+        int t = (o.rev1 ? o.n - 1 - C * lane : C * lane) - o.a;
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            if (i < lim) A[x1.gene(i)] = (uint16_t)t;
+            t += st;
+        }
+    }
     wave_sync();
     uint32_t m[C];
 #pragma unroll
-    for (int i = 0; i < C; ++i) m[i] = A[ox_gene(x2[i >> 3], i & 7)];
+    for (int i = 0; i < C; ++i) m[i] = A[x2.gene(i)];
     // entries of lane l lie after position b in P2's order from lane
     // (q - i + C) / C on (below it if reversed)
     const int b = o.a + o.len, q = o.rev2 ? o.n - 2 - b : b;
@@ -788,14 +853,22 @@ __device__ __forceinline__ void ox_wave(uint16_t* A, const u32x4 (&x1)[VC], cons
         after += __popcll(bal & (o.rev2 ? ~up : up));
     }
     wave_sync();
-    ox_place1<VC>(A, x1, o, VC * lane, VC, lim);
+    // parent 1's genes at their positions in the child (those outside the
+    // segment are overwritten by the kept genes)
+    if (!o.rev1) {
+        if (lim > 0) lane_genes_store<C>(A, x1, lane);
+    } else {
+#pragma unroll
+        for (int i = 0; i < C; ++i)
+            if (i < lim) A[o.n - 1 - C * lane - i] = (uint16_t)x1.gene(i);
+    }
     wave_sync();
     int pos = ox_first(o, (int)excl, after);
     const OxStep st = ox_step(o);
 #pragma unroll
     for (int i = 0; i < C; ++i)
         if (kp[i]) {
-            A[pos] = (uint16_t)ox_gene(x2[i >> 3], i & 7);
+            A[pos] = (uint16_t)x2.gene(i);
             pos = ox_next(st, pos);
         }
     wave_sync();

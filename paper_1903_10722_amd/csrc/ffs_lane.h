@@ -570,36 +570,38 @@ __global__ void __launch_bounds__(512) k_generation_lane(const InstDesc* __restr
             // that their round trips pass under the others' decodes (a large
             // generation 660 -> 586 us; the decode first instead: no gain).
             __builtin_amdgcn_s_setprio(3);
-            auto build = [&](auto vc) {
-                constexpr int VC = decltype(vc)::value;
-                u32x4 ra[VC], rb[VC];
-                const int nv = (n + 7) >> 3;
+            auto build = [&](auto cc) {
+                constexpr int C = decltype(cc)::value;   // genes per lane
+                LaneGenes<C> ra, rb;
                 auto fetch = [&](int c) {
                     const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)w_src, c);
-                    ox_load<VC>(ra, parent1(src), VC * lane, VC, nv);
-                    if (cell) ox_load<VC>(rb, parent2(src), VC * lane, VC, nv);
+                    lane_genes_load<C>(ra, parent1(src), lane, n_pad);
+                    if (cell) lane_genes_load<C>(rb, parent2(src), lane, n_pad);
                 };
                 fetch(0);
                 for (int c = 0; c < wcount; ++c) {
                     const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)w_src, c);
                     const uint32_t cut = (uint32_t)__builtin_amdgcn_readlane((int)w_cut, c);
-                    u32x4 x1[VC], x2[VC];
-#pragma unroll
-                    for (int v = 0; v < VC; ++v) {
-                        x1[v] = ra[v];
-                        x2[v] = cell ? rb[v] : ra[v];
-                    }
+                    const LaneGenes<C> x1 = ra;
+                    LaneGenes<C> x2 = ra;
+                    if (cell) x2 = rb;
                     if (c + 1 < wcount) fetch(c + 1);
-                    ox_wave<VC>(A, x1, x2, cut_of(src, cut), lane);
+                    ox_wave<C>(A, x1, x2, cut_of(src, cut), lane);
                     finish(c);
                 }
             };
-            // up to 512 and 1024 jobs the next child's parents are read while
-            // this one is built; longer rows are read when they are needed
-            if (n <= 512) {
+            // up to 1024 jobs the next child's parents are read while this one
+            // is built; longer rows are read when they are needed
+            if (n <= 64) {
                 build(std::integral_constant<int, 1>{});
-            } else if (n <= 1024) {
+            } else if (n <= 128) {
                 build(std::integral_constant<int, 2>{});
+            } else if (n <= 256) {
+                build(std::integral_constant<int, 4>{});
+            } else if (n <= 512) {
+                build(std::integral_constant<int, 8>{});
+            } else if (n <= 1024) {
+                build(std::integral_constant<int, 16>{});
             } else {
                 for (int c = 0; c < wcount; ++c) {
                     const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)w_src, c);
@@ -934,36 +936,30 @@ __global__ void __launch_bounds__(1024) k_cand_features(const InstDesc* __restri
         cand_features<SM, PT>(A, pJ, rsb, I, cm, acc, lane, Xout + ((size_t)cell * K + c) * kFeat);
         wave_sync();
     };
-    auto build = [&](auto vc) {
-        constexpr int VC = decltype(vc)::value;
-        u32x4 ra[VC], rb[VC];
-        const int nv = (n + 7) >> 3;
+    auto build = [&](auto cc) {
+        constexpr int C = decltype(cc)::value;   // genes per lane
+        LaneGenes<C> ra, rb;
         auto fetch = [&](int c) {
             const uint16_t *p1, *p2;
             parents(c, p1, p2);
-            ox_load<VC>(ra, p1, VC * lane, VC, nv);
-            ox_load<VC>(rb, p2, VC * lane, VC, nv);
+            lane_genes_load<C>(ra, p1, lane, n_pad);
+            lane_genes_load<C>(rb, p2, lane, n_pad);
         };
         fetch(0);
         for (int c = 0; c < K; ++c) {
             const CellMeta cm = meta(c);
-            u32x4 x1[VC], x2[VC];
-#pragma unroll
-            for (int v = 0; v < VC; ++v) {
-                x1[v] = ra[v];
-                x2[v] = rb[v];
-            }
+            const LaneGenes<C> x1 = ra, x2 = rb;
             if (c + 1 < K) fetch(c + 1);
-            ox_wave<VC>(A, x1, x2, ox_cut(n, cm.cx, cm.a, cm.b, false, false), lane);
+            ox_wave<C>(A, x1, x2, ox_cut(n, cm.cx, cm.a, cm.b, false, false), lane);
             finish(c, cm);
         }
     };
     // up to 512 and 1024 jobs the next candidate's parents are read while this
     // one is built; longer rows are read when they are needed
     if (n <= 512) {
-        build(std::integral_constant<int, 1>{});
+        build(std::integral_constant<int, 8>{});
     } else if (n <= 1024) {
-        build(std::integral_constant<int, 2>{});
+        build(std::integral_constant<int, 16>{});
     } else {
         for (int c = 0; c < K; ++c) {
             const CellMeta cm = meta(c);
