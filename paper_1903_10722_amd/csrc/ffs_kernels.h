@@ -166,8 +166,8 @@ __host__ __device__ inline size_t wave_lds_bytes(int G, int n, int n_pad, int S)
 }
 
 // LDS entries of a wave that builds whole rows, one at a time.
-// Above 1024 jobs the crossover's marks have a row of their own.
-__host__ __device__ inline int wave_row(int n_pad) { return n_pad <= 1024 ? n_pad + 8 : 2 * n_pad + 8; }
+// Above 2048 jobs the crossover's marks have a row of their own.
+__host__ __device__ inline int wave_row(int n_pad) { return n_pad <= 2048 ? n_pad + 8 : 2 * n_pad + 8; }
 
 // The processing-time table is staged into LDS stage-major with each row
 // padded by 4 bytes, so that the S rows start on different LDS banks (the S
@@ -912,12 +912,18 @@ __device__ __forceinline__ void ox_group_long(uint16_t* A, uint16_t* M, const ui
     wave_sync();
 }
 
-// The whole wave on a row of more than 1024 genes, as a function of its own
-// (its registers and code stay out of the callers' main path).
-__device__ __attribute__((noinline)) void ox_wave_long(uint16_t* A, uint16_t* M, const uint16_t* P1,
-                                                       const uint16_t* P2, OxCut o, int lane)
+// The whole wave on a row of more than 1024 genes: up to 2048 in registers,
+// above that in passes with the marks in a row of their own (A + n_pad).  Not
+// as a function of its own: each call saved its registers to scratch memory,
+// which was most of it (147456 individuals, one lane per chromosome: 1500 jobs
+// of one stage 737 us with three LDS rows, 854 in passes behind a call, 631
+// now; 2000 jobs of three stages 1706, 1183, 973).
+__device__ __forceinline__ void ox_wave_long(uint16_t* A, int n_pad, const uint16_t* P1, const uint16_t* P2,
+                                             const OxCut& o, int lane)
 {
-    ox_group_long<2>(A, M, P1, P2, o, ox_vectors(o.n, kWave), 0, lane, kWave, true);
+    const int vpl = ox_vectors(o.n, kWave);
+    if (n_pad <= 2048) ox_group_regs<4>(A, P1, P2, o, vpl, 0, lane, kWave, true);
+    else ox_group_long<2>(A, A + n_pad, P1, P2, o, vpl, 0, lane, kWave, true);
 }
 
 template <bool SMALL>   // at most kOxSmall vectors per lane

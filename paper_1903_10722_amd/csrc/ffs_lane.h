@@ -606,7 +606,7 @@ __global__ void __launch_bounds__(512) k_generation_lane(const InstDesc* __restr
                 for (int c = 0; c < wcount; ++c) {
                     const uint32_t src = (uint32_t)__builtin_amdgcn_readlane((int)w_src, c);
                     const uint32_t cut = (uint32_t)__builtin_amdgcn_readlane((int)w_cut, c);
-                    ox_wave_long(A, A + n_pad, parent1(src), parent2(src), cut_of(src, cut), lane);
+                    ox_wave_long(A, n_pad, parent1(src), parent2(src), cut_of(src, cut), lane);
                     finish(c);
                 }
             }
@@ -965,7 +965,7 @@ __global__ void __launch_bounds__(1024) k_cand_features(const InstDesc* __restri
             const CellMeta cm = meta(c);
             const uint16_t *p1, *p2;
             parents(c, p1, p2);
-            ox_wave_long(A, A + n_pad, p1, p2, ox_cut(n, cm.cx, cm.a, cm.b, false, false), lane);
+            ox_wave_long(A, n_pad, p1, p2, ox_cut(n, cm.cx, cm.a, cm.b, false, false), lane);
             finish(c, cm);
         }
     }
