@@ -388,8 +388,9 @@ __device__ __forceinline__ void pipe_step(uint32_t (&key)[MMAX], uint32_t& o_key
 // permutation's genes, each with completion 0 and its time at the first
 // stage.  So every lane runs the same instructions, without selects for the
 // first stage and without a table of (time, job) words built beforehand, and
-// the permutation's 16-bit row is all a group keeps in LDS: 14 + M / 8 VALU
-// operations a step for lists of M = 4, from about 31, and a third of the LDS.
+// the permutation's 16-bit row is all a group keeps in LDS: 13.5 VALU
+// operations a step for lists of M = 4 (four insert the key, half of one
+// renumbers a block's indices), from about 31, and a third of the LDS.
 // What bounds it: the chain of a step, about 15 dependent VALU operations and
 // the table read that the next step waits for, when a SIMD holds one or two
 // waves; VALU issue beyond that.  ffs_evaluate, from the version with table

@@ -9,12 +9,13 @@
 //
 // Slots.  Stage k dispatches its n jobs at slots off_k .. off_k + n - 1
 // (off_k = m_0 + ... + m_{k-1}); the key it removes at a dispatch (the
-// machine's previous job, completion << jb | job) is written back to the
-// slot it read, so the slot sequence of stage k's writes is its release
-// order.  The first m_k of them are the machines' initial empty entries;
-// after its last dispatch the stage writes its remaining entries, in order,
-// to slots off_k + n .. off_k + n + m_k - 1.  Stage k + 1 therefore reads
-// exactly its input order at slots off_{k+1} .. off_{k+1} + n - 1.
+// machine's previous job: completion, in the three-field format the dispatch
+// index within the window, job) is written back to the slot it read, so the
+// slot sequence of stage k's writes is its release order.  The first m_k of
+// them are the machines' initial empty entries; after its last dispatch the
+// stage writes its remaining entries, in order, to slots off_k + n .. off_k + n
+// + m_k - 1.  Stage k + 1 therefore reads exactly its input order at slots
+// off_{k+1} .. off_{k+1} + n - 1.
 // Entries of one stage leave in (completion, dispatch order) order -- the
 // first-in-first-out rule at the next stage -- because a newly dispatched
 // job is inserted after every entry whose completion is not later than its
@@ -687,10 +688,9 @@ __global__ void __launch_bounds__(512) k_generation_lane(const InstDesc* __restr
 // return, which nothing waits for); an invalid row gets makespan -1 and
 // sets the control block's error word.  Bound by vector issue (M + 5
 // operations per job and stage, four more per job for the check), by latency
-// where its LDS holds few waves.  Against the version that read every row
-// twice, value by value, with an atomic that returns per value: a
-// million rows of 100 x 5 259 us instead of 371 (pipelined), 262144 rows of
-// 500 x 10 751 us instead of about 1380.
+// where its LDS holds few waves.  A million rows of 100 x 5 take 238 us (371
+// pipelined), 262144 rows of 500 x 10 593 us (731 pipelined; about 1380 with
+// every row read twice, value by value, and an atomic that returns per value).
 template <int MMAX, typename PT>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) k_evaluate_lane(const InstDesc* __restrict__ I, const int* __restrict__ perms,
                                                        int count, int* __restrict__ out, Control* ctl)
@@ -870,7 +870,8 @@ __device__ __forceinline__ void cand_features(const uint16_t* A, const unsigned 
 // the CELL purpose, generation completed + 1); the wave then builds each
 // candidate on all 64 lanes (order crossover, swap mutation) and writes its
 // features to Xout[(cell * K + c) * 256].  LDS: the job-major table (rows of
-// rsb bytes), then per wave three rows and B * S bucket sums.
+// rsb bytes), then per wave wave_row(n_pad) entries and 240 words of bucket
+// sums.
 template <int SM, typename PT>
 __global__ void __launch_bounds__(1024) k_cand_features(const InstDesc* __restrict__ insts,
                                                        const IslandDesc* __restrict__ isls, int inst,
