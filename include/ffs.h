@@ -240,7 +240,7 @@ int ffs_evaluate_host(ffs_ctx *ctx, int32_t inst, const int32_t *perms, int32_t 
  *   perms: device, int32 [count * n_jobs]; out_makespans: device, int32 [count];
  *   hip_stream: a stream of the current device (NULL = the null stream).
  * Limits: n_jobs <= 4096, n_stages <= 64, the packed-key limit of
- * ffs_create_instance, and 4 n S + S * n_pad * w bytes of state and 1 KiB
+ * ffs_create_instance, and 4 n S + S * n_pad * w bytes of state and 1.5 KiB
  * within 1 MiB (n_pad = n rounded up to 32, w = 1 if every p <= 255 else 2),
  * else FFS_EUNSUPPORTED.  The state lives in a statically allocated device
  * array (1 MiB per GPU, held until the process ends) that every call on a

@@ -171,30 +171,34 @@ const int kMmaxList[] = {2, 3, 4, 5, 6, 8, 16};
 constexpr long long kLaneAutoMin = 131072;
 constexpr long long kChainAutoMin = 131072;   // individuals per context for two launch chains
 // The automatic mapping of ffs_evaluate.  Per row the pipelined decode issues
-// P = (n + sum (m + 1)) (10.5 + mmax) / G vector operations and keeps the chip
-// busy whatever the shape.  The lane decode issues L = n (sum (m + 5) + 4) /
+// P = ((n + sum (m + 1)) (10.5 + mmax) + 20 n / S) / G vector operations (the
+// last term reads and checks the row on a group's S lanes) and keeps the chip
+// busy whatever the shape.  The lane decode issues L = n (sum (m + 6) + 4) /
 // 64, about half of it, plus the stages' partial windows (16 slots), but runs
 // in rounds of the waves that its LDS (keys and bit sets) keeps resident.  It
-// is taken from 65536 rows (a wave per SIMD) on where P times the rows of a CU,
-// over L times the rounds' time, is above 1; above 1.7 below 163840 rows and 2
-// below 98304, where the call is one or two rounds that wait for memory.
-// Microseconds per call, pipelined / lane, at 65536, 131072, 262144 and 524288
-// rows: 512 x 1 191 / 68, 300 / 88, 577 / 162, 1074 / 275; 300 x 3 88 / 77,
-// 125 / 90, 200 / 135, 346 / 229; 100 x 5 61 / 64, 73 / 72, 107 / 94, 172 /
-// 136; 20 x 8 64 / 68, 73 / 65, 109 / 77, 180 / 111; 20 x 20 (80 machines) 150
-// / 106, 237 / 171, 441 / 243, 832 / 397; 500 x 10 223 / 254, 399 / 321, 722 /
-// 592; 700 x 15 382 / 621, 692 / 1205; 500 x 20 462 / 585, 856 / 1124.
-// Over 900 shapes and row counts (1 to 20 stages, 20 to 1000 jobs) the choice
-// costs 1.2 % on average against the better mapping of each.
+// is taken from 65536 rows (a wave per SIMD) on where P times the rows of a CU
+// is more than 1.9 times L times the rounds' time.  Microseconds per call,
+// pipelined / lane, at 65536, 131072, 262144 and 524288 rows: 512 x 1 191 / 68,
+// 300 / 88, 577 / 162, 1074 / 275; 300 x 3 88 / 77, 125 / 90, 200 / 135, 346 /
+// 229; 100 x 5 61 / 64, 73 / 72, 107 / 94, 172 / 136; 20 x 8 64 / 68, 73 / 65,
+// 109 / 77, 180 / 111; 20 x 20 (80 machines) 150 / 106, 237 / 171, 441 / 243,
+// 832 / 397; 500 x 10 223 / 254, 399 / 321, 722 / 592; 500 x 20 462 / 585, 856
+// / 1124; 700 x 20 (120 machines), where the LDS holds three lane waves, at
+// 400000 rows 3548 / 7136; 1000 x 20 (92) at a million 11470 / 15650.  Over
+// 1386 shapes and row counts (1 to 20 stages, 20 to 1000 jobs, up to a million
+// rows) the choice costs 0.4 % on average against the better mapping of each
+// and 23 % at most; with thresholds by row count, and without the two terms of
+// the check and of the stage, it cost 3.2 % and up to twice the time.
 bool lane_eval_auto(int count, int n, int S, int msum, int mmax, int G, const LaneEval& e)
 {
     if (count < 65536) return false;
     constexpr int kCus = 256;
-    const double P = (double)(n + msum + S) * (10.5 + mmax) / G, L = (double)(n + 16) * (msum + 5 * S + 4) / 64.0;
+    const double P = ((double)(n + msum + S) * (10.5 + mmax) + 20.0 * n / S) / G;
+    const double L = (double)(n + 16) * (msum + 6 * S + 4) / 64.0;
     const double w = (double)count / (kWave * kCus);   // waves per CU
     const int full = (int)(w / e.resident), rest = (int)std::ceil(w - (double)full * e.resident);
     const double time = full * e.round + (rest > 0 ? lane_round((rest + 3) / 4) : 0.0);
-    return P * w > (count < 98304 ? 2.0 : count < 163840 ? 1.7 : 1.0) * L * time;
+    return P * w > 1.9 * L * time;
 }
 
 // Chromosomes per wave of the per-stage mapping: one lane per stage, the
