@@ -1946,7 +1946,10 @@ int ffs_best(ffs_ctx* c, int32_t inst, int32_t* out_mk, int32_t* out_gen, int32_
     return FFS_OK;
 }
 
-int ffs_get_population(ffs_ctx* c, int32_t inst, int32_t island, int32_t* genes, int32_t* mk)
+// Aligned, so that the conversion loop's place in its cache lines does not
+// change with the code linked before it (4096 rows of 100 genes 215 to 220 us,
+// 230 to 240 where the function starts at 32 modulo 64).
+__attribute__((aligned(64))) int ffs_get_population(ffs_ctx* c, int32_t inst, int32_t island, int32_t* genes, int32_t* mk)
 {
     int rc = check_bound(c);
     if (rc) return rc;
